@@ -66,7 +66,7 @@ int prof_pair(Ctx* x, int kernel, hipEvent_t* e0, hipEvent_t* e1) {
 static void free_ctx(Ctx* x) {
   drop_events(x);
   void* bufs[] = {x->G, x->gpart, x->part, x->fused_part, x->Xhi, x->Xlo, x->XThi, x->XTlo,
-                  x->XTf, x->HTf, x->VTf, x->ntpart, x->P, x->Pinv, x->syrk_part, x->syrk_tiles, x->V, x->W1, x->Y,
+                  x->HTf, x->VTf, x->Xpk, x->XTpk, x->Vpk, x->pk_apart, x->pk_alpha, x->pk_om, x->P, x->Pinv, x->syrk_part, x->syrk_tiles, x->V, x->W1, x->Y,
                   x->W2, x->cx, x->cgd, x->cr, x->cz, x->cp, x->cq, x->mean, x->omega, x->gbuf, x->ebuf,
                   x->colpart, x->rho, x->bnorm, x->alpha, x->beta, x->relres, x->done,
                   x->redpart, x->status, x->t_dev};
@@ -156,8 +156,10 @@ int firal_profile_end(firal_ctx ctx, double* total_ms, int64_t* launches) {
   return FIRAL_OK;
 }
 
-int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32_t c,
-                 int32_t s_max, int32_t prec, const void* X, const void* H, void* stream) {
+// packed: the context may hold packed operands (gemm_pk.hip) where they apply
+static int create_ctx(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32_t c,
+                      int32_t s_max, int32_t prec, const void* X, const void* H, bool packed,
+                      void* stream) {
   FIRAL_REQ(out != nullptr, "null output pointer");
   *out = nullptr;
   FIRAL_REQ(n_pool >= 1, "n_pool = %lld < 1", (long long)n_pool);
@@ -208,11 +210,18 @@ int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32
     const long long v = atoll(env);
     if (v >= 1 && v < rows) rows = v;
   }
+  // fused tile width in 16-column blocks per wave: FP32 1 (the next row chunk fetched ahead),
+  // bf16x3 2 (its X planes are read once per chunk instead of once per column tile); the
+  // faster of the two measured at configuration 2 for each
+  const char* ncb = getenv("FIRAL_FUSED_MAX_NCB");
+  x->fused_max_ncb = ncb ? (atoi(ncb) == 2 ? 2 : 1) : (prec == FIRAL_BF16X3 ? 2 : 1);
   // bf16x3: chunks start on multiples of 32 rows (the X^T planes are read 8 rows at a time);
-  // the wide FP32 path reads its transposed operands 4 rows at a time from 32-row stages
+  // so are the windows form's of the packed products
   const char* nt_env = getenv("FIRAL_NT");
-  x->use_nt = nt_applies(x) && !(nt_env && atoi(nt_env) == 0);
-  if (prec == FIRAL_BF16X3 || x->use_nt) rows = std::max<int64_t>(32, rows - rows % 32);
+  x->use_pk = packed && prec != FIRAL_F64 && (d > 128 || !fused_covers(x)) &&
+              !(nt_env && atoi(nt_env) == 0);
+  if (prec == FIRAL_BF16X3 || (x->use_pk && pk_windows(prec, d, c)))
+    rows = std::max<int64_t>(32, rows - rows % 32);
   x->chunk_rows = rows;
   const int64_t tiles = tiled_out_tiles(prec, d, sc);
   x->max_splits = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(4096, tiles), 64));
@@ -229,11 +238,6 @@ int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32
 
   const char* unf = getenv("FIRAL_UNFUSED");
   x->force_tiled = x->force_multik = unf && atoi(unf) != 0;
-  // fused tile width in 16-column blocks per wave: FP32 1 (the next row chunk fetched ahead),
-  // bf16x3 2 (its X planes are read once per chunk instead of once per column tile); the
-  // faster of the two measured at configuration 2 for each
-  const char* ncb = getenv("FIRAL_FUSED_MAX_NCB");
-  x->fused_max_ncb = ncb ? (atoi(ncb) == 2 ? 2 : 1) : (prec == FIRAL_BF16X3 ? 2 : 1);
   // BF16X3 PCG: switch to FP32 products below this relative residual (0 = never).  With the
   // residual kept in the projected space the split products converge like FP32 ones, so
   // the switch is off unless asked for.
@@ -263,23 +267,29 @@ int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32
   int rc = FIRAL_OK;
 #define ALLOC(ptr, bytes)                                          \
   if (rc == FIRAL_OK) rc = dmalloc((void**)&(ptr), (size_t)(bytes))
-  ALLOC(x->G, rows * sc * es);
-  ALLOC(x->gpart, std::min<int64_t>(rows, n_pool) * tiled_col_tiles(prec, c, s_max) * 8);
+  PkSizes pk = {};
+  if (x->use_pk) {
+    pk = pk_sizes(x);
+    x->ldn = pk.ldn;
+    ALLOC(x->Xpk, pk.x);
+    ALLOC(x->XTpk, pk.xt);
+    ALLOC(x->HTf, pk.ht);
+    ALLOC(x->Vpk, pk.v);
+    ALLOC(x->pk_apart, pk.apart);
+    ALLOC(x->pk_alpha, pk.alpha);
+    ALLOC(x->pk_om, pk.om);
+  }
+  ALLOC(x->G, std::max<size_t>(rows * sc * es, pk.g));
+  ALLOC(x->gpart, std::max<size_t>(
+                      std::min<int64_t>(rows, n_pool) * tiled_col_tiles(prec, c, s_max) * 8,
+                      pk.dpart));
   ALLOC(x->part, (int64_t)x->max_splits * blk * es);
   ALLOC(x->fused_part, x->fused_part_elems * 4);
   ALLOC(x->P, (int64_t)c * d * d * 8);
   ALLOC(x->Pinv, (int64_t)c * d * d * 8);
   ALLOC(x->syrk_part, (int64_t)x->syrk_splits * c * d * d * es);
   ALLOC(x->syrk_tiles, syrk_tiles.size() * sizeof(int32_t));
-  if (x->use_nt) {
-    x->ldn = nt_ld(x->N);
-    const int64_t ldg = nt_ld(rows), nw = nt_windows(c);
-    if (prec == FIRAL_F32) ALLOC(x->XTf, x->ldn * d * 4);
-    ALLOC(x->HTf, x->ldn * c * 4);
-    if (prec != FIRAL_BF16X3) ALLOC(x->VTf, blk * 4);
-    ALLOC(x->ntpart, ((int64_t)s_max * nw * ldg + (int64_t)s_max * ldg) * 4);
-  }
-  if (prec == FIRAL_BF16X3) {
+  if (prec == FIRAL_BF16X3 && !x->use_pk) {
     // hi/lo planes of V^T for two probe blocks (the gradient's U and W; products use the first)
     ALLOC(x->VTf, blk * 8);
     x->ldt = cdiv(x->N, 8) * 8;
@@ -335,19 +345,26 @@ int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32
     if (hipMemsetAsync(x->status, 0, sizeof(Status), st) != hipSuccess ||
         hipMemcpyAsync(x->syrk_tiles, syrk_tiles.data(), syrk_tiles.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice, st) != hipSuccess ||
-        (prec == FIRAL_BF16X3 && split_x_launch(x, st) != FIRAL_OK) ||
-        (x->use_nt && nt_prepare_ctx(x, st) != FIRAL_OK) ||
+        (x->Xhi && split_x_launch(x, st) != FIRAL_OK) ||
+        (x->use_pk && pk_prepare_ctx(x, st) != FIRAL_OK) ||
         hipStreamSynchronize(st) != hipSuccess) {
       set_error("status initialisation failed");
       rc = FIRAL_EHIP;
     }
   }
   if (rc != FIRAL_OK) {
+    const bool retry = rc == FIRAL_ENOMEM && x->use_pk;
     free_ctx(x);
-    return rc;
+    // a problem whose packed copies do not fit beside it runs on the row-tiled kernels
+    return retry ? create_ctx(out, n_pool, n_lab, d, c, s_max, prec, X, H, false, stream) : rc;
   }
   *out = reinterpret_cast<firal_ctx>(x);
   return FIRAL_OK;
+}
+
+int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32_t c,
+                 int32_t s_max, int32_t prec, const void* X, const void* H, void* stream) {
+  return create_ctx(out, n_pool, n_lab, d, c, s_max, prec, X, H, true, stream);
 }
 
 int firal_destroy(firal_ctx ctx) {
@@ -365,7 +382,8 @@ int firal_hvp(firal_ctx ctx, const double* omega, int64_t n_rows, double shift, 
   FIRAL_REQ(B != out, "out must not alias B");
   FIRAL_REQ(n_rows >= 0 && n_rows <= x->N, "n_rows = %lld outside [0, %lld]", (long long)n_rows,
             (long long)x->N);
-  return hvp_launch(x, omega, n_rows, shift, B, out, s, skip_none(), (hipStream_t)stream);
+  return hvp_launch(x, omega, n_rows, shift, B, out, s, skip_none(), (hipStream_t)stream, false,
+                    true);
 }
 
 int firal_build_precond(firal_ctx ctx, const double* omega, double shift, double* L, double* Pinv,

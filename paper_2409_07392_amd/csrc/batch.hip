@@ -92,9 +92,9 @@ int autotune(Ctx* x, int s, hipStream_t st, int* choice_out) {
   }
   FIRAL_CHECK(probes_launch(x, 1, 1, s, x->V, st));
   // product: the default path (the fused kernel's first tiling where its plan fits, else the
-  // wide or row-tiled kernels the context chose), the other fused tilings whose plans fit
+  // plane or row-tiled products of the context), the other fused tilings whose plans fit
   // (distinct plans only: the row ranges are capped by the row chunks), then the row-tiled
-  // kernels
+  // kernels unless the context takes the plane products
   std::vector<int> cands{0};
   std::vector<std::pair<int, int>> plans;   // (column blocks per wave, row ranges)
   for (int ncb_bit = 0; ncb_bit <= 4; ncb_bit += 4)
@@ -108,7 +108,7 @@ int autotune(Ctx* x, int s, hipStream_t st, int* choice_out) {
       plans.push_back(key);
       if (bits != 0) cands.push_back(bits);
     }
-  cands.push_back(1);
+  if (!x->use_pk) cands.push_back(1);
   double best = 0.0;
   int prod = cands[0];
   for (size_t v = 0; v < cands.size(); ++v) {

@@ -101,15 +101,21 @@ struct Ctx {
   void* XTlo;
   int64_t ldt;
 
-  // wide FP32 path (gemm_nt.hip; d > 128, d % 4 == 0, c > 128): X^T (d x ldn) and H^T
-  // (c x ldn) in FP32, ldn = N rounded up to a multiple of 4 (padding zero), made at creation;
-  // the transposed probe block (s_max c x d); per chunk alpha partials, alpha and omega
-  int use_nt;
-  int64_t ldn;
-  void* XTf;
-  void* HTf;
+  // bf16x3 contexts: hi/lo planes of V^T for two probe blocks (the row-tiled kernels)
   void* VTf;
-  void* ntpart;
+
+  // packed-operand products (gemm_pk.hip; FP32 and bf16x3 contexts the fused kernels do not
+  // cover): X, X^T and H^T (c x ldn) in the order of that file, made at creation; the packed probe
+  // blocks of a call; per chunk the partial sums of alpha, alpha and the row weights
+  int use_pk;
+  int64_t ldn;
+  void* Xpk;
+  void* XTpk;
+  void* HTf;
+  void* Vpk;
+  double* pk_apart;
+  float* pk_alpha;
+  float* pk_om;
 
   // preconditioner
   double* P;            // c * d * d: blocks, factorised in place
@@ -330,19 +336,21 @@ struct FusedPlan {
   int64_t part_elems;   // n_splits * d * s * c
 };
 bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise = false);
+// whether the context's products fit the fused kernel (its plan for s_max probes)
+bool fused_covers(const Ctx* x);
 template <typename T>
 int reduce_parts_launch(const T* part, int64_t n, int P, double shift, const T* B, T* out,
                         Skip skip, hipStream_t st);
-// hi/lo bf16 planes of V^T, (s c) x d, for a probe block B (d x s c, row-major), split once
-int nt3_split_vt(const float* B, int d, int SC, __bf16* VTh, __bf16* VTl, hipStream_t st);
 int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_rows, double shift,
                      const float* B, float* out, int s, Skip skip, hipStream_t st);
 
 // ------------------------------------------------- host-side launchers
 // All enqueue on `st`; `skip` (see Skip) makes every kernel of the call return at once.
-// precise: in a BF16X3 context, take the FP32 products for this call (mixed-precision PCG)
+// precise: in a BF16X3 context, take the FP32 products for this call (mixed-precision PCG);
+// entry: a call of firal_hvp itself, not of a solve
 int hvp_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const void* B,
-               void* out, int s, Skip skip, hipStream_t st, bool precise = false);
+               void* out, int s, Skip skip, hipStream_t st, bool precise = false,
+               bool entry = false);
 // Gram blocks, then P^-1 into x->Pinv; the factor L goes to x->P only when want_l (for d <= 256
 // x->P otherwise keeps the Gram blocks)
 int precond_launch(Ctx* x, const double* omega, double shift, hipStream_t st, bool want_l = false);
@@ -371,13 +379,20 @@ int pcg_launch(Ctx* x, const double* omega, double shift, const double* Pinv, co
                void* Xsol, int s, double tol, int max_iter, uint32_t flags, int slot,
                hipStream_t st);
 int grad_launch(Ctx* x, const void* U, const void* W, int s, double* g, hipStream_t st);
-// wide FP32 path (gemm_nt.hip)
-bool nt_applies(const Ctx* x);
-int64_t nt_ld(int64_t rows);
-int nt_windows(int c);
-int nt_prepare_ctx(Ctx* x, hipStream_t st);
-int hvp_nt_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const float* B,
-                  float* out, int s, Skip skip, hipStream_t st);
+// packed-operand products (gemm_pk.hip): whether a shape takes the windows form of the row step,
+// buffer sizes in bytes (ldn: leading dimension of H^T) for the context's chunk_rows, the packed
+// operands of a context, the product (entry: a call of firal_hvp itself) and the gradient
+bool pk_windows(int prec, int d, int c);
+struct PkSizes {
+  int64_t ldn;
+  size_t x, xt, ht, v, g, apart, alpha, om, dpart;
+};
+PkSizes pk_sizes(const Ctx* x);
+int pk_prepare_ctx(Ctx* x, hipStream_t st);
+int hvp_pk_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const float* B,
+                  float* out, int s, bool entry, Skip skip, hipStream_t st);
+bool grad_pk_applies(const Ctx* x);
+int grad_pk_launch(Ctx* x, const float* U, const float* W, int s, double* g, hipStream_t st);
 // general (any d, c) product through the row-tiled kernels of tiled.hip
 int hvp_tiled_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const void* B,
                      void* out, int s, Skip skip, hipStream_t st, bool precise);

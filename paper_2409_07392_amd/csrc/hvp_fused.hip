@@ -841,6 +841,11 @@ bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise)
   return true;
 }
 
+bool fused_covers(const Ctx* x) {
+  FusedPlan p;
+  return fused_plan(x, x->s_max, x->N, &p);
+}
+
 int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_rows, double shift,
                      const float* B, float* out, int s, Skip skip, hipStream_t st) {
   FusedKernel k = (FusedKernel)p.kernel;

@@ -672,6 +672,39 @@ __global__ __launch_bounds__(256, 2) void k_xtg(
   }
 }
 
+// hi/lo bf16 planes of the transpose of an rows x cols row-major FP32 source: dst[j][i] for the
+// cols x rows destination (leading dimension rows).
+__global__ __launch_bounds__(256) void k_transpose_split(const float* __restrict__ src,
+                                                             int64_t rows, int64_t cols,
+                                                             __bf16* __restrict__ dh,
+                                                             __bf16* __restrict__ dl) {
+  __shared__ float tile[32][33];
+  const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int q = ty; q < 32; q += 8) {
+    const int64_t i = i0 + q, j = j0 + tx;
+    tile[q][tx] = (i < rows && j < cols) ? src[i * cols + j] : 0.f;
+  }
+  __syncthreads();
+  for (int q = ty; q < 32; q += 8) {
+    const int64_t j = j0 + q, i = i0 + tx;
+    if (j < cols && i < rows) {
+      const float v = tile[tx][q];
+      const __bf16 h = (__bf16)v;
+      dh[j * rows + i] = h;
+      dl[j * rows + i] = (__bf16)(v - (float)h);
+    }
+  }
+}
+
+// the planes of V^T ((s c) x d) of a probe block B (d x s c)
+int split_vt(const float* B, int d, int SC, __bf16* VTh, __bf16* VTl, hipStream_t st) {
+  dim3 grid((unsigned)cdiv(d, 32), (unsigned)cdiv(SC, 32));
+  k_transpose_split<<<grid, 256, 0, st>>>(B, d, SC, VTh, VTl);
+  FIRAL_LAUNCHED();
+  return FIRAL_OK;
+}
+
 // g_r = -(1/s) sum over column tiles (in order) of the tile's row dot product.
 __global__ __launch_bounds__(256) void k_grad_sum(const double* __restrict__ dpart, int64_t R,
                                                   int ntiles, int s, double* __restrict__ g) {
@@ -814,7 +847,7 @@ static int hvp_tiled_t(Ctx* x, const double* omega, int64_t n_rows, double shift
   if constexpr (BF3) {
     Vh = (__bf16*)x->VTf;
     Vl = Vh + (int64_t)SC * d;
-    if (n_rows > 0) FIRAL_CHECK(nt3_split_vt((const float*)B, d, SC, Vh, Vl, st));
+    if (n_rows > 0) FIRAL_CHECK(split_vt((const float*)B, d, SC, Vh, Vl, st));
   }
 
   for (int64_t r0 = 0; r0 < n_rows; r0 += x->chunk_rows) {
@@ -868,8 +901,8 @@ static int grad_tiled_t(Ctx* x, const T* U, const T* W, int s, double* g, hipStr
     Uh = Wl + SC * d;
     Ul = Uh + SC * d;
     if (x->n_pool > 0) {
-      FIRAL_CHECK(nt3_split_vt((const float*)W, d, (int)SC, Wh, Wl, st));
-      FIRAL_CHECK(nt3_split_vt((const float*)U, d, (int)SC, Uh, Ul, st));
+      FIRAL_CHECK(split_vt((const float*)W, d, (int)SC, Wh, Wl, st));
+      FIRAL_CHECK(split_vt((const float*)U, d, (int)SC, Uh, Ul, st));
     }
   }
   for (int64_t r0 = 0; r0 < x->n_pool; r0 += x->chunk_rows) {
@@ -898,6 +931,7 @@ int grad_launch(Ctx* x, const void* U, const void* W, int s, double* g, hipStrea
       return FIRAL_OK;
     }
   }
+  if (grad_pk_applies(x)) return grad_pk_launch(x, (const float*)U, (const float*)W, s, g, st);
   if (x->prec == FIRAL_F64)
     return grad_tiled_t<double, false>(x, (const double*)U, (const double*)W, s, g, st);
   if (x->prec == FIRAL_BF16X3)
