@@ -61,7 +61,7 @@ constexpr int kPkT = 128;             // rows and columns of a first-contraction
 constexpr int kPkMaxWaves = 8;        // waves of a second-contraction workgroup
 
 enum PkArith { kPkF32 = 0, kPkB2 = 1, kPkX3 = 2 };
-enum PkMode { kPkFlat = 0, kPkWin = 1, kPkDot = 2 };
+enum PkMode { kPkFlat = 0, kPkWin = 1, kPkDot = 2, kPkFlatX = 3 };
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -69,14 +69,17 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 template <int AR> constexpr int pk_parts() { return AR == kPkX3 ? 3 : 2; }
 
 // Workgroup b of n runs on XCD b % 8; give each XCD a contiguous range of logical tiles.
-__device__ __forceinline__ int64_t pk_lid(int64_t b, int64_t n) {
-  const int64_t q = n >> 3, r = n & 7, x = b & 7, i = b >> 3;
+__device__ __forceinline__ unsigned pk_lid(unsigned b, unsigned n) {
+  const unsigned q = n >> 3, r = n & 7, x = b & 7, i = b >> 3;
   return x * q + (x < r ? x : r) + i;
 }
 
 // Row (within its group of 32) at position pos: FP32 flat 16 b + 4 v + g, FP32 windows the
 // position itself, bf16x3 8 g + 4 b + v, for pos = 16 b + 4 g + v.
 enum PkOrder { kPkRowQ = 0, kPkRowId = 1, kPkRow8 = 2 };
+template <int AR, bool WIN> constexpr int pk_order() {
+  return AR == kPkB2 ? kPkRow8 : WIN ? kPkRowId : kPkRowQ;
+}
 __host__ __device__ __forceinline__ int pk_row(int order, int pos) {
   const int b = pos >> 4, g = (pos >> 2) & 3, v = pos & 3;
   return order == kPkRowQ ? 16 * b + 4 * v + g : order == kPkRowId ? pos : 8 * g + 4 * b + v;
@@ -126,49 +129,72 @@ __device__ __forceinline__ void pk_operand(const f4 (&raw)[2], f4 (&o)[pk_parts<
   }
 }
 
-// One 32-deep stage of a wave: MI row blocks (registers) times the tile's eight column blocks (LDS,
-// [block][part][1 KB]), two column blocks at a time so that 2 MI independent products stand between
-// two that share an accumulator.
-template <int AR, int MI>
-__device__ __forceinline__ void pk_stage(const f4 (&a)[MI][pk_parts<AR>()],
-                                         const float* __restrict__ b, int lane,
-                                         f32x4 (&acc)[MI][8]) {
-  constexpr int P = pk_parts<AR>();
+// An operand's values with those of rows at or beyond lim cleared (row(u): row of value u): eight
+// bf16 or four FP32.
+template <bool BF, typename F>
+__device__ __forceinline__ f4 pk_keep(f4 x, int lim, F row) {
+  if constexpr (BF) {
 #pragma unroll
-  for (int j = 0; j < 8; j += 2) {
-    f4 bv[2][P];
+    for (int w = 0; w < 4; ++w) {
+      const unsigned m =
+          (row(2 * w) < lim ? 0xFFFFu : 0u) | (row(2 * w + 1) < lim ? 0xFFFF0000u : 0u);
+      x[w] = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, (float)x[w]) & m);
+    }
+  } else {
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int v = 0; v < 4; ++v) x[v] = row(v) < lim ? x[v] : 0.f;
+  }
+  return x;
+}
+
+// A unit of a stage: the wave's MI row blocks (a, registers) times UJ column blocks (b, registers).
+// Every accumulator takes its products in the order of k (bf16: x_0 y_0, x_0 y_1, x_1 y_0 in
+// kPkB2, the smallest first in kPkX3); the MI UJ accumulators take turns.
+template <int AR, int MI, int UJ>
+__device__ __forceinline__ void pk_unit(const f4 (&a)[MI][pk_parts<AR>()],
+                                        const f4 (&b)[UJ][pk_parts<AR>()], int j0,
+                                        f32x4 (&acc)[MI][8]) {
+  if constexpr (AR == kPkF32) {
 #pragma unroll
-      for (int p = 0; p < P; ++p)
-        bv[q][p] = *reinterpret_cast<const f4*>(b + ((j + q) * P + p) * 256 + lane * 4);
-    if constexpr (AR == kPkF32) {
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-              acc[i][j + q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][h][e], bv[q][h][e],
-                                                                   acc[i][j + q], 0, 0, 0);
-    } else {
-      // plane pairs: bf16x3 x_0 y_0, x_0 y_1, x_1 y_0; three planes smallest first
-      constexpr int n = AR == kPkB2 ? 3 : 6;
-      constexpr int pa[6] = {AR == kPkB2 ? 0 : 2, 0, 1, 1, 0, 0};
-      constexpr int pb[6] = {0, AR == kPkB2 ? 1 : 2, AR == kPkB2 ? 0 : 1, 0, 1, 0};
-#pragma unroll
-      for (int t = 0; t < n; ++t)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
+        for (int q = 0; q < UJ; ++q)
 #pragma unroll
           for (int i = 0; i < MI; ++i)
-            acc[i][j + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, a[i][pa[t]]), __builtin_bit_cast(bf16x8, bv[q][pb[t]]),
-                acc[i][j + q], 0, 0, 0);
-    }
+            acc[i][j0 + q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][h][e], b[q][h][e],
+                                                                  acc[i][j0 + q], 0, 0, 0);
+  } else {
+    constexpr int n = AR == kPkB2 ? 3 : 6;
+    constexpr int pa[6] = {AR == kPkB2 ? 0 : 2, 0, 1, 1, 0, 0};
+    constexpr int pb[6] = {0, AR == kPkB2 ? 1 : 2, AR == kPkB2 ? 0 : 1, 0, 1, 0};
+#pragma unroll
+    for (int t = 0; t < n; ++t)
+#pragma unroll
+      for (int q = 0; q < UJ; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          acc[i][j0 + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, a[i][pa[t]]), __builtin_bit_cast(bf16x8, b[q][pb[t]]),
+              acc[i][j0 + q], 0, 0, 0);
   }
+}
+
+// The LDS stage buffers of both kernels: one is read, the next is complete, the third is written, so
+// that a unit's operands are read from LDS a unit ahead, across the stage barrier too.
+constexpr int kPkBufs = 3;
+template <int AR> constexpr int pk_buf() { return 8 * pk_parts<AR>() * 256; }   // floats
+
+template <int AR, int UJ>
+__device__ __forceinline__ void pk_read(f4 (&b)[UJ][pk_parts<AR>()], const float* buf, int j0,
+                                        int lane) {
+  constexpr int P = pk_parts<AR>();
+#pragma unroll
+  for (int q = 0; q < UJ; ++q)
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      b[q][p] = *reinterpret_cast<const f4*>(buf + ((j0 + q) * P + p) * 256 + lane * 4);
 }
 
 // Keeps the compiler's scheduler from moving instructions across this point: the next stage's
@@ -183,12 +209,28 @@ __device__ __forceinline__ double row16_sum(double v) {
   v = dpp_add<0x140, 0xF, 0xF>(v);   // row_mirror
   return v;
 }
-__device__ __forceinline__ float row16_sum_xor(float s) {
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
-  s += __shfl_xor(s, 4, 64);
-  s += __shfl_xor(s, 8, 64);
-  return s;
+// One step of a sum over lanes that halves the lane's 2 N values: it keeps the half its bit `up`
+// selects and adds its partner's values of that half (the partner, by CTRL, has the other bit).
+template <int N, int CTRL>
+__device__ __forceinline__ void half_step(double (&t)[8], bool up) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double keep = up ? t[N + i] : t[i], send = up ? t[i] : t[N + i];
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(send), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(send), CTRL, 0xF, 0xF, true);
+    t[i] = keep + __hiloint2double(hi, lo);
+  }
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_add_f(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                                           0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float row16_sum_f(float v) {
+  v = dpp_add_f<0xB1>(v);
+  v = dpp_add_f<0x4E>(v);
+  v = dpp_add_f<0x141>(v);
+  return dpp_add_f<0x140>(v);
 }
 
 // Column tile ct: its first column and its width.  Windows: tile ct is window ct / s of probe
@@ -200,7 +242,7 @@ struct PkCols {
   }
   __device__ __forceinline__ void tile(int ct, int& n0, int& width) const {
     if (nw) {
-      const int w = ct / s, p = ct - w * s, col0 = w * kPkT;
+      const int w = (int)((unsigned)ct / (unsigned)s), p = ct - w * s, col0 = w * kPkT;
       n0 = p * c + col0;
       width = c - col0 < kPkT ? c - col0 : kPkT;
     } else {
@@ -218,7 +260,7 @@ constexpr int kPkSegC = 64;          // probes narrower than this are summed thr
 
 template <int AR, int MODE>
 constexpr size_t pk_xv_lds() {
-  const size_t main_b = (size_t)2 * 8 * pk_parts<AR>() * 1024;
+  const size_t main_b = (size_t)kPkBufs * pk_buf<AR>() * 4;
   const size_t seg_b = MODE == kPkFlat ? (size_t)4 * 16 * kPkSegLd * 4 : 0;
   return main_b > seg_b ? main_b : seg_b;
 }
@@ -229,30 +271,28 @@ constexpr size_t pk_xv_lds() {
 // kPkDot: dpart[ct][row] = sum over the tile's columns of G_u (G - alpha) h, G and alpha those of
 // the earlier kPkFlat call on W.
 template <int AR, int MODE>
-__global__ __launch_bounds__(256, 2) void k_pk_xv(
+__global__ __launch_bounds__(256, AR == kPkX3 ? 2 : 3) void k_pk_xv(
     const float* __restrict__ Xp, int nkb, int64_t R, const float* __restrict__ Vp, PkCols cols,
-    int order, const float* __restrict__ HT, int64_t ldh, const double* __restrict__ omega,
+    const float* __restrict__ HT, int64_t ldh, const double* __restrict__ omega,
     float* __restrict__ G, int64_t nrb, double* __restrict__ apart, int64_t ldb,
     const float* __restrict__ alpha, double* __restrict__ dpart, Skip skip) {
   if (skip_now(skip)) return;
   extern __shared__ __align__(16) unsigned char pk_lds[];
-  float* Bs = reinterpret_cast<float*>(pk_lds);   // [2][8][parts][1 KB]
-  constexpr int P = pk_parts<AR>();
-  constexpr int kBuf = 8 * P * 256;               // floats per buffer
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float* Bs = reinterpret_cast<float*>(pk_lds);   // [3][8][parts][1 KB]
+  constexpr int P = pk_parts<AR>(), kBuf = pk_buf<AR>();
+  constexpr int order = pk_order<AR, MODE == kPkWin>();
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, g = lane >> 4;
-  const int nct = cols.tiles(), c = cols.c, SC = cols.SC;
+  const int nct = cols.tiles(), c = cols.c;
   // tiles in groups of 8 row tiles: consecutive logical ids take the 8 row tiles of a group for
   // one column tile, then the next column tile, so that the workgroups resident on one XCD share
   // 8 tiles of X and a few of V in its L2 (the last group may hold fewer row tiles)
-  const int64_t lid = pk_lid(blockIdx.x, gridDim.x);
-  const int64_t nrt = (R + kPkT - 1) / kPkT;
-  const int64_t grp = lid / (8 * (int64_t)nct);
-  const int64_t g0 = grp * 8;
-  const int64_t gsz = nrt - g0 < 8 ? nrt - g0 : 8;
-  const int64_t in = lid - grp * 8 * (int64_t)nct;
-  const int ct = (int)(in / gsz);
-  const int64_t rt = g0 + (in - (int64_t)ct * gsz);
+  const unsigned lid = pk_lid(blockIdx.x, gridDim.x), nrt = (unsigned)((R + kPkT - 1) / kPkT);
+  const unsigned grp = lid / (8u * nct), in = lid - grp * 8u * nct;
+  const unsigned gsz = nrt - grp * 8 < 8 ? nrt - grp * 8 : 8;
+  const int ct = (int)(gsz == 8 ? in >> 3 : in / gsz);
+  const int64_t rt = grp * 8 + (in - (unsigned)ct * gsz);
   const int64_t row0 = rt * kPkT + 32 * wave;
 
   f32x4 acc[2][8];
@@ -261,71 +301,146 @@ __global__ __launch_bounds__(256, 2) void k_pk_xv(
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const float* xw = Xp + (row0 >> 4) * nkb * 512 + lane * 4;
-  const float* vt = Vp + (int64_t)ct * nkb * kBuf + tid * 4;
-  f4 a[2][P], an[2][2], bn[2 * P];
-  auto load_a = [&](int kb) {
+  // uniform bases: the lane's share of an address is a constant 32-bit offset
+  const float* xw = Xp + (row0 >> 4) * nkb * 512;
+  const float* vt = Vp + (int64_t)ct * nkb * kBuf;
+  f4 bn[2 * P], bu[2][2][P];
+  auto load_a = [&](f4 (&r)[2][2], int kb) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        an[i][h] = *reinterpret_cast<const f4*>(xw + ((int64_t)i * nkb + kb) * 512 + h * 256);
+        r[i][h] = reinterpret_cast<const f4*>(xw + ((int64_t)i * nkb + kb) * 512 + h * 256)[lane];
   };
   auto load_b = [&](int kb) {
 #pragma unroll
     for (int t = 0; t < 2 * P; ++t)
-      bn[t] = *reinterpret_cast<const f4*>(vt + (int64_t)kb * kBuf + t * 1024);
+      bn[t] = reinterpret_cast<const f4*>(vt + (int64_t)kb * kBuf + t * 1024)[tid];
   };
   auto store_b = [&](int buf) {
 #pragma unroll
     for (int t = 0; t < 2 * P; ++t)
       *reinterpret_cast<f4*>(Bs + buf * kBuf + t * 1024 + tid * 4) = bn[t];
   };
-  load_a(0);
+  const int last = nkb - 1;
+  // past the last stage the loads repeat it into buffers whose values are not used
+  int rd = 0, nx = 1, wr = 2;
+  // one stage with the operand a; the next stage's raw operand is loaded into r
+  auto stage = [&](const f4 (&a)[2][P], f4 (&r)[2][2], int kb) {
+    const float* b = Bs + rd * kBuf;
+    load_a(r, kb < last ? kb + 1 : last);
+    load_b(kb + 2 <= last ? kb + 2 : last);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u == 3) store_b(wr);
+      if (u < 3)
+        pk_read<AR, 2>(bu[(u + 1) & 1], b, 2 * u + 2, lane);
+      else
+        pk_read<AR, 2>(bu[0], Bs + nx * kBuf, 0, lane);
+      pk_order_fence();
+      pk_unit<AR, 2, 2>(a, bu[u & 1], 2 * u, acc);
+      pk_order_fence();
+    }
+    const int t = rd;
+    rd = nx;
+    nx = wr;
+    wr = t;
+    __syncthreads();
+  };
+  f4 r0[2][2];
+  load_a(r0, 0);
   load_b(0);
   store_b(0);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) pk_operand<AR>(an[i], a[i]);
+  load_b(last > 0 ? 1 : 0);
+  store_b(1);
   __syncthreads();
-  for (int kb = 0; kb < nkb; ++kb) {
-    const int nx = kb + 1 < nkb ? kb + 1 : kb;   // the last pass reloads its own stage
-    load_a(nx);
-    load_b(nx);
-    pk_order_fence();
-    pk_stage<AR, 2>(a, Bs + (kb & 1) * kBuf, lane, acc);
-    pk_order_fence();
-    store_b((kb & 1) ^ 1);
+  pk_read<AR, 2>(bu[0], Bs, 0, lane);
+  if constexpr (AR == kPkX3) {
+    f4 a[2][P];
+    for (int kb = 0; kb < nkb; ++kb) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) pk_operand<AR>(an[i], a[i]);
-    __syncthreads();
+      for (int i = 0; i < 2; ++i) pk_operand<AR>(r0[i], a[i]);
+      stage(a, r0, kb);
+    }
+  } else {
+    f4 r1[2][2];   // the raw operands are the operands: two sets in turn
+    int kb = 0;
+    for (; kb + 1 < nkb; kb += 2) {
+      stage(r0, r1, kb);
+      stage(r1, r0, kb + 1);
+    }
+    if (kb < nkb) stage(r0, r1, kb);
   }
 
   // Epilogue.  Lane (g, li) of block (i, j) holds positions row0 + 16 i + 4 g + v, v = 0..3, of
-  // column n0 + 16 j + li of the tile.  Columns beyond the tile's width read its first column; their
-  // G is zero.
+  // column n0 + 16 j + li of the tile.  Columns beyond the tile's width have zero G.  Positions beyond the call's rows hold other rows' values or zero: the second kernel
+  // clears them.  Every load is issued before the first is used.  VALU work here competes with the
+  // other workgroup's MFMAs for issue, so the sums use as few operations as their order allows.
   int n0, width;
   cols.tile(ct, n0, width);
-  float* gt = G + ((int64_t)ct * nrb + (row0 >> 4)) * 2048 + lane * 4;
+  float* gt = G + ((int64_t)ct * nrb + (row0 >> 4)) * 2048;   // uniform
+  // probe and class of the tile's first column, and the last probe
+  const int p_lo = (int)((unsigned)n0 / (unsigned)c), k_lo = n0 - p_lo * c;
+  const int p_hi = (int)((unsigned)(n0 + width - 1) / (unsigned)c);
+  f4 h[2][8];
+  const float* hp[8];
+  int pj[8];   // probe of the lane's column (kPkDot)
+  {
+    const float* h0 = HT + row0 + 4 * g;
+    unsigned k = k_lo + li;   // class of the lane's column, counted on past the tile's width
+    int p = p_lo;
+    if (c < kPkSegC) {
+      p += k / (unsigned)c;
+      k %= (unsigned)c;
+    } else {
+      p += k >= (unsigned)c;
+      k = min(k, k - c);   // k - c wraps to a large value below c
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      pj[j] = MODE == kPkDot ? min(p, cols.s - 1) : 0;
+      hp[j] = reinterpret_cast<const float*>(reinterpret_cast<const char*>(h0) +
+                                             (uint64_t)k * (unsigned)(4 * ldh));
+      if constexpr (MODE != kPkDot) {
+        h[0][j] = *reinterpret_cast<const f4*>(hp[j]);
+        h[1][j] = *reinterpret_cast<const f4*>(hp[j] + 16);
+      }
+      k += 16;
+      if (c < 16) {
+        p += k / (unsigned)c;
+        k %= (unsigned)c;
+      } else {
+        p += k >= (unsigned)c;
+        k = min(k, k - c);
+      }
+    }
+  }
   if constexpr (MODE == kPkDot) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int64_t pos = row0 + 16 * i + 4 * g;
-      f4 e[8], h[8], al[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int n = n0 + (16 * j + li < width ? 16 * j + li : 0), p = n / c;
-        e[j] = *reinterpret_cast<const f4*>(gt + (i * 8 + j) * 256);
-        h[j] = *reinterpret_cast<const f4*>(HT + (int64_t)(n - p * c) * ldh + pos);
-        al[j] = *reinterpret_cast<const f4*>(alpha + (int64_t)p * ldb + pos);
-      }
+      const float* ap = alpha + row0 + 16 * i + 4 * g;
       double t[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
+      for (int j0 = 0; j0 < 8; j0 += 4) {   // four columns' loads at a time (registers)
+        f4 e[4], al[4], hv[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float x = acc[i][j][v] * ((e[j][v] - al[j][v]) * h[j][v]);
-          t[v] += 16 * j + li < width ? (double)x : 0.0;
+        for (int q = 0; q < 4; ++q) {
+          e[q] = reinterpret_cast<const f4*>(gt + (i * 8 + j0 + q) * 256)[lane];
+          hv[q] = *reinterpret_cast<const f4*>(hp[j0 + q] + 16 * i);
+          al[q] = *reinterpret_cast<const f4*>(
+              reinterpret_cast<const char*>(ap) + (uint64_t)(unsigned)pj[j0 + q] * (unsigned)(4 * ldb));
         }
+        pk_order_fence();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (16 * (j0 + q) >= width) continue;   // uniform
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float x = acc[i][j0 + q][v] * ((e[q][v] - al[q][v]) * hv[q][v]);
+            t[v] += (double)(16 * (j0 + q) + li < width ? x : 0.f);
+          }
+        }
+      }
 #pragma unroll
       for (int v = 0; v < 4; ++v) t[v] = row16_sum(t[v]);
       if (li == 0) {
@@ -338,88 +453,111 @@ __global__ __launch_bounds__(256, 2) void k_pk_xv(
     }
     return;
   } else {
-    const int p_lo = n0 / c, p_hi = (n0 + width - 1) / c;   // probes the tile touches
+    if constexpr (MODE == kPkWin) {
+      float om[2][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int64_t pos = row0 + 16 * i + 4 * g;
-      float om[4];
-      bool in_r[4];
-      f4 h[8];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t r = row0 + pk_row(order, 16 * i + 4 * g + v);
-        in_r[v] = r < R;
-        om[v] = MODE == kPkWin && omega ? (float)omega[r < R ? r : 0] : 1.f;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int n = n0 + (16 * j + li < width ? 16 * j + li : 0);
-        h[j] = *reinterpret_cast<const f4*>(HT + (int64_t)(n % c) * ldh + pos);
-      }
-      // rows beyond the call's rows are stored as zero; G is non-temporal: a chunk's G is read back
-      // by the second kernel from HBM, and should not evict X, V and h from L2
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          if constexpr (MODE == kPkWin) acc[i][j][v] *= om[v];
-          acc[i][j][v] = in_r[v] ? acc[i][j][v] : 0.f;
+          const int64_t r = row0 + pk_row(order, 16 * i + 4 * g + v);
+          om[i][v] = omega ? (float)omega[r < R ? r : 0] : 1.f;
         }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][j][v] *= om[i][v];
+    }
+    // non-temporal: a chunk's G is read back by the second kernel from HBM, and should not evict X,
+    // V and h from L2
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
         __builtin_nontemporal_store(f4{acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]},
-                                    reinterpret_cast<f4*>(gt + (i * 8 + j) * 256));
-      }
-      if constexpr (MODE == kPkWin) {
-        // FP32 sums over the window's two halves of 64 columns, then their sum
-        const int w = ct / cols.s, p = ct - w * cols.s;
+                                    reinterpret_cast<f4*>(gt + (i * 8 + j) * 256) + lane);
+    if constexpr (MODE == kPkWin) {
+      // FP32 sums over the window's two halves of 64 columns, then their sum
+      const int w = ct / cols.s, p = ct - w * cols.s;
+      double* ap = apart + ((int64_t)p * cols.nw + w) * ldb + row0 + 4 * g;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
         float t[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        if (width == kPkT) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+          for (int j = 0; j < 8; ++j)
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (16 * j + li < width)
-              t[j >> 2][v] = fmaf(acc[i][j][v], in_r[v] ? h[j][v] : 0.f, t[j >> 2][v]);
+            for (int v = 0; v < 4; ++v)
+              t[j >> 2][v] = fmaf(acc[i][j][v], h[i][j][v], t[j >> 2][v]);
+        } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) t[0][v] = row16_sum_xor(t[0][v]) + row16_sum_xor(t[1][v]);
+          for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (16 * j + li < width)
+                t[j >> 2][v] = fmaf(acc[i][j][v], h[i][j][v], t[j >> 2][v]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[0][v] = row16_sum_f(t[0][v]) + row16_sum_f(t[1][v]);
         if (li == 0) {
-          double* ap = apart + ((int64_t)p * cols.nw + w) * ldb + pos;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) ap[v] = (double)t[0][v];
+          for (int v = 0; v < 4; ++v) ap[16 * i + v] = (double)t[0][v];
         }
-      } else if (c >= kPkSegC) {
-        // at most three probes: each summed over the lane's columns, then over the 16 lanes
-        for (int p = p_lo; p <= p_hi; ++p) {
-          const int lo = p * c - n0, hi = min(lo + c, width);   // its columns within the tile
-          double t[4] = {0.0, 0.0, 0.0, 0.0};
+      }
+    } else if (c >= kPkSegC) {
+      // at most three probes: each summed over the lane's columns, then over the 16 lanes.  FP32
+      // products up to c = 128 (kPkFlat), exact ones beyond (kPkFlatX)
+      if constexpr (MODE == kPkFlat) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int m = 16 * j + li;
-            const bool on = m >= lo && m < hi;
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const bool u = on && in_r[v];
-              if (c <= kPkT)
-                t[v] += u ? (double)(acc[i][j][v] * h[j][v]) : 0.0;
-              else
-                t[v] += u ? (double)acc[i][j][v] * (double)h[j][v] : 0.0;
-            }
-          }
+          for (int j = 0; j < 8; ++j)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) t[v] = row16_sum(t[v]);
-          if (li == 0) {
-            double* ap = apart + (int64_t)(ct + p) * ldb + pos;
+            for (int v = 0; v < 4; ++v) acc[i][j][v] *= h[i][j][v];
+      }
+      auto term = [&](int i, int j, int v, float x) {
+        if constexpr (MODE == kPkFlat) return (double)x;
+        float y = h[i][j][v];
+        asm("" : "+v"(x), "+v"(y));   // keeps the conversions inside the probe loop (registers)
+        return (double)x * (double)y;
+      };
+      for (int p = p_lo; p <= p_hi; ++p) {
+        const int lo = p * c - n0, hi = min(lo + c, width);   // its columns within the tile
+        double t[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int v = 0; v < 4; ++v) ap[v] = t[v];
+        for (int j = 0; j < 8; ++j) {
+          // uniform branches: the block lies outside the probe, inside it, or is cut by its edge
+          if (16 * j + 16 <= lo || 16 * j >= hi) continue;
+          if (16 * j >= lo && 16 * j + 16 <= hi) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t[e] += term(e >> 2, j, e & 3, acc[e >> 2][j][e & 3]);
+          } else {
+            const bool on = 16 * j + li >= lo && 16 * j + li < hi;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              t[e] += term(e >> 2, j, e & 3, on ? acc[e >> 2][j][e & 3] : 0.f);
           }
         }
-      } else {
-        // narrow probes: the wave's 16 x 128 products through its own LDS rows (the pipeline
-        // buffers are free after the last barrier), one lane per (row, probe)
-        float* seg = reinterpret_cast<float*>(pk_lds) + wave * 16 * kPkSegLd;
+        // value e = 4 i + v ends in the lanes with li / 2 = e
+        half_step<4, 0x140>(t, (li & 8) != 0);   // row_mirror
+        half_step<2, 0x141>(t, (li & 4) != 0);   // row_half_mirror
+        half_step<1, 0x1B>(t, (li & 2) != 0);    // quad_perm [3,2,1,0]
+        const double sum = dpp_add<0xB1, 0xF, 0xF>(t[0]);
+        if ((li & 1) == 0)
+          apart[(int64_t)(ct + p) * ldb + row0 + 16 * (li >> 3) + 4 * g + ((li >> 1) & 3)] = sum;
+      }
+    } else if constexpr (MODE == kPkFlat) {
+      // narrow probes: 16 x 128 products at a time through the wave's own LDS rows (the pipeline
+      // buffers are free after the last barrier), one lane per (row, probe)
+      float* seg = reinterpret_cast<float*>(pk_lds) + wave * 16 * kPkSegLd;
+      for (int i = 0; i < 2; ++i) {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            seg[(4 * g + v) * kPkSegLd + 16 * j + li] = in_r[v] ? acc[i][j][v] * h[j][v] : 0.f;
+            seg[(4 * g + v) * kPkSegLd + 16 * j + li] =
+                i == 0 ? acc[0][j][v] * h[0][j][v] : acc[1][j][v] * h[1][j][v];
         __builtin_amdgcn_wave_barrier();
         for (int it = lane; it < 16 * (p_hi - p_lo + 1); it += 64) {
           const int rr = it & 15, p = p_lo + (it >> 4);
@@ -442,10 +580,9 @@ __global__ __launch_bounds__(256) void k_pk_alpha(const double* __restrict__ apa
                                                   float* __restrict__ alpha,
                                                   float* __restrict__ omf, Skip skip) {
   if (skip_now(skip)) return;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)cols.s * Rp) return;
-  const int p = (int)(e / Rp);
-  const int64_t pos = e - (int64_t)p * Rp;
+  const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int p = blockIdx.y;
+  if (pos >= Rp) return;
   double a = 0.0;
   if (cols.nw) {
     for (int w = 0; w < cols.nw; ++w) a += apart[((int64_t)p * cols.nw + w) * ldb + pos];
@@ -468,23 +605,23 @@ __global__ __launch_bounds__(256) void k_pk_alpha(const double* __restrict__ apa
 template <int AR, int MI, int TASKS, bool WIN>
 __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     const float* __restrict__ XTp, int nab, int d, const float* __restrict__ G, int64_t nrb,
-    PkCols cols, int order, const float* __restrict__ HT, int64_t ldh,
+    PkCols cols, const float* __restrict__ HT, int64_t ldh,
     const float* __restrict__ alpha, const float* __restrict__ omf, int64_t ldb, int64_t R,
     int64_t rows_per_split, int nmt, float* __restrict__ part, int64_t part_stride, int accumulate,
     Skip skip) {
   if (skip_now(skip)) return;
   extern __shared__ __align__(16) unsigned char pk_lds[];
-  float* Bs = reinterpret_cast<float*>(pk_lds);   // [2][8][parts][1 KB]
-  constexpr int P = pk_parts<AR>();
-  constexpr int kBuf = 8 * P * 256;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NW = blockDim.x >> 6;
+  float* Bs = reinterpret_cast<float*>(pk_lds);   // [3][8][parts][1 KB]
+  constexpr int P = pk_parts<AR>(), kBuf = pk_buf<AR>(), order = pk_order<AR, WIN>();
+  const int tid = threadIdx.x, lane = tid & 63, NW = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, g = lane >> 4;
   const int nct = cols.tiles(), c = cols.c, SC = cols.SC;
-  const int64_t lid = pk_lid(blockIdx.x, gridDim.x);
-  const int mt = (int)(lid % nmt);
-  const int64_t rest = lid / nmt;
-  const int ct = (int)(rest % nct);
-  const int sp = (int)(rest / nct);
+  const unsigned lid = pk_lid(blockIdx.x, gridDim.x);
+  const int mt = nmt == 1 ? 0 : (int)(lid % (unsigned)nmt);
+  const unsigned rest = nmt == 1 ? lid : lid / (unsigned)nmt;
+  const int sp = (int)(rest / (unsigned)nct);
+  const int ct = (int)(rest - (unsigned)sp * nct);
   const int64_t rb = (int64_t)sp * rows_per_split;
   const int64_t re = rb + rows_per_split < R ? rb + rows_per_split : R;
   const int ab0 = (mt * NW + wave) * MI;            // the wave's first 16-row block of the output
@@ -509,17 +646,16 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     hp[t] = HT + (int64_t)(n - p * c) * ldh + 4 * g;
     bp[t] = alpha + (int64_t)p * ldb + 4 * g;
   }
-  const float* gp = G + (int64_t)ct * nrb * 2048 + lane * 4;
+  const float* gp = G + (int64_t)ct * nrb * 2048;   // uniform
   const float* op = omf + 4 * g;
-  f4 a[MI][P], an[MI][2];
   f4 gv[TASKS][2], hv[TASKS][2], bv[TASKS][2], ov[2];
-  auto load_a = [&](int64_t kb) {
+  auto load_a = [&](f4 (&r)[MI][2], int64_t kb) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const int ab = ab0 + i < nab ? ab0 + i : nab - 1;   // clamped blocks: dropped outputs
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        an[i][h] = *reinterpret_cast<const f4*>(XTp + (kb * nab + ab) * 512 + h * 256 + lane * 4);
+        r[i][h] = reinterpret_cast<const f4*>(XTp + (kb * nab + ab) * 512 + h * 256)[lane];
     }
   };
   auto load_g = [&](int64_t kb) {
@@ -528,7 +664,8 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
       if constexpr (!WIN) ov[q] = *reinterpret_cast<const f4*>(op + 32 * kb + 16 * q);
 #pragma unroll
       for (int t = 0; t < TASKS; ++t) {
-        gv[t][q] = *reinterpret_cast<const f4*>(gp + ((2 * kb + q) * 8 + wave + NW * t) * 256);
+        gv[t][q] =
+            reinterpret_cast<const f4*>(gp + ((2 * kb + q) * 8 + wave + NW * t) * 256)[lane];
         hv[t][q] = *reinterpret_cast<const f4*>(hp[t] + 32 * kb + 16 * q);
         bv[t][q] = *reinterpret_cast<const f4*>(bp[t] + 32 * kb + 16 * q);
       }
@@ -536,7 +673,6 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
   };
   // rows at or beyond re (only in the split's last stage) become zero in both operands
   auto store_g = [&](int64_t kb, int buf) {
-    const bool full = 32 * kb + 32 <= re;
 #pragma unroll
     for (int t = 0; t < TASKS; ++t) {
       f4 y[2];
@@ -544,10 +680,15 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          float x = (gv[t][q][v] - bv[t][q][v]) * hv[t][q][v];
-          if constexpr (!WIN) x *= ov[q][v];
-          y[q][v] = full || 32 * kb + pk_row(order, 16 * q + 4 * g + v) < re ? x : 0.f;
+          y[q][v] = (gv[t][q][v] - bv[t][q][v]) * hv[t][q][v];
+          if constexpr (!WIN) y[q][v] *= ov[q][v];
         }
+      if (32 * kb + 32 > re) {
+        const int lim = (int)(re - 32 * kb);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          y[q] = pk_keep<false>(y[q], lim, [&](int v) { return pk_row(order, 16 * q + 4 * g + v); });
+      }
       f4 o[P];
       pk_parts_of<AR>(y, o);
 #pragma unroll
@@ -555,49 +696,78 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
         *reinterpret_cast<f4*>(Bs + buf * kBuf + ((wave + NW * t) * P + p) * 256 + lane * 4) = o[p];
     }
   };
-  auto take_a = [&](int64_t kb) {
-    if (32 * kb + 32 > re) {
+  auto mask_a = [&](f4 (&r)[MI][2], int64_t kb) {
+    if (32 * kb + 32 <= re) return;
+    const int lim = (int)(re - 32 * kb);
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if constexpr (AR == kPkB2) {
-            bf16x8 x = __builtin_bit_cast(bf16x8, an[i][h]);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-              if (32 * kb + pk_row(order, 16 * (u >> 2) + 4 * g + (u & 3)) >= re)
-                x[u] = (__bf16)0.0f;
-            an[i][h] = __builtin_bit_cast(f4, x);
-          } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              if (32 * kb + pk_row(order, 16 * h + 4 * g + v) >= re) an[i][h][v] = 0.f;
-          }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i) pk_operand<AR>(an[i], a[i]);
+      for (int h = 0; h < 2; ++h)
+        r[i][h] = pk_keep<AR == kPkB2>(r[i][h], lim, [&](int u) {
+          return pk_row(order, AR == kPkB2 ? 16 * (u >> 2) + 4 * g + (u & 3) : 16 * h + 4 * g + u);
+        });
   };
-  const int64_t kb0 = rb >> 5, kb1 = re > rb ? (re + 31) >> 5 : kb0;
+  constexpr int UJ = AR == kPkX3 && MI == 3 ? 1 : 2;   // column blocks of a unit, by registers
+  constexpr int NU = 8 / UJ;
+  f4 bu[2][UJ][P], r0[MI][2];
+  const int64_t kb0 = rb >> 5, kb1 = re > rb ? (re + 31) >> 5 : kb0, last = kb1 - 1;
+  auto at = [&](int64_t kb) { return kb < last ? kb : last; };   // past the last stage: it again
   if (kb1 > kb0) {
-    load_a(kb0);
     load_g(kb0);
     store_g(kb0, 0);
-    take_a(kb0);
+    load_g(at(kb0 + 1));
+    store_g(at(kb0 + 1), 1);
+    load_g(at(kb0 + 2));
+    load_a(r0, kb0);
   }
   __syncthreads();
-  const bool live = ab0 < nab;   // wave-uniform
-  for (int64_t kb = kb0; kb < kb1; ++kb) {
-    const int buf = (int)(kb - kb0) & 1;
-    const int64_t nx = kb + 1 < kb1 ? kb + 1 : kb;   // the last pass reloads its own stage
-    load_a(nx);
-    load_g(nx);
-    pk_order_fence();
-    if (live) pk_stage<AR, MI>(a, Bs + buf * kBuf, lane, acc);
-    pk_order_fence();
-    store_g(nx, buf ^ 1);
-    take_a(nx);
+  pk_read<AR, UJ>(bu[0], Bs, 0, lane);
+  const bool live = ab0 < nab;   // uniform
+  int rd = 0, nx = 1, wr = 2;
+  // one stage with the operand a; the next stage's raw operand is loaded into r
+  auto stage = [&](const f4 (&a)[MI][P], f4 (&r)[MI][2], int64_t kb) {
+    const float* b = Bs + rd * kBuf;
+    load_a(r, at(kb + 1));
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      if (u < NU - 1)
+        pk_read<AR, UJ>(bu[(u + 1) & 1], b, UJ * (u + 1), lane);
+      else
+        pk_read<AR, UJ>(bu[0], Bs + nx * kBuf, 0, lane);
+      pk_order_fence();
+      if (live) pk_unit<AR, MI, UJ>(a, bu[u & 1], UJ * u, acc);
+      pk_order_fence();
+      if (u == 0) {   // G' two stages ahead; its next values are loaded as soon as it is stored
+        store_g(at(kb + 2), wr);
+        load_g(at(kb + 3));
+      }
+    }
+    const int t = rd;
+    rd = nx;
+    nx = wr;
+    wr = t;
     __syncthreads();
+  };
+  if constexpr (AR == kPkX3) {
+    f4 a[MI][P];
+    for (int64_t kb = kb0; kb < kb1; ++kb) {
+      mask_a(r0, kb);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) pk_operand<AR>(r0[i], a[i]);
+      stage(a, r0, kb);
+    }
+  } else {
+    f4 r1[MI][2];   // the raw operands are the operands: two sets in turn
+    int64_t kb = kb0;
+    for (; kb + 1 < kb1; kb += 2) {
+      stage(r0, r1, kb);
+      mask_a(r1, kb + 1);
+      stage(r1, r0, kb + 1);
+    }
+    if (kb < kb1) {
+      mask_a(r0, kb);
+      stage(r0, r1, kb);
+    }
   }
 
   // the split's partial output: lane (g, li) of block (i, j) holds rows a = 16 (ab0 + i) + 4 g + v
@@ -778,16 +948,25 @@ struct PkChunk {
   hipStream_t st;
 };
 
+int pk_set_lds(const void* kernel, size_t bytes, DeviceOnce& once) {
+  if (bytes <= 64 * 1024 || once.done()) return FIRAL_OK;
+  FIRAL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  once.set();
+  return FIRAL_OK;
+}
+
 template <int AR, int MODE>
 int pk_xv_launch(const PkChunk& k, bool prof, const float* Vp) {
   Ctx* x = k.x;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (prof) FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT, &e0, &e1));
   const unsigned nwg = (unsigned)(k.Rp / kPkT * k.cols.tiles());
+  static DeviceOnce attr;
+  FIRAL_CHECK(pk_set_lds((const void*)k_pk_xv<AR, MODE>, pk_xv_lds<AR, MODE>(), attr));
   hipExtLaunchKernelGGL((k_pk_xv<AR, MODE>), dim3(nwg), dim3(256),
                         (uint32_t)pk_xv_lds<AR, MODE>(), k.st, e0, e1, 0u,
                         (const float*)x->Xpk + k.ch * (k.q.cp / 16) * k.q.nkb * 512, k.q.nkb, k.R,
-                        Vp, k.cols, k.q.order, (const float*)x->HTf + k.ch * k.q.cp, x->ldn,
+                        Vp, k.cols, (const float*)x->HTf + k.ch * k.q.cp, x->ldn,
                         k.omega, (float*)x->G, k.Rp / 16, x->pk_apart, k.Rp,
                         (const float*)x->pk_alpha, x->gpart, k.skip);
   FIRAL_LAUNCHED();
@@ -795,7 +974,7 @@ int pk_xv_launch(const PkChunk& k, bool prof, const float* Vp) {
 }
 
 int pk_alpha_launch(const PkChunk& k) {
-  k_pk_alpha<<<(unsigned)cdiv((int64_t)k.cols.s * k.Rp, 256), 256, 0, k.st>>>(
+  k_pk_alpha<<<dim3((unsigned)cdiv(k.Rp, 256), (unsigned)k.cols.s), 256, 0, k.st>>>(
       k.x->pk_apart, k.cols, k.Rp, k.Rp, k.R, k.q.order, k.omega, k.x->pk_alpha, k.x->pk_om,
       k.skip);
   FIRAL_LAUNCHED();
@@ -806,13 +985,16 @@ template <int AR, int MI, int TASKS, bool WIN>
 int pk_xtg_launch(const PkChunk& k, int nw, int nmt, int S) {
   Ctx* x = k.x;
   const int64_t rps = cdiv(cdiv(k.R, S), 32) * 32;   // splits start on whole stages
+  constexpr size_t lds = kPkBufs * pk_buf<AR>() * 4;
+  static DeviceOnce attr;
+  FIRAL_CHECK(pk_set_lds((const void*)k_pk_xtg<AR, MI, TASKS, WIN>, lds, attr));
   hipEvent_t e0, e1;
   FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT_T, &e0, &e1));
   hipExtLaunchKernelGGL((k_pk_xtg<AR, MI, TASKS, WIN>),
                         dim3((unsigned)((int64_t)nmt * k.cols.tiles() * S)), dim3(64 * nw),
-                        (uint32_t)(2 * 8 * pk_parts<AR>() * 1024), k.st, e0, e1, 0u,
+                        (uint32_t)lds, k.st, e0, e1, 0u,
                         (const float*)x->XTpk + k.ch * (k.q.cp / 32) * k.q.nab * 512, k.q.nab,
-                        x->d, (const float*)x->G, k.Rp / 16, k.cols, k.q.order,
+                        x->d, (const float*)x->G, k.Rp / 16, k.cols,
                         (const float*)x->HTf + k.ch * k.q.cp, x->ldn, (const float*)x->pk_alpha,
                         (const float*)x->pk_om, k.Rp, k.R, rps, nmt, (float*)x->part,
                         (int64_t)x->d * k.cols.SC, (int)(k.ch > 0), k.skip);
@@ -872,7 +1054,12 @@ int hvp_pk_t(Ctx* x, const PkGeom& q, const double* omega, int64_t n_rows, doubl
     const int64_t r0 = ch * x->chunk_rows, R = std::min<int64_t>(x->chunk_rows, n_rows - r0);
     const PkChunk k{x, q, cols, ch, R, cdiv(R, kPkT) * kPkT, omega ? omega + r0 : nullptr, skip,
                     st};
-    FIRAL_CHECK((pk_xv_launch<AR, WIN ? kPkWin : kPkFlat>(k, true, Vp)));
+    if constexpr (WIN)
+      FIRAL_CHECK((pk_xv_launch<AR, kPkWin>(k, true, Vp)));
+    else if (c <= kPkT)
+      FIRAL_CHECK((pk_xv_launch<AR, kPkFlat>(k, true, Vp)));
+    else
+      FIRAL_CHECK((pk_xv_launch<AR, kPkFlatX>(k, true, Vp)));
     FIRAL_CHECK(pk_alpha_launch(k));
     if (nw == 4)
       FIRAL_CHECK((pk_xtg_launch<AR, 2, 2, WIN>(k, nw, nmt, S)));
@@ -888,6 +1075,7 @@ int hvp_pk_t(Ctx* x, const PkGeom& q, const double* omega, int64_t n_rows, doubl
 template <int AR>
 int grad_pk_t(Ctx* x, const PkGeom& q, const float* U, const float* W, int s, double* g,
               hipStream_t st) {
+  const int c = x->c;
   const PkCols cols = pk_cols(x, s, false);
   float* Wp = (float*)x->Vpk;
   float* Up = Wp + (int64_t)pk_cols(x, x->s_max, false).tiles() * q.nkb * 8 * pk_parts<AR>() * 256;
@@ -896,7 +1084,10 @@ int grad_pk_t(Ctx* x, const PkGeom& q, const float* U, const float* W, int s, do
   for (int64_t ch = 0; ch * x->chunk_rows < x->n_pool; ++ch) {
     const int64_t r0 = ch * x->chunk_rows, R = std::min<int64_t>(x->chunk_rows, x->n_pool - r0);
     const PkChunk k{x, q, cols, ch, R, cdiv(R, kPkT) * kPkT, nullptr, skip_none(), st};
-    FIRAL_CHECK((pk_xv_launch<AR, kPkFlat>(k, false, Wp)));
+    if (c <= kPkT)
+      FIRAL_CHECK((pk_xv_launch<AR, kPkFlat>(k, false, Wp)));
+    else
+      FIRAL_CHECK((pk_xv_launch<AR, kPkFlatX>(k, false, Wp)));
     FIRAL_CHECK(pk_alpha_launch(k));
     FIRAL_CHECK((pk_xv_launch<AR, kPkDot>(k, false, Up)));
     k_pk_grad_sum<<<(unsigned)cdiv(R, 256), 256, 0, st>>>(x->gpart, R, cols.tiles(), s, g + r0);
