@@ -677,6 +677,237 @@ __global__ __launch_bounds__(256) void k_sweep_blk(const double* __restrict__ P,
     }
 }
 
+// Inverse of each SPD block of 128 < d <= 576 for callers that do not ask for the factor: the
+// sweeps above and below, sixteen pivots at a time and with the update of the other rows on FP64
+// MFMA, bit for bit: every element takes the same products and sums, rounded in the same order
+// (an FP64 MFMA adds its four products one after the other, each with one rounding).  A solve in
+// FP32 rounds M^-1 r, and what flips there moves its result by far more than the inverse's own
+// error, so the inverse keeps its bits.
+// ROWS (d <= 256, as k_sweep): row p before its sweep is R_p, T_p = R_p / pivot, and every other
+// row takes M[r][q] -= T_p[r] R_p[q], p by p; column p becomes T_p.  Else (as k_sweep_glb): the
+// rows of the panel are swept as a whole, and the others take M[i][j] -= sum_m Bo[m][i] Rs[m][j]
+// with Bo the rows as loaded and Rs as swept; columns of the panel are Rs transposed.
+// Per panel of sixteen rows: thread q takes column q of the panel into registers and sweeps it with
+// the coefficients of each pivot (in LDS), no barrier between pivots; the two operand panels go to
+// LDS and the waves update 16 x 16 tiles in place in the output (they do not fit a CU's registers
+// and LDS at d = 256), kInvTiles at a time from a common counter, while wave 0 first updates the
+// next pivot block and sweeps it for its coefficients.
+// What bounds it: the tiles' passes through one CU's path to L2, then the FP64 rate.
+// 100 blocks of 256: 4.08 ms with one pivot and two barriers of 1024 threads at a time (k_sweep)
+// -> 0.41 ms; 200 blocks of 383: 8.75 ms with the panels and tiles of k_sweep_glb -> 1.8 ms.
+constexpr int kInvMaxD = 576, kInvTiles = 4;
+// row pitch of the LDS panels: 16 mod 32 doubles, so that the two k of half a wave's read meet no
+// bank twice
+template <bool ROWS> constexpr int kInvPitch = ROWS ? 272 : 592;
+
+// x of one lane, uniform
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// LDS written by lanes of a wave and read by others of the same wave
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Sweep of the 16 x 16 pivot block in `Kb` (row stride kSwLD), in place, by one wave: lane l holds
+// row l / 4, columns 4 (l % 4) + k.  Co[p][r]: what a column's sweep needs of pivot p, T_p[r]
+// (ROWS) or column p; Ro[p]: row p before its sweep; Ip[p]: 1 / pivot.  False when a pivot is not
+// positive.
+template <bool ROWS>
+__device__ __forceinline__ bool sweep16(double* Kb, double* Co, double* Ro, double* Ip, int lane) {
+  const int r = lane >> 2, cg = (lane & 3) * 4;
+  double b[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) b[k] = Kb[r * kSwLD + cg + k];
+  bool ok = true;
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const double piv = lane_value(b[p & 3], 4 * p + (p >> 2));
+    ok = ok && piv > 0.0;
+    const double ip = 1.0 / piv;
+    if (r == p) {    // row p for all lanes (one wave: its LDS accesses stay in order)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Ro[p * 16 + cg + k] = b[k];
+    }
+    wave_lds_fence();
+    double apc[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) apc[k] = Ro[p * 16 + cg + k];
+    const double x = ROWS ? Ro[p * 16 + r] : __shfl(b[p & 3], 4 * r + (p >> 2), 64);
+    const double pri = x * ip;
+    if ((lane & 3) == 0) Co[p * 16 + r] = ROWS ? pri : x;
+    if (lane == 0) Ip[p] = ip;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = cg + k;
+      const double u = ROWS ? fma(-pri, apc[k], b[k]) : fma(-(x * apc[k]), ip, b[k]);
+      b[k] = r != p ? (c != p ? u : pri) : (c != p ? apc[k] * ip : -ip);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) Kb[r * kSwLD + cg + k] = b[k];
+  return __all(ok);
+}
+
+template <bool ROWS>
+__global__ __launch_bounds__(1024) void k_inv_mfma(const double* P, double* Pinv, int d,
+                                                   int32_t* bad) {
+  const int kb = blockIdx.x, lane = threadIdx.x & 63, tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, g = lane >> 4;
+  constexpr int dp = kInvPitch<ROWS>;
+  const int nb = (d + 15) / 16;
+  __shared__ double Lp[16 * dp];   // [16][dp] the left operand: -T or Bo
+  __shared__ double Rp[16 * dp];   // [16][dp] the right operand: R or Rs
+  __shared__ double Kb[16 * kSwLD];
+  __shared__ __align__(16) double Co[256], Ro[256], Ip[16];
+  __shared__ int fail, next;
+  const double* A0 = P + (int64_t)kb * d * d;
+  double* Y = Pinv + (int64_t)kb * d * d;
+
+  // element (row, col) of the block as it stands; outside it the identity
+  auto load = [&](const double* src, int I, int J) {
+    f64x4 t;
+    const int col = 16 * J + li;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int row = 16 * I + g + 4 * w;
+      t[w] = row < d && col < d ? src[(int64_t)row * d + col] : (row == col ? 1.0 : 0.0);
+    }
+    return t;
+  };
+  auto update = [&](const f64x4& t, int I, int J) {
+    f64x4 c = ROWS ? t : Mfma16<double>::zero();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64(Lp[(4 * k + g) * dp + 16 * I + li],
+                                               Rp[(4 * k + g) * dp + 16 * J + li], c, 0, 0, 0);
+    return ROWS ? c : t - c;
+  };
+  auto pivots = [&](const f64x4& t) {   // by wave 0
+#pragma unroll
+    for (int w = 0; w < 4; ++w) Kb[(g + 4 * w) * kSwLD + li] = t[w];
+    wave_lds_fence();
+    if (!sweep16<ROWS>(Kb, Co, Ro, Ip, lane) && lane == 0) {
+      fail = 1;
+      atomicMin(bad, kb);
+    }
+  };
+
+  if (wave == 0) {
+    if (lane == 0) fail = 0;
+    pivots(load(A0, 0, 0));
+  }
+  __syncthreads();
+  if (fail) return;   // the same for every thread
+  for (int K = 0; K < nb; ++K) {
+    const double* src = K == 0 ? A0 : Y;
+    const int k0 = 16 * K, q = tid;
+    const bool last = K + 1 == nb;
+    if (tid == 0) next = 0;
+    if (q < 16 * nb) {
+      double v[16];
+      if (q >= k0 && q < k0 + 16) {
+        // of R_p, tile column q takes what follows its own pivot (its start is T_q, below)
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+          v[p] = Kb[p * kSwLD + q - k0];
+          Rp[p * dp + q] = ROWS ? (p > q - k0 ? Ro[p * 16 + q - k0] : 0.0) : v[p];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          v[r] = k0 + r < d && q < d ? src[(int64_t)(k0 + r) * d + q] : 0.0;
+        if (!ROWS) {
+#pragma unroll
+          for (int p = 0; p < 16; ++p) Lp[p * dp + q] = v[p];
+        }
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+          const double R = v[p], ip = Ip[p], T = R * ip;
+          if (ROWS) {
+            Rp[p * dp + q] = R;
+            Lp[p * dp + q] = -T;
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (r != p) {
+              const double c = Co[p * 16 + r];
+              v[r] = ROWS ? fma(-c, R, v[r]) : fma(-(c * R), ip, v[r]);
+            }
+          v[p] = T;
+        }
+        if (!ROWS) {
+#pragma unroll
+          for (int p = 0; p < 16; ++p) Rp[p * dp + q] = v[p];
+        }
+      }
+      if (q < d) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (k0 + r < d) Y[(int64_t)(k0 + r) * d + q] = last ? -v[r] : v[r];
+      }
+    }
+    __syncthreads();
+    if (wave == 0 && !last) pivots(update(load(src, K + 1, K + 1), K + 1, K + 1));
+    // tiles (I, J) with I != K, numbered row by row; the next pivot block goes no further
+    const int nt = (nb - 1) * nb;
+    for (;;) {
+      int id0 = 0;
+      if (lane == 0) id0 = atomicAdd(&next, kInvTiles);
+      id0 = __builtin_amdgcn_readfirstlane(id0);
+      if (id0 >= nt) break;
+      f64x4 t[kInvTiles];
+      int I[kInvTiles], J[kInvTiles];
+      const int i0 = (int)((unsigned)id0 / (unsigned)nb), j0 = id0 - i0 * nb;
+#pragma unroll
+      for (int n = 0; n < kInvTiles; ++n) {
+        const int wrap = j0 + n >= nb, i = i0 + wrap;   // nb >= 9 > kInvTiles: at most one row on
+        I[n] = i + (i >= K);
+        J[n] = j0 + n - (wrap ? nb : 0);
+        if (I[n] >= nb) I[n] = J[n] = -1;
+        if (I[n] < 0) continue;
+        if (J[n] != K) {
+          t[n] = load(src, I[n], J[n]);
+        } else {
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {   // T_q of the tile's rows; else Rs transposed
+            const int at = li * dp + 16 * I[n] + g + 4 * w;
+            t[n][w] = ROWS ? -Lp[at] : Rp[at];
+          }
+        }
+      }
+#pragma unroll
+      for (int n = 0; n < kInvTiles; ++n) {
+        if (I[n] < 0 || (I[n] == K + 1 && J[n] == K + 1)) continue;
+        const f64x4 x = ROWS || J[n] != K ? update(t[n], I[n], J[n]) : t[n];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int row = 16 * I[n] + g + 4 * w, col = 16 * J[n] + li;
+          if (row < d && col < d) Y[(int64_t)row * d + col] = last ? -x[w] : x[w];
+        }
+      }
+    }
+    __syncthreads();   // the tiles, the LDS panels and the next pivot block
+    if (fail) return;  // the same for every thread
+  }
+}
+
+typedef void (*InvKernel)(const double*, double*, int, int32_t*);
+// d <= 128 has the register sweep of 256 threads (k_sweep_blk); past d = 576 the two panels leave
+// LDS.  Between, the MFMA form was the faster one at every size measured, k_sweep or k_sweep_glb ->
+// it: two blocks of 129 0.157 -> 0.121 ms, of 160 0.193 -> 0.146, of 256 3.86 -> 0.41, of 257 2.89
+// -> 0.49, of 576 23.0 -> 3.8; 300 blocks of 129 0.329 -> 0.269, of 256 8.6 -> 1.04, of 384 18.4 ->
+// 4.0, of 576 56 -> 14.
+static InvKernel pick_inv(int d) {
+  if (d <= 128 || d > kInvMaxD) return nullptr;
+  return d <= 256 ? k_inv_mfma<true> : k_inv_mfma<false>;
+}
 // The sweep for blocks too large for registers (d > 256): block kb is copied to Pinv and swept
 // there in global memory, NB pivots at a time.  With the block partitioned at pivots K as
 // [[K, B^T], [B, D]], sweeping K leaves [[-K^-1, K^-1 B^T], [B K^-1, D - B K^-1 B^T]].  The NB
@@ -921,8 +1152,12 @@ static int precond_t(Ctx* x, const double* omega, double shift, bool want_l, hip
   int threads = 0;
   SweepKernel sw = pick_sweep(d, &threads);
   SweepBlkKernel sb = want_l ? nullptr : pick_sweep_blk(d);
+  InvKernel iv = want_l ? nullptr : pick_inv(d);
   if (sb) {
     sb<<<c, 256, 0, st>>>(x->P, x->Pinv, d, &x->status->bad_block);
+    FIRAL_LAUNCHED();
+  } else if (iv) {
+    iv<<<c, 1024, 0, st>>>(x->P, x->Pinv, d, &x->status->bad_block);
     FIRAL_LAUNCHED();
   } else if (sw) {
     sw<<<c, threads, 0, st>>>(x->P, x->Pinv, d, &x->status->bad_block, want_l ? 1 : 0);
@@ -979,8 +1214,12 @@ int chol_blocks_launch(double* P, double* Pinv, int d, int c, int32_t* bad, bool
   int threads = 0;
   SweepKernel sw = pick_sweep(d, &threads);
   SweepBlkKernel sb = want_l ? nullptr : pick_sweep_blk(d);
+  InvKernel iv = want_l ? nullptr : pick_inv(d);
   if (sb) {
     sb<<<c, 256, 0, st>>>(P, Pinv, d, bad);
+    FIRAL_LAUNCHED();
+  } else if (iv) {
+    iv<<<c, 1024, 0, st>>>(P, Pinv, d, bad);
     FIRAL_LAUNCHED();
   } else if (sw) {
     sw<<<c, threads, 0, st>>>(P, Pinv, d, bad, want_l ? 1 : 0);
