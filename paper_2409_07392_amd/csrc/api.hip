@@ -232,6 +232,7 @@ static int create_ctx(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, 
   // taken at a fixed iteration count move with it
   x->gram_form = gram_form_for(prec, d, c, X);
   syrk_plan(prec, d, c, x->gram_form, x->n_cu, &syrk_tiles, &x->syrk_splits);
+  x->gram_packed = gram_packed(x, &syrk_tiles);
   x->syrk_ntiles = (int)(syrk_tiles.size() / 2);
   x->col_parts = (int)std::max<int64_t>(1, std::min<int64_t>(d, cdiv(256, s_max)));
   x->red_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(n_pool, 256), 1024));
@@ -279,7 +280,9 @@ static int create_ctx(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, 
     ALLOC(x->pk_alpha, pk.alpha);
     ALLOC(x->pk_om, pk.om);
   }
-  ALLOC(x->G, std::max<size_t>(rows * sc * es, pk.g));
+  x->g_bytes = std::max<size_t>(rows * sc * es, pk.g);
+  if (x->gram_packed) x->g_bytes = std::max<size_t>(x->g_bytes, gram_min_bytes(x));
+  ALLOC(x->G, x->g_bytes);
   ALLOC(x->gpart, std::max<size_t>(
                       std::min<int64_t>(rows, n_pool) * tiled_col_tiles(prec, c, s_max) * 8,
                       pk.dpart));

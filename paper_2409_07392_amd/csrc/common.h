@@ -81,6 +81,8 @@ struct Ctx {
   int64_t fused_part_elems;
   int fused_max_ncb;    // fused product: column blocks per wave, 2 (wide tiles) or 1 (two
                         // workgroups' registers per CU, next chunk fetched ahead)
+  bool gram_packed;     // Gram blocks from packed operands (in G)
+  size_t g_bytes;       // of G (the Gram kernel's packed operands too)
   int gram_form;        // preconditioner Gram kernel (kGramClassic, kGramWide, kGramWideBf3)
   int fused_wgs;        // fused product: workgroups a launch aims for (row ranges x column
                         // tiles; 0 = 256); firal_autotune chooses it
@@ -360,6 +362,8 @@ int precond_launch(Ctx* x, const double* omega, double shift, hipStream_t st, bo
 // bf16x3 products when FIRAL_BF3_GRAM=1 (FP32 otherwise).  Chosen once, at context creation.
 constexpr int kGramClassic = 0, kGramWide = 1, kGramWideBf3 = 2;
 int gram_form_for(int prec, int d, int c, const void* X);
+int64_t gram_min_bytes(const Ctx* x);
+bool gram_packed(const Ctx* x, std::vector<int32_t>* tiles);   // and its pair tiles
 void syrk_plan(int prec, int d, int c, int form, int n_cu, std::vector<int32_t>* tiles,
                int* splits);
 // FP64 weighted Gram blocks sum_r omega_r h_rk (1 - h_rk) x_r x_r^T + shift I over rows [0, N)

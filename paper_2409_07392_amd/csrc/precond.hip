@@ -371,6 +371,217 @@ __global__ __launch_bounds__(256, 2) void k_syrkw(const float* __restrict__ X,
     }
 }
 
+// The Gram GEMM of contexts with FP32 arithmetic: tiles of 16 a x 16 b pairs against all classes
+// of a class tile (up to 128), wave w taking a columns 4 w .. 4 w + 3 against all 16 b columns and
+// CMW class blocks, so that a pair product x_a x_b is formed once per workgroup.  Both operands
+// come packed (k_gram_pack): u = omega h (1 - h) and x, in stages of 32 rows of a split, as the
+// 1 KB blocks of 16 rows x 16 columns that a wave reads from LDS as one 16-byte vector a lane,
+// zero outside the split and past c and d.
+// Beside FP32 MFMA a SIMD issues about one other vector instruction per MFMA, so what bounds the
+// kernel is the MFMA rate as long as little else is issued: here four products per 4 CMW MFMAs
+// and the copies.  Formed and bounds-checked in the kernel (once per pair tile, 136 times at
+// d = 256), u and x took a third of the time: c = 100, d = 256, N = 200100 17.1 -> 11.8 ms (132
+// TFLOP/s of 153), c = 200, d = 383, N = 60200 25.7 -> 15.2 ms, with the packing's 0.13 ms, CMW
+// fitted to c (100 classes: 7 blocks, not 8) and the equal runs below (16.3 and 19.9 ms without).
+// The order of the rows of an accumulator's sum is that of the kernels which read X and H as they
+// are: instruction q of a 16-row block takes rows 4 g + q (kGramWide) or 4 q + g.
+constexpr int kGramMaxWgs = 4096, kGramMinStages = 16, kGramCutStages = 64;
+template <bool WIDE>
+__global__ __launch_bounds__(256) void k_gram_pack(const float* __restrict__ X,
+                                                   const float* __restrict__ H,
+                                                   const double* __restrict__ omega, int64_t N,
+                                                   int d, int c, int64_t rps, int stage0, int T,
+                                                   int nct, int cmw, int nab,
+                                                   f32x4* __restrict__ U, f32x4* __restrict__ XP,
+                                                   int32_t* __restrict__ done) {
+  const int sp = blockIdx.x / T, t = blockIdx.x % T;
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int e = threadIdx.x; e < kGramMaxWgs; e += 256) done[e] = 0;
+  const int64_t rb = (int64_t)sp * rps, re = rb + rps < N ? rb + rps : N;
+  const int64_t r0 = rb + (int64_t)(stage0 + t) * 32;
+  if (r0 >= re) return;   // never read
+  const int nu = nct * cmw;
+  f32x4* u = U + (int64_t)blockIdx.x * nu * 128;
+  f32x4* xp = XP + (int64_t)blockIdx.x * nab * 128;
+  for (int e = blockIdx.y * 512 + threadIdx.x, i = 0; i < 2; ++i, e += 256) {
+    if (e >= (nu + nab) * 128) return;
+    const int li = e & 15, g = (e >> 4) & 3, blk = e >> 6;
+    const bool is_u = blk < 2 * nu;
+    const int kg = is_u ? (blk / cmw) & 1 : (blk - 2 * nu) / nab;
+    const int cb = is_u ? blk / (2 * cmw) * cmw + blk % cmw : (blk - 2 * nu) % nab;
+    const int col = 16 * cb + li;
+    f32x4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t r = r0 + 16 * kg + (WIDE ? 4 * g + q : 4 * q + g);
+      float y = 0.f;
+      if (is_u) {
+        if (r < re && col < c) {
+          const float h = H[r * c + col];
+          y = (omega ? (float)omega[r] : 1.f) * h * (1.f - h);
+        }
+      } else if (r < re && col < d) {
+        y = X[r * d + col];
+      }
+      v[q] = y;
+    }
+    if (is_u) u[e] = v;
+    else xp[e - nu * 128] = v;
+  }
+}
+
+// Stages [stage0, stage0 + nkc) of every unit (class tile, pair tile, split); later ranges go on
+// from the sums in `part`.  With more units than workgroups the stages of all units, end to end,
+// are cut into equal runs, one a workgroup (units alone leave the last round of workgroups nearly
+// empty: 1088 units on 512 slots at d = 256, c = 100).  A run is at least a unit long, so a unit
+// is cut at most once, and its sum is carried over the cut through `part`: a workgroup takes the
+// head of its last unit first and the tail of its first unit last, for which the workgroup before
+// it has then had as much time as the head takes.  That workgroup's head waits for nothing and
+// was dispatched earlier, so the wait ends.  Units of under 64 stages are not cut: what a run
+// exchanges then costs more than the uneven last round (c = 1000, d = 400, N = 500, 16 stages: 4.07
+// ms, cut 4.43).
+// workgroups that a CU's registers hold
+constexpr int gram_wgs_per_cu(int cmw) {
+  return cmw <= 1 ? 7 : cmw <= 2 ? 5 : cmw <= 3 ? 4 : cmw <= 5 ? 3 : 2;
+}
+template <int CMW>
+__global__ __launch_bounds__(256, gram_wgs_per_cu(CMW)) void k_gram(
+    const f32x4* __restrict__ U, const f32x4* __restrict__ XP, int64_t N, int d, int c,
+    const int32_t* __restrict__ tiles, int ntiles, int units, int nct, int nab, int64_t rps,
+    int stage0, int nkc, int T, float* part, int32_t* done) {
+  constexpr int NB = 2 * (CMW + 2), NL = (NB + 3) / 4;   // 1 KB blocks of a stage, per wave
+  __shared__ f32x4 sm[2][NB * 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int li = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t total = (int64_t)units * nkc, run = (total + gridDim.x - 1) / gridDim.x;
+  const int64_t lo = blockIdx.x * run, hi = lo + run < total ? lo + run : total;
+  if (lo >= hi) return;
+  const int u0 = (int)(lo / nkc), u1 = (int)((hi - 1) / nkc);
+
+  for (int n = 0; n <= u1 - u0; ++n) {
+    // the last unit first, then the whole ones, then the first
+    const int u = n == 0 ? u1 : n == u1 - u0 ? u0 : u0 + n;
+    const int kb = u == u0 ? (int)(lo - (int64_t)u * nkc) : 0;
+    const int ke = u == u1 ? (int)(hi - (int64_t)u * nkc) : nkc;
+    const int cls_t = u % nct, pt = u / nct % ntiles, sp = u / nct / ntiles;
+    const int A = tiles[2 * pt], B = tiles[2 * pt + 1];
+    const int c0 = cls_t * 16 * CMW, a0 = 16 * A, b0 = 16 * B;
+    const int64_t rb = (int64_t)sp * rps;
+    const int64_t nrows = (rb + rps < N ? rb + rps : N) - rb;
+    const int all = nrows > 0 ? (int)((nrows + 31) / 32) - stage0 : 0;   // the split's stages
+    const int kn = ke < all ? ke : all;
+    const bool resume = stage0 > 0 || kb > 0;
+    float* out = part + (int64_t)sp * c * d * d;
+    const int b = b0 + li;
+    if (kb > 0) {
+      if (tid == 0)
+        while (__hip_atomic_load(done + blockIdx.x - 1, __ATOMIC_ACQUIRE,
+                                 __HIP_MEMORY_SCOPE_AGENT) == 0)
+          __builtin_amdgcn_s_sleep(8);
+      __syncthreads();
+    }
+
+    f32x4 acc[CMW][4];
+#pragma unroll
+    for (int i = 0; i < CMW; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (resume) {
+          const int a = a0 + 4 * wave + j;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int k = c0 + 16 * i + 4 * g + v;
+            if (k < c && a < d && b <= a) acc[i][j][v] = out[((int64_t)k * d + a) * d + b];
+          }
+        }
+      }
+
+    // block m of a stage: CMW of u per 16 rows, then a's and b's
+    const f32x4* src[NL];
+    int step[NL];
+#pragma unroll
+    for (int m = 0; m < NL; ++m) {
+      const int blk = wave + 4 * m, x = blk - 2 * CMW;   // x: a, a, b, b
+      if (x < 0) {
+        src[m] = U + ((((int64_t)sp * T + kb) * nct + cls_t) * 2 * CMW + blk) * 64 + lane;
+        step[m] = nct * 2 * CMW * 64;
+      } else {
+        src[m] = XP + (((int64_t)sp * T + kb) * 2 * nab + (x & 1) * nab + (x < 2 ? A : B)) * 64 +
+                 lane;
+        step[m] = 2 * nab * 64;
+      }
+    }
+    f32x4 st[NL];
+    auto load = [&]() {
+#pragma unroll
+      for (int m = 0; m < NL; ++m)
+        if (wave + 4 * m < NB) {
+          st[m] = *src[m];
+          src[m] += step[m];
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+      for (int m = 0; m < NL; ++m)
+        if (wave + 4 * m < NB) sm[buf][(wave + 4 * m) * 64 + lane] = st[m];
+    };
+    if (kb < kn) {
+      load();
+      store(kb & 1);
+    }
+    __syncthreads();
+    for (int kt = kb; kt < kn; ++kt) {
+      const int buf = kt & 1;
+      if (kt + 1 < kn) load();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kg = 0; kg < 2; ++kg) {
+        const f32x4* us = &sm[buf][kg * CMW * 64 + lane];
+        const f32x4 xb = sm[buf][(2 * CMW + 2 + kg) * 64 + lane];
+        f32x4 bv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4 xa = sm[buf][(2 * CMW + kg) * 64 + 16 * g + 4 * wave + j];
+          bv[j] = f32x4{xa[0] * xb[0], xa[1] * xb[1], xa[2] * xb[2], xa[3] * xb[3]};
+        }
+        f32x4 av = us[0];
+#pragma unroll
+        for (int i = 0; i < CMW; ++i) {
+          const f32x4 nv = us[(i + 1 < CMW ? i + 1 : i) * 64];
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[j][q], acc[i][j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          av = nv;
+        }
+      }
+      if (kt + 1 < kn) store(buf ^ 1);
+      __syncthreads();
+    }
+
+#pragma unroll
+    for (int i = 0; i < CMW; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int a = a0 + 4 * wave + j;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int k = c0 + 16 * i + 4 * g + v;
+          if (k < c && a < d && b <= a) out[((int64_t)k * d + a) * d + b] = acc[i][j][v];
+        }
+      }
+    if (ke < nkc) {
+      __syncthreads();   // the other waves' sums are out: thread 0 releases them with its own
+      if (tid == 0)
+        __hip_atomic_store(done + blockIdx.x, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
 // P[k][a][b] = sum over splits (in order, FP64) of the lower-triangle entry (max, min) +
 // shift [a == b]: P is exactly symmetric.
 template <typename T>
@@ -1125,6 +1336,56 @@ static void launch_syrk(Ctx* x, const double* omega, int64_t rps, hipStream_t st
       rps, (T*)x->syrk_part);
 }
 
+// Class tiles and blocks of k_gram: as few tiles of at most 128 classes, cut alike.
+static void gram_shape(int c, int* nct, int* cmw) {
+  *nct = (int)cdiv(c, 128);
+  *cmw = (int)cdiv(cdiv(c, *nct), 16);
+}
+// Bytes of one stage of every split, packed.
+static int64_t gram_stage_bytes(const Ctx* x) {
+  int nct, cmw;
+  gram_shape(x->c, &nct, &cmw);
+  return (int64_t)x->syrk_splits * (nct * cmw + cdiv(x->d, 16)) * 2048;
+}
+// Scratch that a context holds at least (its product buffer, mostly larger): 32 stages a split, so
+// that taking the sums out of `part` and back is little beside them, or all there are.
+int64_t gram_min_bytes(const Ctx* x) {
+  return kGramMaxWgs * 4 +
+         gram_stage_bytes(x) * std::min<int64_t>(32, cdiv(cdiv(x->N, x->syrk_splits), 32));
+}
+
+static int gram_launch(Ctx* x, const double* omega, int64_t rps, hipStream_t st) {
+  int nct, cmw;
+  gram_shape(x->c, &nct, &cmw);
+  const int nab = (int)cdiv(x->d, 16), S = x->syrk_splits;
+  const int64_t stages = cdiv(rps, 32);
+  const int T = (int)std::min<int64_t>(
+      stages, ((int64_t)x->g_bytes - kGramMaxWgs * 4) / gram_stage_bytes(x));
+  int32_t* done = (int32_t*)x->G;
+  f32x4* U = (f32x4*)(done + kGramMaxWgs);
+  f32x4* XP = U + (int64_t)S * T * nct * cmw * 128;
+  auto pack = x->gram_form == kGramClassic ? k_gram_pack<false> : k_gram_pack<true>;
+  typedef void (*K)(const f32x4*, const f32x4*, int64_t, int, int, const int32_t*, int, int, int,
+                    int, int64_t, int, int, int, float*, int32_t*);
+  static const K kernels[8] = {k_gram<1>, k_gram<2>, k_gram<3>, k_gram<4>,
+                               k_gram<5>, k_gram<6>, k_gram<7>, k_gram<8>};
+  const int units = nct * x->syrk_ntiles * S;
+  const bool cut = stages >= kGramCutStages;
+  const int wgs = !cut ? units : std::min({units, x->n_cu * gram_wgs_per_cu(cmw), kGramMaxWgs});
+  for (int64_t s0 = 0; s0 < stages; s0 += T) {
+    const int nkc = (int)std::min<int64_t>(T, stages - s0);
+    pack<<<dim3((unsigned)(S * T), (unsigned)cdiv(nct * cmw + nab, 4)), 256, 0, st>>>((const float*)x->X, (const float*)x->H, omega, x->N,
+                                            x->d, x->c, rps, (int)s0, T, nct, cmw, nab, U, XP,
+                                            done);
+    FIRAL_LAUNCHED();
+    kernels[cmw - 1]<<<(unsigned)wgs, 256, 0, st>>>(U, XP, x->N, x->d, x->c, x->syrk_tiles,
+                                                    x->syrk_ntiles, units, nct, nab, rps, (int)s0,
+                                                    nkc, T, (float*)x->syrk_part, done);
+    FIRAL_LAUNCHED();
+  }
+  return FIRAL_OK;
+}
+
 template <typename T>
 static int precond_t(Ctx* x, const double* omega, double shift, bool want_l, hipStream_t st) {
   const int d = x->d, c = x->c;
@@ -1133,7 +1394,9 @@ static int precond_t(Ctx* x, const double* omega, double shift, bool want_l, hip
   k_bad_reset<<<1, 1, 0, st>>>(x->status);
   FIRAL_LAUNCHED();
   const SyrkShape sh = syrk_shape(x->prec, c, x->gram_form);
-  if (x->gram_form != kGramClassic) {
+  if (x->gram_packed) {
+    FIRAL_CHECK(gram_launch(x, omega, rps, st));
+  } else if (x->gram_form != kGramClassic) {
     const int nct = (int)cdiv(c, sh.tc());
     const int64_t nwg = (int64_t)nct * x->syrk_ntiles * S;
     auto k = x->gram_form == kGramWideBf3 ? k_syrkw<8, true> : k_syrkw<8, false>;
@@ -1207,6 +1470,24 @@ void syrk_plan(int prec, int d, int c, int form, int n_cu, std::vector<int32_t>*
   const int64_t mem_cap = std::max<int64_t>(1, ((int64_t)1 << 28) / blk);
   *splits = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cdiv(1024, wgs), 64),
                                                         mem_cap));
+}
+
+// Whether a context's Gram blocks are formed from packed operands, its pair tiles then 16 x 16: with
+// FP32 arithmetic from sixteen stages of 32 rows a split on.  Below, the packing's launch costs what
+// it saves or more (with the reduction): N = 300, d = 20, c = 5 (one stage) 0.030 -> 0.040 ms, N =
+// 3000, d = 256, c = 100 (12 stages) 0.481 -> 0.487; from there on N = 20000, d = 100, c = 10 (17
+// stages) 0.094 -> 0.083, N = 60000, d = 383, c = 70 13.3 -> 6.9.
+bool gram_packed(const Ctx* x, std::vector<int32_t>* tiles) {
+  if (x->prec == FIRAL_F64 || x->gram_form == kGramWideBf3 ||
+      cdiv(cdiv(x->N, x->syrk_splits), 32) < kGramMinStages)
+    return false;
+  tiles->clear();
+  for (int A = 0; 16 * A < x->d; ++A)
+    for (int B = 0; B <= A; ++B) {
+      tiles->push_back(A);
+      tiles->push_back(B);
+    }
+  return true;
 }
 
 int chol_blocks_launch(double* P, double* Pinv, int d, int c, int32_t* bad, bool want_inv,
