@@ -199,6 +199,12 @@ class DeviceOnce {
   std::atomic<uint64_t> bits_{0};
 };
 
+// LDS written by lanes of a wave and read by others of the same wave
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ------------------------------------------------------------- MFMA
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));

@@ -919,12 +919,6 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-// LDS written by lanes of a wave and read by others of the same wave
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Sweep of the 16 x 16 pivot block in `Kb` (row stride kSwLD), in place, by one wave: lane l holds
 // row l / 4, columns 4 (l % 4) + k.  Co[p][r]: what a column's sweep needs of pivot p, T_p[r]
 // (ROWS) or column p; Ro[p]: row p before its sweep; Ip[p]: 1 / pivot.  False when a pivot is not

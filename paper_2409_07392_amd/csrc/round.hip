@@ -765,6 +765,211 @@ __global__ __launch_bounds__(256, sizeof(CT) == 4 ? 4 : 3) void k_round_score(co
   }
 }
 
+// The same scores for operands that fit in LDS (FP32: d <= 144, FP64: d <= 96): a workgroup of
+// eight waves takes one class, stages its operand once in LDS as the blocks of 16 k x 16 columns
+// that a wave reads as one vector a lane (of the u half those on and above its triangle), and each
+// wave walks row tiles of 16 RB rows on its own: x of a tile is read straight into the registers
+// that feed the MFMA, a tile ahead, and there is no barrier after the staging.  The products, u . v
+// and v . v take their terms in the order of k_round_score (column blocks in pairs, pairs by parity).
+// What bounds it: the MFMA rate.  k_round_score staged 64 rows and 16 k at a time, bounds-checked,
+// with a barrier each, and added 16 lanes' sums in all of them (beside FP32 MFMA other vector
+// instructions issue one per MFMA: that alone is 215 us here); c = 10, d = 100, n = 50,000: FP32 277
+// -> 190 us (104 of 153 TFLOP/s), c = 50, d = 50, n = 5,000: FP64 98 -> 65 us.
+template <typename T, typename CT> constexpr int cls_rb(int nb) {   // by registers
+  return sizeof(CT) == 4 && nb <= (sizeof(T) == 4 ? 7 : 6) ? 2 : 1;
+}
+template <typename CT> constexpr int kClsMaxNB = sizeof(CT) == 4 ? 9 : 6;
+template <typename CT> constexpr size_t cls_lds(int nb) {
+  return (size_t)(nb * nb + nb * (nb + 1) / 2 + 16) * 256 * sizeof(CT);
+}
+
+// value of the lane's neighbour (lane distance 1)
+__device__ __forceinline__ float lane_xor1(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1,
+                                                               0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_xor1(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0xB1, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0xB1, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+template <typename T, typename CT, int NB>
+__global__ __launch_bounds__(512, 2) void k_round_score_cls(const T* __restrict__ X,
+                                                            const T* __restrict__ H, int64_t r0,
+                                                            int64_t R, int d, int c,
+                                                            const CT* __restrict__ W, double eta,
+                                                            int wpc, CT* __restrict__ Tout) {
+  constexpr int RB = cls_rb<T, CT>(NB), ldo = 16 * NB, kStage = 4;
+  typedef Mfma16<CT> MF;
+  typedef CT cv4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) char cls_smem[];
+  cv4* Bv = (cv4*)cls_smem;          // [s][j][lane]
+  cv4* Bu = Bv + NB * NB * 64;       // [j][s <= j][lane]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, g = lane >> 4;
+  CT* Rd = (CT*)(Bu + NB * (NB + 1) / 2 * 64) + wave * 512;   // [dot product, v][lane]
+  const int k = blockIdx.x / wpc, part = blockIdx.x % wpc;
+  const CT* Wk = W + (int64_t)k * d * 2 * ldo;
+#pragma unroll 1
+  for (int b0 = wave; b0 < NB * NB; b0 += 8 * kStage) {   // kStage blocks' loads in flight
+    cv4 v[kStage], u[kStage];
+#pragma unroll
+    for (int n = 0; n < kStage; ++n) {
+      const int b = b0 + 8 * n < NB * NB ? b0 + 8 * n : b0, s = b / NB, j = b % NB;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int a = 16 * s + 4 * q + g;
+        const CT* w = Wk + (int64_t)(a < d ? a : 0) * 2 * ldo + 16 * j + li;
+        v[n][q] = w[ldo];
+        u[n][q] = w[0];
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < kStage; ++n) {
+      const int b = b0 + 8 * n, s = b / NB, j = b % NB;
+      if (b >= NB * NB) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (16 * s + 4 * q + g >= d) v[n][q] = u[n][q] = CT(0);
+      Bv[b * 64 + lane] = v[n];
+      if (s <= j) Bu[(j * (j + 1) / 2 + s) * 64 + lane] = u[n];
+    }
+  }
+  __syncthreads();
+
+  const int64_t nt = (R + 16 * RB - 1) / (16 * RB);
+  const int64_t step = (int64_t)wpc * 8;
+  int64_t t = (int64_t)part * 8 + wave;
+  if (t >= nt) return;
+  // x of row 16 i + li of a tile, k = 16 s + 4 q + g; rows past the chunk read its last row
+  T raw[RB][NB][4];
+  auto load = [&](int64_t tile) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const int64_t r = tile * 16 * RB + 16 * i + li;
+      const T* xr = X + (r0 + (r < R ? r : R - 1)) * d;
+#pragma unroll
+      for (int s = 0; s < NB; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int a = 16 * s + 4 * q + g;
+          raw[i][s][q] = xr[s + 1 < NB || a < d ? a : 0];
+        }
+    }
+  };
+  load(t);
+  for (; t < nt; t += step) {
+    CT x[RB][NB][4];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int s = 0; s < NB; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          x[i][s][q] = s + 1 < NB || 16 * s + 4 * q + g < d ? (CT)raw[i][s][q] : CT(0);
+    if (t + step < nt) load(t + step);
+    CT sum[RB][2];   // of this lane's row and dot product, by parity of the pair of blocks
+#pragma unroll
+    for (int i = 0; i < RB; ++i) sum[i][0] = sum[i][1] = CT(0);
+    asm volatile("" ::: "memory");   // the operand is read anew for every tile (not kept)
+#pragma unroll
+    for (int p = 0; p < (NB + 1) / 2; ++p) {
+      const int nj = 2 * p + 1 < NB ? 2 : 1;
+      typename MF::acc au[RB][2], av[RB][2];
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) au[i][jj] = av[i][jj] = MF::zero();
+      cv4 bv[2][2], bu[2][2];   // [s parity][column block], read a stage ahead
+      auto read = [&](int s) {
+#pragma unroll
+        for (int jj = 0; jj < nj; ++jj) {
+          const int j = 2 * p + jj;
+          bv[s & 1][jj] = Bv[(s * NB + j) * 64 + lane];
+          if (s <= j) bu[s & 1][jj] = Bu[(j * (j + 1) / 2 + s) * 64 + lane];
+        }
+      };
+      read(0);
+#pragma unroll
+      for (int s = 0; s < NB; ++s) {
+        if (s + 1 < NB) read(s + 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int jj = 0; jj < nj; ++jj)
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+              av[i][jj] = MF::run(x[i][s][q], bv[s & 1][jj][q], av[i][jj]);
+              if (s <= 2 * p + jj) au[i][jj] = MF::run(x[i][s][q], bu[s & 1][jj][q], au[i][jj]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // u . v and v . v over the 32 columns: the two of a lane, then over 16 lanes as the butterfly
+      // over lane distances 1, 2, 4 and 8 adds them, each sum formed by two lanes from LDS
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          CT t1 = CT(0), t2 = CT(0);
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            t1 = fma(au[i][jj][v], av[i][jj][v], t1);
+            t2 = fma(av[i][jj][v], av[i][jj][v], t2);
+          }
+          Rd[v * 64 + lane] = t1;
+          Rd[(4 + v) * 64 + lane] = t2;
+        }
+        wave_lds_fence();
+        const cv4 e0 = *(const cv4*)(Rd + lane * 8), e1 = *(const cv4*)(Rd + lane * 8 + 4);
+        wave_lds_fence();
+        const CT h8 = ((e0[0] + e0[1]) + (e0[2] + e0[3])) + ((e1[0] + e1[1]) + (e1[2] + e1[3]));
+        sum[i][p & 1] += h8 + lane_xor1(h8);
+      }
+    }
+    // lane: dot product lane / 32, row (g, v) = (lane / 2 % 4, lane / 8 % 4) of the block
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const CT q1 = sum[i][0] + sum[i][1];
+      const CT q2 = __shfl_down(q1, 32, 64);
+      const int64_t gr = t * 16 * RB + 16 * i + MF::row(lane >> 1 & 3, lane >> 3 & 3);
+      if ((lane & 33) == 0 && gr < R) {
+        const double h = (double)H[(r0 + gr) * c + k];
+        const CT gk = (CT)(h * (1.0 - h));        // g formed in FP64, then rounded to CT
+        Tout[(int64_t)k * R + gr] = gk * q2 / (CT(1) + (CT)eta * gk * q1);
+      }
+    }
+  }
+}
+
+template <typename T, typename CT>
+using ScoreClsKernel = void (*)(const T*, const T*, int64_t, int64_t, int, int, const CT*, double,
+                                int, CT*);
+template <typename T, typename CT, int... I>
+static ScoreClsKernel<T, CT> score_cls_of(int nb, std::integer_sequence<int, I...>) {
+  static const ScoreClsKernel<T, CT> k[] = {k_round_score_cls<T, CT, I + 1>...};
+  return k[nb - 1];
+}
+// the kernel for d, with its LDS limit raised; null where the operand does not fit
+template <typename T, typename CT>
+static int score_cls_kernel(int d, ScoreClsKernel<T, CT>* out) {
+  const int nb = (int)cdiv(d, 16);
+  *out = nullptr;
+  if (nb > kClsMaxNB<CT>) return FIRAL_OK;
+  ScoreClsKernel<T, CT> k =
+      score_cls_of<T, CT>(nb, std::make_integer_sequence<int, kClsMaxNB<CT>>{});
+  static DeviceOnce once[kClsMaxNB<CT>];
+  if (!once[nb - 1].done()) {
+    FIRAL_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)cls_lds<CT>(nb)));
+    once[nb - 1].set();
+  }
+  *out = k;
+  return FIRAL_OK;
+}
+
 __device__ __forceinline__ bool better(double v1, int64_t i1, double v2, int64_t i2) {
   if (i1 < 0) return false;
   if (i2 < 0) return true;
@@ -1039,6 +1244,8 @@ static int round_score_t(Round* r, const CT* W, double* r_out, hipStream_t st) {
   const T* X = (const T*)x->X;
   const T* H = (const T*)x->H;
   CT* Tb = (CT*)r->Tb;
+  ScoreClsKernel<T, CT> cls;
+  FIRAL_CHECK((score_cls_kernel<T, CT>(r->d, &cls)));
   for (int64_t r0 = 0; r0 < r->n_pool; r0 += r->R) {
     const int64_t R = std::min<int64_t>(r->R, r->n_pool - r0);
     const int64_t nwg = cdiv(R, kScoreTM) * r->c;
@@ -1046,8 +1253,18 @@ static int round_score_t(Round* r, const CT* W, double* r_out, hipStream_t st) {
     FIRAL_CHECK(prof_pair(r->x, FIRAL_PROF_ROUND_SCORE, &e0, &e1));
     // all c operands (d x 2 ldo each) within 2 MiB: walk the classes of a row tile together
     const int rows_major = (int64_t)r->c * r->d * 2 * r->ldo * sizeof(CT) <= ((int64_t)2 << 20);
+    if (cls) {
+      // one workgroup a CU at the least, eight row tiles each where there are as many
+      const int64_t nt = cdiv(cdiv(R, 16 * cls_rb<T, CT>((int)cdiv(r->d, 16))), 8);
+      const size_t lds = cls_lds<CT>((int)cdiv(r->d, 16));
+      const int per_cu = lds <= 80 * 1024 ? 2 : 1;
+      const int wpc = (int)std::max<int64_t>(1, std::min<int64_t>(nt, x->n_cu * per_cu / r->c));
+      hipExtLaunchKernelGGL(cls, dim3((unsigned)(wpc * r->c)), dim3(512), (unsigned)lds, st, e0, e1,
+                            0u, X, H, r0, R, r->d, r->c, W, r->eta, wpc, Tb);
+    } else {
     hipExtLaunchKernelGGL(k_round_score<T, CT>, dim3((unsigned)nwg), dim3(256), 0u, st, e0, e1,
                           0u, X, H, r0, R, r->d, r->c, W, r->ldo, r->eta, rows_major, Tb);
+    }
     FIRAL_LAUNCHED();
     k_round_rsum<CT><<<(unsigned)cdiv(R, 256), 256, 0, st>>>(Tb, R, r->c, r0, r->mask, r_out,
                                                              r->pval, r->pidx);
