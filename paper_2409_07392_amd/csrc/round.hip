@@ -42,6 +42,18 @@ __device__ __forceinline__ int64_t xcd_lid_r(int64_t b, int64_t n) {
   return x * q + (x < r ? x : r) + i;
 }
 
+// value of the lane's neighbour (lane distance 1)
+__device__ __forceinline__ float lane_xor1(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1,
+                                                               0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_xor1(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0xB1, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0xB1, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 __global__ void k_fill_f64(double* p, int64_t n, double v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -60,6 +72,79 @@ __global__ void k_round_omega(const double* __restrict__ z, int64_t n_pool, int6
                               double* __restrict__ om) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < N) om[i] = i < n_pool ? z[i] : 1.0;
+}
+
+// Li_k = L_k^-1 (lower) for d <= 128, every column's forward substitution at once: thread (ty, tx)
+// of 16 x 16 keeps entries (ty + 16 u, tx + 16 v) in registers; row p is divided by L_pp and goes to
+// LDS, and the rows below it lose L_ip times it, one barrier a row (two places in turn), L in LDS.
+// Each entry subtracts its products in the order of k_tri_inv: the same bits.  d = 100, c = 10: 583 us
+// with a column a thread from global memory -> 51 us.
+template <int D16>
+__global__ __launch_bounds__(256) void k_tri_inv_reg(const double* __restrict__ L,
+                                                     double* __restrict__ Li, int d) {
+  constexpr int DP = 16 * D16, LS = DP + 1;
+  extern __shared__ double tri_smem[];
+  double* Ls = tri_smem;                 // [DP][LS]
+  double* row = tri_smem + DP * LS;      // [2][DP]
+  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  const double* Lk = L + (int64_t)blockIdx.x * d * d;
+  double* Y = Li + (int64_t)blockIdx.x * d * d;
+  for (int e = tid; e < d * d; e += 256) Ls[e / d * LS + e % d] = Lk[e];
+  double a[D16][D16];
+#pragma unroll
+  for (int u = 0; u < D16; ++u)
+#pragma unroll
+    for (int v = 0; v <= u; ++v) a[u][v] = u == v && ty == tx ? 1.0 : 0.0;
+  __syncthreads();
+#pragma unroll
+  for (int P = 0; P < D16; ++P) {
+    for (int pp = 0; pp < 16; ++pp) {
+      const int p = 16 * P + pp;
+      if (p >= d) break;
+      double* y = row + (p & 1) * DP;
+      if (ty == pp) {
+        const double lpp = Ls[p * LS + p];
+#pragma unroll
+        for (int v = 0; v <= P; ++v) y[tx + 16 * v] = a[P][v] /= lpp;
+      }
+      __syncthreads();
+      double yv[D16], lv[D16];
+#pragma unroll
+      for (int v = 0; v <= P; ++v) yv[v] = y[tx + 16 * v];
+#pragma unroll
+      for (int u = P; u < D16; ++u) lv[u] = Ls[(ty + 16 * u) * LS + p];
+#pragma unroll
+      for (int u = P; u < D16; ++u)
+#pragma unroll
+        for (int v = 0; v <= P; ++v)
+          if (u > P || ty > pp) a[u][v] = fma(-lv[u], yv[v], a[u][v]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < D16; ++u)
+#pragma unroll
+    for (int v = 0; v < D16; ++v) {
+      const int i = ty + 16 * u, j = tx + 16 * v;
+      if (i < d && j < d) Y[(int64_t)i * d + j] = v <= u ? a[u][v] : 0.0;
+    }
+}
+
+template <int... I>
+static int tri_inv_reg_launch(const double* L, double* Li, int d, int c, hipStream_t st,
+                              std::integer_sequence<int, I...>) {
+  typedef void (*K)(const double*, double*, int);
+  static const K kernels[] = {k_tri_inv_reg<I + 1>...};
+  static DeviceOnce once[sizeof...(I)];
+  const int n = (d + 15) / 16, DP = 16 * n;
+  const int lds = (DP * (DP + 1) + 2 * DP) * (int)sizeof(double);
+  if (!once[n - 1].done()) {
+    FIRAL_HIP(hipFuncSetAttribute((const void*)kernels[n - 1],
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    once[n - 1].set();
+  }
+  kernels[n - 1]<<<c, 256, lds, st>>>(L, Li, d);
+  FIRAL_LAUNCHED();
+  return FIRAL_OK;
 }
 
 // Li_k = L_k^-1 (lower): column j by forward substitution, one column per thread.
@@ -247,105 +332,107 @@ __global__ __launch_bounds__(kTriThreads) void k_tridiag(double* __restrict__ A,
 }
 
 // The same reduction for d <= 128 with the block in registers: thread (ty, tx) of 16 x 16
-// keeps A[ty + 16u][tx + 16w] (zero padding), and per step only column j, the partial sums
-// of A v by thread column, and v and w go through LDS.  v and p are zero on the finished
-// rows 0..j, so the rank-2 update leaves them alone.  The columns are walked in blocks of
-// 16 (compile-time block index into the register tile).
+// keeps A[ty + 16u][tx + 16w] (zero padding).  Per step two barriers: column j goes to LDS; every
+// thread forms the reflector and beta for itself (each wave sums the squares), its part of A v, and
+// the wave the sums of its rows (a row's sixteen parts lie in one wave: they pass through LDS, two
+// lanes a row) and its part of v . A v; after the second barrier every thread has p = beta A v and
+// K = (beta/2) p . v and updates its entries.  v and p are zero on the finished rows 0..j, so the
+// rank-2 update leaves them alone; the blocks of finished rows and columns are skipped (the columns
+// are walked in blocks of 16, a compile-time index into the register tile).
+// What bounds it: the latency of a step's chain (sum, square root, A v, sum).  c = 10, d = 100: 193 us
+// with four barriers and the scalar work of a step in one wave -> 114 us; c = 50, d = 50 58 -> 48 us.
+constexpr int kTriRS = 18;   // row stride of the parts of A v in LDS (16-byte aligned)
 struct TriLds {
-  double* col;   // [128] column j of the current matrix
-  double* v;     // [128]
-  double* w;     // [128]
-  double* part;  // [16][129] partial sums of A v, by thread column
+  double* col;   // [2][128] column j of the current matrix, alternate by step
+  double* p;     // [128] beta A v
+  double* part;  // this wave's parts of A v, [4 D16][kTriRS]
+  double* pv;    // [4] v . A v by wave
   double* dg;    // [128]
   double* of;    // [128]
-  double* bc;    // [2][2] beta and the "reflect" flag, alternate sets by step parity
 };
 
 template <int J, int D16>
 __device__ __forceinline__ void tri_block(double (&a)[D16][D16], const TriLds& L, int d, int tid) {
-  constexpr int PL = 129;
-  const int ty = tid >> 4, tx = tid & 15;
+  const int ty = tid >> 4, tx = tid & 15, lane = tid & 63;
   for (int jj = 0; jj < 16; ++jj) {
     const int j = 16 * J + jj;
     if (j + 2 >= d) return;   // uniform
-    const int r0 = j + 1, n2 = d - r0;
-    // 1. column j (rows below the diagonal) and the diagonal entry to LDS
+    const int r0 = j + 1;
+    double* col = L.col + 128 * (j & 1);
     if (tx == jj) {
 #pragma unroll
-      for (int u = 0; u < D16; ++u) {
+      for (int u = J; u < D16; ++u) {
         const int i = ty + 16 * u;
-        if (i > j) L.col[i] = a[u][J];
+        col[i] = i > j ? a[u][J] : 0.0;   // zero padding: rows from d on are zero
         if (i == j) L.dg[j] = a[u][J];
       }
     }
     __syncthreads();
-    double* bj = L.bc + 2 * (j & 1);
-    // 2. wave 0: sigma, the reflector v (zero on rows 0..j) and beta
-    if (tid < 64) {
-      double sg = 0.0;
-      for (int i = r0 + 1 + tid; i < d; i += 64) sg += L.col[i] * L.col[i];
-      sg = wave_sum(sg);
-      const double x0 = L.col[r0];
-      if (sg == 0.0) {
-        if (tid == 0) {
-          L.of[j] = x0;
-          bj[1] = 0.0;
-        }
-      } else {
-        const double nx = sqrt(x0 * x0 + sg);
-        const double alpha = x0 >= 0.0 ? -nx : nx;
-        const double v0 = x0 - alpha;
-        for (int i = tid; i < 16 * D16; i += 64) L.v[i] = i < r0 || i >= d ? 0.0 : (i == r0 ? v0 : L.col[i]);
-        if (tid == 0) {
-          L.of[j] = alpha;
-          bj[0] = 2.0 / (v0 * v0 + sg);
-          bj[1] = 1.0;
-        }
+    // the reflector v (zero on rows 0..j) and beta
+    double vq[D16], vi[D16];
+    const double x0 = col[r0];
+    double sg = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = lane + 64 * h;
+      const double x = i > r0 && i < 16 * D16 ? col[i] : 0.0;
+      sg = fma(x, x, sg);
+    }
+#pragma unroll
+    for (int w = J; w < D16; ++w) {
+      vq[w] = col[tx + 16 * w];
+      vi[w] = col[ty + 16 * w];
+    }
+    sg = wave_sum(sg);
+    if (sg == 0.0) {   // already tridiagonal in this column
+      if (tid == 0) L.of[j] = x0;
+      continue;
+    }
+    const double nx = sqrt(x0 * x0 + sg);
+    const double alpha = x0 >= 0.0 ? -nx : nx;
+    const double v0 = x0 - alpha;
+    const double beta = 2.0 / (v0 * v0 + sg);
+    if (tid == 0) L.of[j] = alpha;
+#pragma unroll
+    for (int w = J; w < D16; ++w) {   // r0 lies in block J or J + 1
+      if (w <= J + 1) {
+        vq[w] = tx + 16 * w == r0 ? v0 : vq[w];
+        vi[w] = ty + 16 * w == r0 ? v0 : vi[w];
       }
     }
-    __syncthreads();
-    if (bj[1] == 0.0) continue;   // already tridiagonal in this column
-    const double beta = bj[0];
-    // 3. partial sums of A v over this thread's columns, for its rows
-    double vq[D16];
+    // A v: this thread's parts, then its wave's rows
+    double pv = 0.0;
 #pragma unroll
-    for (int w = 0; w < D16; ++w) vq[w] = L.v[tx + 16 * w];
-#pragma unroll
-    for (int u = 0; u < D16; ++u) {
+    for (int u = J; u < D16; ++u) {
       double sp = 0.0;
 #pragma unroll
-      for (int w = 0; w < D16; ++w) sp = fma(a[u][w], vq[w], sp);
-      L.part[tx * PL + ty + 16 * u] = sp;
+      for (int w = J; w < D16; ++w) sp = fma(a[u][w], vq[w], sp);
+      L.part[(4 * u + (ty & 3)) * kTriRS + tx] = sp;
+      pv = fma(vi[u], sp, pv);
     }
+    wave_lds_fence();
+    if (lane >> 1 < 4 * D16) {
+      const double* q = L.part + (lane >> 1) * kTriRS + 8 * (lane & 1);
+      double s = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+      s += lane_xor1(s);
+      const int i = (ty & ~3) + (lane >> 1 & 3) + 16 * (lane >> 3);
+      if ((lane & 1) == 0) L.p[i] = i > j ? beta * s : 0.0;
+    }
+    pv = wave_sum(pv);
+    if (lane == 0) L.pv[tid >> 6] = pv;
     __syncthreads();
-    // 4. wave 0: p = beta A v on the trailing rows (zero on 0..j), K = (beta/2) p . v,
-    //    w = p - K v
-    if (tid < 64) {
-      double pv = 0.0;
-      for (int i = tid; i < 16 * D16; i += 64) {
-        double sum = 0.0;
+    // w = p - K v; A -= v w^T + w v^T on this thread's entries
+    const double K = 0.5 * beta * (beta * ((L.pv[0] + L.pv[1]) + (L.pv[2] + L.pv[3])));
+    double wi[D16], wq[D16];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) sum += L.part[t * PL + i];
-        const double pi = i > j && i < d ? beta * sum : 0.0;
-        L.w[i] = pi;
-        pv += pi * L.v[i];
-      }
-      const double K = 0.5 * beta * wave_sum(pv);
-      for (int i = tid; i < 16 * D16; i += 64) L.w[i] = L.w[i] - K * L.v[i];
-    }
-    __syncthreads();
-    // 5. A -= v w^T + w v^T on this thread's entries
-    double vi[D16], wi[D16], wq[D16];
-#pragma unroll
-    for (int u = 0; u < D16; ++u) {
-      vi[u] = L.v[ty + 16 * u];
-      wi[u] = L.w[ty + 16 * u];
-      wq[u] = L.w[tx + 16 * u];
+    for (int u = J; u < D16; ++u) {
+      wi[u] = fma(-K, vi[u], L.p[ty + 16 * u]);
+      wq[u] = fma(-K, vq[u], L.p[tx + 16 * u]);
     }
 #pragma unroll
-    for (int u = 0; u < D16; ++u)
+    for (int u = J; u < D16; ++u)
 #pragma unroll
-      for (int w = 0; w < D16; ++w) a[u][w] = a[u][w] - vi[u] * wq[w] - wi[u] * vq[w];
+      for (int w = J; w < D16; ++w) a[u][w] = a[u][w] - vi[u] * wq[w] - wi[u] * vq[w];
   }
 }
 
@@ -359,9 +446,8 @@ template <int D16>
 __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all, int d,
                                                      double* __restrict__ diag,
                                                      double* __restrict__ off) {
-  __shared__ double col[128], v[128], w[128], dg[128], of[128];
-  __shared__ double part[16 * 129];
-  __shared__ double bc[4];
+  __shared__ double col[2 * 128], p[128], pv[4], dg[128], of[128];
+  __shared__ __align__(16) double part[4][4 * D16 * kTriRS];
   const int blk = blockIdx.x, tid = threadIdx.x;
   const int ty = tid >> 4, tx = tid & 15;
   const double* Ag = A_all + (int64_t)blk * d * d;
@@ -373,7 +459,7 @@ __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all,
       const int i = ty + 16 * u, j = tx + 16 * q;
       a[u][q] = i < d && j < d ? Ag[(int64_t)i * d + j] : 0.0;
     }
-  const TriLds L{col, v, w, part, dg, of, bc};
+  const TriLds L{col, p, part[tid >> 6], pv, dg, of};
   tri_blocks<D16>(a, L, d, tid, std::make_integer_sequence<int, D16>{});
   // the last 2 x 2 (or 1 x 1) block
 #pragma unroll
@@ -395,45 +481,54 @@ __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all,
   }
 }
 
-// Eigenvalues of each tridiagonal (diag a, off-diagonal e) on Sturm counts: the number of
-// negative pivots of the LDL^T factorisation of T - x I is the number of eigenvalues below x
-// (monotone in x).  Eigenvalue j starts from Gershgorin's bounds; S lanes of a wave share it
-// and each evaluates one of S interior points of its bracket, a ballot finds the first point
-// above the eigenvalue, and the bracket shrinks (S + 1)-fold per step (S = 1: bisection).
+// Eigenvalues of each tridiagonal (diag a, off-diagonal e) on Sturm counts: with the leading minors
+// p_i = (a_i - x) p_i-1 - e_i-1^2 p_i-2 of T - x I, the number of changes of sign is the number of
+// eigenvalues below x (monotone in x).  Eigenvalue j starts from Gershgorin's bounds; S lanes of a
+// wave share it and each evaluates one of S interior points of its bracket, a ballot finds the first
+// point above the eigenvalue, and the bracket shrinks (S + 1)-fold per step (S = 1: bisection).
 // Steps stop once the bracket is within 4 u ||T|| + 4 u |x| (u = 2^-53, the accuracy of the
-// counts) or stops shrinking.  Pivots smaller than pivmin are replaced by -pivmin (LAPACK's
-// safeguard).  Grid: (block, eigenvalue range of 256 / S).
+// counts) or stops shrinking.
+// T is scaled by a power of two to a norm below one (exact), and p_i, p_i-1 by one every eight steps,
+// so that no minor leaves the range.  e^2 is at least 2^-120 (e moves by 2^-60 ||T|| at most, far
+// below the bracket's width): after a minor of exactly zero the next one has the sign opposite to
+// the one before, one change whichever sign the zero has, and the recurrence does not stop there.
+// What bounds it: the chain of d dependent steps, one fma each.  The pivots q_i = p_i / p_i-1 need a
+// division a step: d = 100, c = 10 63 -> 23 us, d = 50, c = 50 69 -> 24 us.
+// Grid: (block, eigenvalue range of 256 / S).
 template <int S>
 __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
                                                const double* __restrict__ off, int d,
                                                double* __restrict__ lam) {
   constexpr int EPW = 256 / S;
-  __shared__ double a[kMaxD], e2[kMaxD];
-  __shared__ double bnd[3];
+  __shared__ __align__(16) double ae[2 * kMaxD];   // a_i, e_i-1^2
+  __shared__ double bnd[2];
   const int blk = blockIdx.x, tid = threadIdx.x;
   const double* dg = diag + (int64_t)blk * d;
   const double* of = off + (int64_t)blk * d;
-  double lo = INFINITY, hi = -INFINITY, emax = 0.0;
+  double lo = INFINITY, hi = -INFINITY;
   for (int i = tid; i < d; i += blockDim.x) {
-    a[i] = dg[i];
     const double el = i > 0 ? fabs(of[i - 1]) : 0.0, er = i + 1 < d ? fabs(of[i]) : 0.0;
-    e2[i] = i + 1 < d ? of[i] * of[i] : 0.0;
     lo = fmin(lo, dg[i] - el - er);
     hi = fmax(hi, dg[i] + el + er);
-    emax = fmax(emax, er * er);
   }
   lo = -block_max<256>(-lo);
   hi = block_max<256>(hi);
-  emax = block_max<256>(emax);
   if (tid == 0) {
     bnd[0] = lo;
     bnd[1] = hi;
-    bnd[2] = 2.2250738585072014e-308 * fmax(1.0, emax);
   }
   __syncthreads();
-  const double L0 = bnd[0], H0 = bnd[1], pivmin = bnd[2];
+  const double nrm0 = fmax(fabs(bnd[0]), fabs(bnd[1]));
+  const int sh = nrm0 > 0.0 && nrm0 < INFINITY ? ilogb(nrm0) + 1 : 0;
+  for (int i = tid; i < d; i += blockDim.x) {
+    ae[2 * i] = ldexp(dg[i], -sh);
+    const double el = i > 0 ? ldexp(of[i - 1], -sh) : 0.0;
+    ae[2 * i + 1] = i > 0 ? fmax(el * el, 0x1p-120) : 0.0;
+  }
+  __syncthreads();
+  const double L0 = ldexp(bnd[0], -sh), H0 = ldexp(bnd[1], -sh);
   const double nrm = fmax(fabs(L0), fabs(H0));
-  const double tol = 4.0 * 1.1102230246251565e-16 * nrm + pivmin;
+  const double tol = 4.0 * 1.1102230246251565e-16 * nrm + 2.2250738585072014e-308;
   const int sl = tid % S, j = blockIdx.y * EPW + tid / S;
   const int gshift = (tid & 63) / S * S;        // first lane of this lane's group in the wave
   constexpr unsigned long long kGroupMask = S == 64 ? ~0ull : (1ull << (S % 64)) - 1;
@@ -445,13 +540,26 @@ __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
     const double x = l + (sl + 1) * h;
     int cnt = 0;
     if (active) {
-      double q = a[0] - x;
-      if (fabs(q) < pivmin) q = -pivmin;
-      cnt += q < 0.0;
-      for (int i = 1; i < d; ++i) {
-        q = (a[i] - x) - e2[i - 1] / q;
-        if (fabs(q) < pivmin) q = -pivmin;
-        cnt += q < 0.0;
+      double p0 = 1.0, p1 = 1.0;   // minors i - 2 and i - 1 (that of index -2 takes e^2 = 0)
+      uint32_t signs = 0;          // of the minors so far, the last one in bit 0
+      auto minor = [&](int i) {
+        const double t = ae[2 * i + 1] * p0;
+        p0 = p1;
+        p1 = fma(ae[2 * i] - x, p1, -t);
+        signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p1), 31);
+      };
+      int i = 0;
+      for (; i + 8 <= d; i += 8) {
+#pragma unroll
+        for (int n = 0; n < 8; ++n) minor(i + n);
+        cnt += __popc((signs ^ (signs >> 1)) & 0xffu);
+        const int e = -max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+        p0 = ldexp(p0, e);
+        p1 = ldexp(p1, e);
+      }
+      for (; i < d; ++i) {
+        minor(i);
+        cnt += (signs ^ (signs >> 1)) & 1u;
       }
     }
     const uint64_t m = __ballot(active && cnt > j);
@@ -466,96 +574,68 @@ __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
       u = nu;
     }
   }
-  if (on && sl == 0) lam[(int64_t)blk * d + j] = 0.5 * (l + u);
+  if (on && sl == 0) lam[(int64_t)blk * d + j] = ldexp(0.5 * (l + u), sh);
 }
 
 // ------------------------------------------------------------------ nu
 // nu_{t+1}: the root of phi(nu) = sum_kj (nu + eta lam_kj)^-2 = 1 on
 // [1 - eta lam_min, sqrt(cd) - eta lam_min] (phi decreases there from >= 1 to <= 1).
 // Newton steps on phi^-1/2 - 1 (close to linear in nu), replaced by bisection whenever they
-// leave the bracket; stops when the bracket or the step vanishes.  One workgroup.
-__global__ __launch_bounds__(1024) void k_round_nu(const double* __restrict__ lam, int64_t n,
-                                                   double eta, double* __restrict__ nu_out) {
-  __shared__ double bc[4];
-  __shared__ int done;
-  const int tid = threadIdx.x;
+// leave the bracket; stops when the bracket or the step vanishes.  One workgroup; every thread
+// receives the sums over the waves and takes the same steps, so an iteration has one barrier (the
+// sums alternate between two places).  Up to kNuReg eigenvalues a thread stay in registers.
+// Four waves up to 4096 eigenvalues: c d = 2500 47 us with two reductions of four barriers and a
+// scalar step by one thread, 24 us in 16 waves -> 13 us; c d = 1000 14 us in one wave, 26 us in 16
+// -> 12.5 us.
+constexpr int kNuReg = 16;
+template <int kNuThreads>
+__global__ __launch_bounds__(kNuThreads) void k_round_nu(const double* __restrict__ lam, int64_t n,
+                                                         double eta, double* __restrict__ nu_out) {
+  constexpr int NW = kNuThreads / 64;
+  __shared__ double red[2][2][NW];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  double lv[kNuReg];
   double mn = INFINITY;
-  for (int64_t e = tid; e < n; e += blockDim.x) mn = fmin(mn, lam[e]);
-  const double negmax = block_max<1024>(-mn);
-  if (tid == 0) bc[0] = -negmax;
+#pragma unroll
+  for (int u = 0; u < kNuReg; ++u) {
+    const int64_t e = tid + (int64_t)kNuThreads * u;
+    lv[u] = e < n ? lam[e] : INFINITY;
+    mn = fmin(mn, lv[u]);
+  }
+  for (int64_t e = tid + (int64_t)kNuThreads * kNuReg; e < n; e += kNuThreads) mn = fmin(mn, lam[e]);
+  for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));   // exact: any order
+  if (lane == 0) red[1][0][wave] = mn;
   __syncthreads();
-  mn = bc[0];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) mn = fmin(mn, red[1][0][w]);
   double lo = 1.0 - eta * mn, hi = sqrt((double)n) - eta * mn;
   double nu = lo;
-  if (tid == 0) done = 0;
-  __syncthreads();
   for (int it = 0; it < 300; ++it) {
     double f = 0.0, fp = 0.0;
-    for (int64_t e = tid; e < n; e += blockDim.x) {
-      const double a = 1.0 / (nu + eta * lam[e]);
+    auto add = [&](double l) {
+      const double a = 1.0 / (nu + eta * l);
       const double a2 = a * a;
       f += a2;
       fp += a2 * a;
-    }
-    f = block_sum<1024>(f);
-    fp = block_sum<1024>(fp);
-    if (tid == 0) {
-      const double phi = f, dphi = -2.0 * fp;
-      if (phi > 1.0) lo = nu;
-      else if (phi < 1.0) hi = nu;
-      double nn;
-      if (phi == 1.0) {
-        nn = nu;
-      } else {
-        nn = nu + 2.0 * phi * (1.0 - sqrt(phi)) / dphi;
-        if (!(nn > lo && nn < hi)) nn = 0.5 * (lo + hi);
-      }
-      if (nn == nu || !(hi - lo > 4e-16 * fabs(hi))) done = 1;
-      bc[1] = nn;
-      bc[2] = lo;
-      bc[3] = hi;
-    }
-    __syncthreads();
-    nu = bc[1];
-    lo = bc[2];
-    hi = bc[3];
-    const int stop = done;
-    __syncthreads();
-    if (stop) break;
-  }
-  if (tid == 0) *nu_out = nu;
-}
-
-// The same iteration for up to 64 kNuPerLane eigenvalues in one wave: each lane keeps its
-// eigenvalues in registers and every lane receives the wave-wide sums, so all lanes take
-// the same steps and no barrier is needed.
-constexpr int kNuPerLane = 32;
-__global__ __launch_bounds__(64) void k_round_nu_wave(const double* __restrict__ lam, int n,
-                                                      double eta, double* __restrict__ nu_out) {
-  const int l = threadIdx.x;
-  double lv[kNuPerLane];
-  double mn = INFINITY;
+    };
 #pragma unroll
-  for (int u = 0; u < kNuPerLane; ++u) {
-    const int e = l + 64 * u;
-    lv[u] = e < n ? lam[e] : 0.0;
-    if (e < n) mn = fmin(mn, lv[u]);
-  }
-  for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));   // exact: any order
-  double lo = 1.0 - eta * mn, hi = sqrt((double)n) - eta * mn;
-  double nu = lo;
-  for (int it = 0; it < 300; ++it) {
-    double f = 0.0, fp = 0.0;
-#pragma unroll
-    for (int u = 0; u < kNuPerLane; ++u)
-      if (l + 64 * u < n) {
-        const double a = 1.0 / (nu + eta * lv[u]);
-        const double a2 = a * a;
-        f += a2;
-        fp += a2 * a;
-      }
+    for (int u = 0; u < kNuReg; ++u)
+      if (tid + (int64_t)kNuThreads * u < n) add(lv[u]);
+    for (int64_t e = tid + (int64_t)kNuThreads * kNuReg; e < n; e += kNuThreads) add(lam[e]);
     f = wave_sum(f);
     fp = wave_sum(fp);
+    double(*rd)[NW] = red[it & 1];
+    if (lane == 0) {
+      rd[0][wave] = f;
+      rd[1][wave] = fp;
+    }
+    __syncthreads();
+    f = fp = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      f += rd[0][w];
+      fp += rd[1][w];
+    }
     const double phi = f, dphi = -2.0 * fp;
     if (phi > 1.0) lo = nu;
     else if (phi < 1.0) hi = nu;
@@ -566,11 +646,11 @@ __global__ __launch_bounds__(64) void k_round_nu_wave(const double* __restrict__
       nn = nu + 2.0 * phi * (1.0 - sqrt(phi)) / dphi;
       if (!(nn > lo && nn < hi)) nn = 0.5 * (lo + hi);
     }
-    const bool stop = nn == nu || !(hi - lo > 4e-16 * fabs(hi));
+    const bool stop = nn == nu || !(hi - lo > 4e-16 * fabs(hi));   // the same in every thread
     nu = nn;
     if (stop) break;
   }
-  if (l == 0) *nu_out = nu;
+  if (tid == 0) *nu_out = nu;
 }
 
 // D_k = nu I + eta (C_k + O_k / b)
@@ -781,18 +861,6 @@ template <typename T, typename CT> constexpr int cls_rb(int nb) {   // by regist
 template <typename CT> constexpr int kClsMaxNB = sizeof(CT) == 4 ? 9 : 6;
 template <typename CT> constexpr size_t cls_lds(int nb) {
   return (size_t)(nb * nb + nb * (nb + 1) / 2 + 16) * 256 * sizeof(CT);
-}
-
-// value of the lane's neighbour (lane distance 1)
-__device__ __forceinline__ float lane_xor1(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1,
-                                                               0xf, 0xf, true));
-}
-__device__ __forceinline__ double lane_xor1(double x) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0xB1, 0xf, 0xf, true);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0xB1, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
 template <typename T, typename CT, int NB>
@@ -1298,10 +1366,10 @@ static int round_step_launch(Round* r, hipStream_t st) {
                                              r->Hacc, r->Ew, r->mask, r->flags + 1);
   FIRAL_LAUNCHED();
   FIRAL_CHECK(eigvals_launch(r, r->Ew, st));
-  if ((int64_t)c * d <= 64 * kNuPerLane)
-    k_round_nu_wave<<<1, 64, 0, st>>>(r->lam, c * d, r->eta, r->nu + t + 1);
+  if ((int64_t)c * d <= 256 * kNuReg)
+    k_round_nu<256><<<1, 256, 0, st>>>(r->lam, (int64_t)c * d, r->eta, r->nu + t + 1);
   else
-    k_round_nu<<<1, 1024, 0, st>>>(r->lam, (int64_t)c * d, r->eta, r->nu + t + 1);
+    k_round_nu<1024><<<1, 1024, 0, st>>>(r->lam, (int64_t)c * d, r->eta, r->nu + t + 1);
   FIRAL_LAUNCHED();
   FIRAL_CHECK(round_operand(r, r->nu + t + 1, st));
   r->t = t + 1;
@@ -1425,8 +1493,12 @@ extern "C" int firal_round_create(firal_round* out, firal_ctx ctx, const double*
   RCHK(gram64_launch(x->prec, (const char*)x->X + es * r->n_pool * d,
                      (const char*)x->H + es * r->n_pool * c, nullptr, r->N - r->n_pool, d, c,
                      r->tiles, r->ntiles, r->splits, 0.0, r->gpart, r->Ho, st));
-  k_tri_inv<<<c, 256, 0, st>>>(r->Lf, r->Li, d);
-  if (hipGetLastError() != hipSuccess) return fail(FIRAL_EHIP);
+  if (d <= 128) {
+    RCHK(tri_inv_reg_launch(r->Lf, r->Li, d, c, st, std::make_integer_sequence<int, 8>{}));
+  } else {
+    k_tri_inv<<<c, 256, 0, st>>>(r->Lf, r->Li, d);
+    if (hipGetLastError() != hipSuccess) return fail(FIRAL_EHIP);
+  }
   // O_k = L^-1 H_o L^-T (Ew as the intermediate H_o L^-T)
   RCHK(bgemm(BGemm{r->Ho, dd, d, 1, r->Li, dd, 1, d, r->Ew, dd, d, 1, d, d, d}, c, st));
   RCHK(bgemm(BGemm{r->Li, dd, d, 1, r->Ew, dd, d, 1, r->Ot, dd, d, 1, d, d, d}, c, st));
