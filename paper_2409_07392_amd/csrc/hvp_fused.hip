@@ -18,6 +18,7 @@
 // gradient of eq. 11 (k_grad_fused: X U and X W per chunk, then the per-row
 // contraction, with no second product).
 #include <algorithm>
+#include <utility>
 
 #include <hip/hip_ext.h>
 
@@ -300,6 +301,238 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused(
           if (a < d) out[(int64_t)a * SC + col0 + col] = acc2[i][ab][v];
         }
     }
+  }
+}
+
+// The same product for tiles of at most one column block a wave, with one barrier a chunk: in step i
+// a wave stages chunk i + 2 and fetches chunk i + 3, forms G of chunk i + 1, adds X^T G' of chunk
+// i - 1 and takes its share of the Gamma step of chunk i, so that one wave's Gamma step and staging
+// run beside another's products (four X buffers and three of G and h in LDS; X^T is read from the
+// row-major X by rows, conflict-free at a row stride of 4 mod 16 floats).  Half the waves take the
+// Gamma step before their products.  The products and sums are those of k_hvp_fused, in its order.
+// What bounds it: the MFMA rate of the SIMDs that hold two of the busy waves (C16 of 8); before, the
+// four barriers a chunk and its LDS reads one at a time: n = 50,000, d = 100, c = 10, s = 20 80 us
+// (5.0 us a chunk) -> 68 us (4.3; its MFMAs 3.3).
+// Beside FP32 MFMA a SIMD issues about one other vector instruction per MFMA, so the rest of a step
+// is kept short: addresses are a uniform base plus an offset kept per thread, a chunk that ends
+// early is a branch of its own, and the Gamma step is compiled for each c <= 16.
+__constant__ double kFusedUnitWeight = 1.0;   // the row weight when none is given
+// floats of one buffer of h: the values, the weights, one that takes what lies past the chunk
+__host__ __device__ constexpr int pipe_hbuf(int c) { return kRC * (c + 1) + 1; }
+
+// gamma_row for a c known when compiled: the same sums
+template <int C>
+__device__ __forceinline__ void gamma_fixed(float* g, const float* h, float w) {
+  constexpr int GT = kRC + 4;
+  float gv[C], hv[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    gv[k] = g[k * GT];
+    hv[k] = h[k];
+  }
+  float alpha = 0.f;
+#pragma unroll
+  for (int k = 0; k < C; ++k) alpha += gv[k] * hv[k];
+#pragma unroll
+  for (int k = 0; k < C; ++k) g[k * GT] = w * ((gv[k] - alpha) * hv[k]);
+}
+__device__ __forceinline__ void gamma_any(float* g, const float* h, float w, int c) {
+  switch (c) {
+#define GAMMA_CASE(C) case C: gamma_fixed<C>(g, h, w); break;
+    GAMMA_CASE(2) GAMMA_CASE(3) GAMMA_CASE(4) GAMMA_CASE(5) GAMMA_CASE(6)
+    GAMMA_CASE(7) GAMMA_CASE(8) GAMMA_CASE(9) GAMMA_CASE(10) GAMMA_CASE(11)
+    GAMMA_CASE(12) GAMMA_CASE(13) GAMMA_CASE(14) GAMMA_CASE(15) GAMMA_CASE(16)
+#undef GAMMA_CASE
+    default: gamma_row<false>(g, kRC + 4, h, w, c);
+  }
+}
+
+// NH: h values per thread and chunk
+template <int D16, int NH>
+__global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
+    const float* __restrict__ X, const float* __restrict__ H, const double* __restrict__ omega,
+    int64_t n_rows, int d, int c, int SC, const float* __restrict__ B, int probes_per_tile, int s,
+    int n_ctiles, int64_t rows_per_split, int n_splits, int, int, int, int CP,
+    float* __restrict__ part, XPlanes, Skip skip) {
+  if (skip_now(skip)) return;
+  constexpr int DP = 16 * D16, XS = DP + 4, GT = kRC + 4;
+  const int nwg = gridDim.x;
+  const int lid = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);   // as k_hvp_fused
+  if (lid >= n_splits * n_ctiles) return;
+  const int ct = lid % n_ctiles, split = lid / n_ctiles;
+  const int j0 = ct * probes_per_tile;
+  const int sp = min(probes_per_tile, s - j0);
+  const int col0 = j0 * c, CT = sp * c, C16 = (CT + 15) >> 4;
+  const int64_t rb = (int64_t)split * rows_per_split;
+  const int64_t re = rb + rows_per_split < n_rows ? rb + rows_per_split : n_rows;
+  const int rows = (int)(re - rb), n = (rows + kRC - 1) / kRC;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const bool busy = wave < C16;
+  extern __shared__ float lds[];
+  const int xbuf = kRC * XS, gbuf = CP * GT, hbuf = pipe_hbuf(c);
+  float* Xs = lds;                 // [4][kRC][XS]
+  float* Gs = Xs + 4 * xbuf;       // [3][CP][GT]
+  float* Hs = Gs + 3 * gbuf;       // [3] of [kRC][c], then the chunk's weights
+
+  // V: k index 16g + 4lk + t for "step" 4g + t; a row of the block is a uniform base plus vo
+  const int col = wave * 16 + li;
+  const bool cok = busy && col < CT;
+  const uint32_t vo = 4 * lk * (uint32_t)SC + (cok ? col : 0);
+  const float* Bt = B + col0;
+  float breg[4 * D16];
+#pragma unroll
+  for (int g = 0; g < D16; ++g)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (g + 1 < D16) {
+        const float v = Bt[(uint32_t)(16 * g + t) * (uint32_t)SC + vo];
+        breg[4 * g + t] = cok ? v : 0.f;
+      } else {
+        const int k = 16 * g + 4 * lk + t;
+        breg[4 * g + t] = cok && k < d ? Bt[(uint32_t)k * (uint32_t)SC + col] : 0.f;
+      }
+    }
+  f32x4 acc2[D16];
+#pragma unroll
+  for (int ab = 0; ab < D16; ++ab) acc2[ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // staging: value tid + 512 q of the chunk's kRC d (and kRC c) values; the columns from d on are
+  // zeroed once.  A fetch has no branch and no use of what it loads (either would wait for the
+  // loads in flight, 1.7 us a chunk): values past the chunk's end read its last one, and go to
+  // places that nothing reads, or are zeroed when stored in a chunk that ends early.
+  int xo[D16], ho[NH];
+  {
+    const int dr = kThreads / d, da = kThreads % d;
+    int r = tid / d, a = tid - r * d;
+#pragma unroll
+    for (int q = 0; q < D16; ++q) {
+      xo[q] = r < kRC ? r * XS + a : DP;
+      r += dr;
+      a += da;
+      if (a >= d) {
+        a -= d;
+        ++r;
+      }
+    }
+    for (int z = d + (tid & 3); z < XS; z += 4) Xs[(tid >> 2) * XS + z] = 0.f;   // 128 rows
+  }
+  const int nc = kRC * c;
+#pragma unroll
+  for (int q = 0; q < NH; ++q) ho[q] = tid + kThreads * q < nc ? tid + kThreads * q : nc + kRC;
+  float xr[D16], hr[NH];
+  double om;
+  const double* wsrc = omega ? omega : &kFusedUnitWeight;
+  auto load = [&](int i) {
+    const int64_t r0 = rb + (int64_t)i * kRC;
+    const int R = min(kRC, rows - i * kRC);
+    const float* xp = X + r0 * d;
+    const float* hp = H + r0 * c;
+#pragma unroll
+    for (int q = 0; q < D16; ++q) xr[q] = xp[min((uint32_t)(tid + kThreads * q), (uint32_t)(R * d - 1))];
+#pragma unroll
+    for (int q = 0; q < NH; ++q) hr[q] = hp[min((uint32_t)(tid + kThreads * q), (uint32_t)(R * c - 1))];
+    om = wsrc[omega ? r0 + min(lane, R - 1) : 0];
+  };
+  auto store = [&](int i) {
+    float* xs = Xs + (i & 3) * xbuf;
+    float* hs = Hs + i % 3 * hbuf;
+    const int R = min(kRC, rows - i * kRC);
+    if (R < kRC) {
+#pragma unroll
+      for (int q = 0; q < D16; ++q) xr[q] = tid + kThreads * q < R * d ? xr[q] : 0.f;
+#pragma unroll
+      for (int q = 0; q < NH; ++q) hr[q] = tid + kThreads * q < R * c ? hr[q] : 0.f;
+      om = lane < R ? om : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < D16; ++q) xs[xo[q]] = xr[q];
+#pragma unroll
+    for (int q = 0; q < NH; ++q) hs[ho[q]] = hr[q];
+    if (wave == 0 && lane < kRC) hs[nc + lane] = (float)om;
+  };
+
+  if (n > 0) {
+    load(0);
+    store(0);
+    if (n > 1) load(1);
+  }
+  __syncthreads();
+  const int gr = tid & (kRC - 1), gp = tid / kRC;   // row and first probe of the Gamma step
+  const int order = wave >= kNW / 2;                // the upper waves take it first
+  for (int i = -1; i <= n; ++i) {
+    if (i + 2 < n) store(i + 2);
+    if (i + 3 < n) load(i + 3);
+#pragma unroll 1
+    for (int ph = 0; ph < 2; ++ph) {
+      if (ph != order) {
+        if (i < 0 || i >= n) continue;
+        const float* hs = Hs + i % 3 * hbuf;
+        for (int j = gp; j < sp; j += kThreads / kRC)
+          gamma_any(Gs + i % 3 * gbuf + j * c * GT + gr, hs + gr * c, hs[nc + gr], c);
+        continue;
+      }
+      if (!busy) continue;
+      if (i + 1 < n) {   // G of chunk i + 1
+        const float* xs = Xs + ((i + 1) & 3) * xbuf + li * XS + 4 * lk;
+        f32x4 g0 = f32x4{0.f, 0.f, 0.f, 0.f}, g1 = g0;
+        f32x4v a0[2], a1[2];   // read a group ahead (the compiler alone reads them when needed)
+        a0[0] = *(const f32x4v*)xs;
+        a1[0] = *(const f32x4v*)(xs + 16 * XS);
+#pragma unroll
+        for (int g = 0; g < D16; ++g) {
+          if (g + 1 < D16) {
+            a0[(g + 1) & 1] = *(const f32x4v*)(xs + 16 * (g + 1));
+            a1[(g + 1) & 1] = *(const f32x4v*)(xs + 16 * XS + 16 * (g + 1));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[g & 1][t], breg[4 * g + t], g0, 0, 0, 0);
+            g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[g & 1][t], breg[4 * g + t], g1, 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        float* gs = Gs + (i + 1) % 3 * gbuf + (wave * 16 + li) * GT + 4 * lk;
+        *(f32x4v*)gs = f32x4v{g0[0], g0[1], g0[2], g0[3]};
+        *(f32x4v*)(gs + 16) = f32x4v{g1[0], g1[1], g1[2], g1[3]};
+      }
+      if (i >= 1) {      // Out += X^T G' of chunk i - 1
+        const float* xs = Xs + ((i - 1) & 3) * xbuf + 4 * lk * XS + li;
+        const float* gs = Gs + (i - 1) % 3 * gbuf + (wave * 16 + li) * GT + 4 * lk;
+        const f32x4v b0 = *(const f32x4v*)gs, b1 = *(const f32x4v*)(gs + 16);
+        float xa[2][D16];      // X of a row group, read a group ahead
+#pragma unroll
+        for (int ab = 0; ab < D16; ++ab) xa[0][ab] = xs[16 * ab];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {   // rows 16 (m / 4) + 4 lk + m % 4
+          if (m < 7) {
+#pragma unroll
+            for (int ab = 0; ab < D16; ++ab)
+              xa[(m + 1) & 1][ab] = xs[(16 * ((m + 1) / 4) + (m + 1) % 4) * XS + 16 * ab];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int ab = 0; ab < D16; ++ab)
+            acc2[ab] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                xa[m & 1][ab], m < 4 ? b0[m % 4] : b1[m % 4], acc2[ab], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+  if (cok) {
+    float* out = part + (int64_t)split * d * SC + col0;
+#pragma unroll
+    for (int ab = 0; ab < D16; ++ab)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (ab + 1 < D16 || ab * 16 + 4 * lk + v < d)
+          out[(uint32_t)(16 * ab + v) * (uint32_t)SC + vo] = acc2[ab][v];
   }
 }
 
@@ -754,6 +987,14 @@ static FusedKernel pick_ncb(int ncb) {
   return nullptr;
 }
 
+template <int... D>
+static FusedKernel pick_pipe(int D16, int c, std::integer_sequence<int, D...>) {
+  static const FusedKernel k[3][sizeof...(D)] = {{k_hvp_fused_pipe<D + 1, 1>...},
+                                                 {k_hvp_fused_pipe<D + 1, 2>...},
+                                                 {k_hvp_fused_pipe<D + 1, 8>...}};
+  return k[c <= 16 ? 0 : c <= 32 ? 1 : 2][D16 - 1];
+}
+
 template <int D16>
 static FusedKernel pick_bf3_ncb(int ncb) {
   if (ncb == 1) return k_hvp_fused_bf3<D16, 1>;
@@ -824,11 +1065,17 @@ bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise)
   const int64_t rps = ((n_rows + splits - 1) / splits + kRC - 1) / kRC * kRC;
   splits = (n_rows + rps - 1) / rps;
   p->part_elems = splits * (int64_t)d * s * c;
-  p->kernel = bf3 ? (void*)pick_bf3(D16, ncb) : (void*)pick(D16, ncb);
+  // one column block a wave: the pipelined kernel where its buffers fit in LDS
+  const size_t pipe_lds = 4 * ((size_t)4 * kRC * g.XS + (size_t)3 * g.CP * g.GT +
+                               (size_t)3 * pipe_hbuf(c));
+  const bool pipe = !bf3 && ncb == 1 && pipe_lds <= 156 * 1024;
+  if (pipe) lds_bytes = pipe_lds;
+  p->kernel = bf3 ? (void*)pick_bf3(D16, ncb) : pipe ? (void*)pick_pipe(D16, c, std::make_integer_sequence<int, 8>{})
+                                              : (void*)pick(D16, ncb);
   if (!p->kernel) return false;
   p->bf3 = bf3;
   p->D16 = D16;
-  p->ncb = ncb;
+  p->ncb = pipe ? 0 : ncb;
   p->probes_per_tile = pp;
   p->n_ctiles = n_ct;
   p->rows_per_split = rps;
@@ -851,11 +1098,13 @@ int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_
   FusedKernel k = (FusedKernel)p.kernel;
   // largest dynamic LDS size granted per device and instantiation (devices 0 .. 15 remembered;
   // on others the attribute is set on every call)
-  static std::atomic<size_t> attr_set[16][2][17][3] = {};
+  static std::atomic<size_t> attr_set[16][2][17][5] = {};   // last: ncb, or the pipelined NH
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) dev = -1;
   std::atomic<size_t>* granted =
-      dev >= 0 && dev < 16 ? &attr_set[dev][p.bf3][p.D16][p.ncb] : nullptr;
+      dev >= 0 && dev < 16 ? &attr_set[dev][p.bf3][p.D16][p.ncb > 0 ? p.ncb
+                                                            : x->c <= 16 ? 0 : x->c <= 32 ? 3 : 4]
+                           : nullptr;
   if (p.lds_bytes > 64 * 1024 && (!granted || granted->load() < p.lds_bytes)) {
     FIRAL_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)p.lds_bytes));
