@@ -282,6 +282,7 @@ static int create_ctx(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, 
   }
   x->g_bytes = std::max<size_t>(rows * sc * es, pk.g);
   if (x->gram_packed) x->g_bytes = std::max<size_t>(x->g_bytes, gram_min_bytes(x));
+  if (prec == FIRAL_F64) x->g_bytes = std::max<size_t>(x->g_bytes, fused64_bytes(d, c, s_max));
   ALLOC(x->G, x->g_bytes);
   ALLOC(x->gpart, std::max<size_t>(
                       std::min<int64_t>(rows, n_pool) * tiled_col_tiles(prec, c, s_max) * 8,

@@ -82,7 +82,7 @@ struct Ctx {
   int fused_max_ncb;    // fused product: column blocks per wave, 2 (wide tiles) or 1 (two
                         // workgroups' registers per CU, next chunk fetched ahead)
   bool gram_packed;     // Gram blocks from packed operands (in G)
-  size_t g_bytes;       // of G (the Gram kernel's packed operands too)
+  size_t g_bytes;       // of G (the Gram kernel's packed operands, FP64 fused partials too)
   int gram_form;        // preconditioner Gram kernel (kGramClassic, kGramWide, kGramWideBf3)
   int fused_wgs;        // fused product: workgroups a launch aims for (row ranges x column
                         // tiles; 0 = 256); firal_autotune chooses it
@@ -351,6 +351,11 @@ int reduce_parts_launch(const T* part, int64_t n, int P, double shift, const T* 
                         Skip skip, hipStream_t st);
 int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_rows, double shift,
                      const float* B, float* out, int s, Skip skip, hipStream_t st);
+
+// the FP64 form (taken false: the shape or the scratch in G does not allow it, nothing launched)
+size_t fused64_bytes(int d, int c, int s_max);
+int hvp_fused64_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const double* B,
+                       double* out, int s, Skip skip, hipStream_t st, bool* taken);
 
 // ------------------------------------------------- host-side launchers
 // All enqueue on `st`; `skip` (see Skip) makes every kernel of the call return at once.

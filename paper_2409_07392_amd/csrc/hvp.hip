@@ -72,6 +72,12 @@ int hvp_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const 
       plan.part_elems <= x->fused_part_elems)
     return hvp_fused_launch(x, plan, omega, n_rows, shift, (const float*)B, (float*)out, s, skip,
                             st);
+  if (x->prec == FIRAL_F64 && !x->force_tiled) {
+    bool taken = false;
+    FIRAL_CHECK(hvp_fused64_launch(x, omega, n_rows, shift, (const double*)B, (double*)out, s, skip,
+                                   st, &taken));
+    if (taken) return FIRAL_OK;
+  }
   // a bf16x3 context's packed operands are bf16 planes: its FP32 products (precise) are row-tiled
   if (x->use_pk && !(x->prec == FIRAL_BF16X3 && precise))
     return hvp_pk_launch(x, omega, n_rows, shift, (const float*)B, (float*)out, s, entry, skip,

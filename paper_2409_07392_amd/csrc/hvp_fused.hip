@@ -70,16 +70,16 @@ struct XPlanes {
 // probe's c values of G for the row, h the row's probabilities, w its weight:
 // alpha = g . h, then g <- w (g - alpha) h.  Up to 16 classes the row is held in registers
 // (one pass over LDS, when the kernel has the registers: REG); beyond, it is streamed twice.
-template <bool REG>
-__device__ __forceinline__ void gamma_row(float* g, int GT, const float* h, float w, int c) {
+template <bool REG, typename T>
+__device__ __forceinline__ void gamma_row(T* g, int GT, const T* h, T w, int c) {
   constexpr int kGR = 16;
   if (REG && c <= kGR) {
-    float gv[kGR], hv[kGR];
-    float alpha = 0.f;
+    T gv[kGR], hv[kGR];
+    T alpha = T(0);
 #pragma unroll
     for (int k = 0; k < kGR; ++k) {
-      gv[k] = k < c ? g[k * GT] : 0.f;
-      hv[k] = k < c ? h[k] : 0.f;
+      gv[k] = k < c ? g[k * GT] : T(0);
+      hv[k] = k < c ? h[k] : T(0);
     }
 #pragma unroll
     for (int k = 0; k < kGR; ++k) alpha += gv[k] * hv[k];
@@ -88,23 +88,23 @@ __device__ __forceinline__ void gamma_row(float* g, int GT, const float* h, floa
       if (k < c) g[k * GT] = w * ((gv[k] - alpha) * hv[k]);
     return;
   }
-  float alpha = 0.f;
+  T alpha = T(0);
   for (int k0 = 0; k0 < c; k0 += 4) {
-    float gv[4], hv[4];
+    T gv[4], hv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      gv[u] = k0 + u < c ? g[(k0 + u) * GT] : 0.f;
-      hv[u] = k0 + u < c ? h[k0 + u] : 0.f;
+      gv[u] = k0 + u < c ? g[(k0 + u) * GT] : T(0);
+      hv[u] = k0 + u < c ? h[k0 + u] : T(0);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) alpha += gv[u] * hv[u];
   }
   for (int k0 = 0; k0 < c; k0 += 4) {
-    float gv[4], hv[4];
+    T gv[4], hv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      gv[u] = k0 + u < c ? g[(k0 + u) * GT] : 0.f;
-      hv[u] = k0 + u < c ? h[k0 + u] : 0.f;
+      gv[u] = k0 + u < c ? g[(k0 + u) * GT] : T(0);
+      hv[u] = k0 + u < c ? h[k0 + u] : T(0);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -317,45 +317,63 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused(
 // is kept short: addresses are a uniform base plus an offset kept per thread, a chunk that ends
 // early is a branch of its own, and the Gamma step is compiled for each c <= 16.
 __constant__ double kFusedUnitWeight = 1.0;   // the row weight when none is given
-// floats of one buffer of h: the values, the weights, one that takes what lies past the chunk
-__host__ __device__ constexpr int pipe_hbuf(int c) { return kRC * (c + 1) + 1; }
+// values of one buffer of h: the values, the weights, one that takes what lies past the chunk
+__host__ __device__ constexpr int pipe_hbuf(int rc, int c) { return rc * (c + 1) + 1; }
+template <typename T> constexpr int pipe_rc = sizeof(T) == 4 ? kRC : 16;   // rows per chunk
 
 // gamma_row for a c known when compiled: the same sums
-template <int C>
-__device__ __forceinline__ void gamma_fixed(float* g, const float* h, float w) {
-  constexpr int GT = kRC + 4;
-  float gv[C], hv[C];
+template <int C, int GT, typename T>
+__device__ __forceinline__ void gamma_fixed(T* g, const T* h, T w) {
+  T gv[C], hv[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) {
     gv[k] = g[k * GT];
     hv[k] = h[k];
   }
-  float alpha = 0.f;
+  T alpha = T(0);
 #pragma unroll
   for (int k = 0; k < C; ++k) alpha += gv[k] * hv[k];
 #pragma unroll
   for (int k = 0; k < C; ++k) g[k * GT] = w * ((gv[k] - alpha) * hv[k]);
 }
-__device__ __forceinline__ void gamma_any(float* g, const float* h, float w, int c) {
+template <int GT, typename T>
+__device__ __forceinline__ void gamma_any(T* g, const T* h, T w, int c) {
   switch (c) {
-#define GAMMA_CASE(C) case C: gamma_fixed<C>(g, h, w); break;
+#define GAMMA_CASE(C) case C: gamma_fixed<C, GT>(g, h, w); break;
     GAMMA_CASE(2) GAMMA_CASE(3) GAMMA_CASE(4) GAMMA_CASE(5) GAMMA_CASE(6)
     GAMMA_CASE(7) GAMMA_CASE(8) GAMMA_CASE(9) GAMMA_CASE(10) GAMMA_CASE(11)
     GAMMA_CASE(12) GAMMA_CASE(13) GAMMA_CASE(14) GAMMA_CASE(15) GAMMA_CASE(16)
 #undef GAMMA_CASE
-    default: gamma_row<false>(g, kRC + 4, h, w, c);
+    default: gamma_row<false>(g, GT, h, w, c);
   }
 }
 
-// NH: h values per thread and chunk
-template <int D16, int NH>
+// The same step by four lanes a row and probe (lane part lk takes classes lk mod 4): with many
+// classes a chunk of 16 rows has few probes, and one lane each would walk them alone (c = 50, d = 50,
+// n = 5,000, s = 10: 67 us a product, so 41 us).  FP64 only, where the order of the sum is free.
+template <int GT>
+__device__ __forceinline__ void gamma_lanes(double* g, const double* h, double w, int c, int lk) {
+  double alpha = 0.0;
+#pragma unroll 2
+  for (int k = lk; k < c; k += 4) alpha = fma(g[k * GT], h[k], alpha);
+  alpha += __shfl_xor(alpha, 16, 64);
+  alpha += __shfl_xor(alpha, 32, 64);
+#pragma unroll 2
+  for (int k = lk; k < c; k += 4) g[k * GT] = w * ((g[k * GT] - alpha) * h[k]);
+}
+
+// FP64 contexts take the same kernel with chunks of 16 rows.  NH: h values per thread and chunk.
+template <typename T, int D16, int NH>
 __global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
-    const float* __restrict__ X, const float* __restrict__ H, const double* __restrict__ omega,
-    int64_t n_rows, int d, int c, int SC, const float* __restrict__ B, int probes_per_tile, int s,
+    const T* __restrict__ X, const T* __restrict__ H, const double* __restrict__ omega,
+    int64_t n_rows, int d, int c, int SC, const T* __restrict__ B, int probes_per_tile, int s,
     int n_ctiles, int64_t rows_per_split, int n_splits, int, int, int, int CP,
-    float* __restrict__ part, XPlanes, Skip skip) {
+    T* __restrict__ part, XPlanes, Skip skip) {
   if (skip_now(skip)) return;
-  constexpr int DP = 16 * D16, XS = DP + 4, GT = kRC + 4;
+  typedef Mfma16<T> MF;
+  typedef T v4 __attribute__((ext_vector_type(4)));
+  constexpr int kRC = pipe_rc<T>, RB = kRC / 16;
+  constexpr int DP = 16 * D16, XS = DP + 4, GT = kRC + 4, NX = (kRC * DP + kThreads - 1) / kThreads;
   const int nwg = gridDim.x;
   const int lid = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);   // as k_hvp_fused
   if (lid >= n_splits * n_ctiles) return;
@@ -371,44 +389,44 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   const bool busy = wave < C16;
-  extern __shared__ float lds[];
-  const int xbuf = kRC * XS, gbuf = CP * GT, hbuf = pipe_hbuf(c);
-  float* Xs = lds;                 // [4][kRC][XS]
-  float* Gs = Xs + 4 * xbuf;       // [3][CP][GT]
-  float* Hs = Gs + 3 * gbuf;       // [3] of [kRC][c], then the chunk's weights
+  extern __shared__ __align__(16) unsigned char pipe_smem[];
+  const int xbuf = kRC * XS, gbuf = CP * GT, hbuf = pipe_hbuf(kRC, c);
+  T* Xs = (T*)pipe_smem;                 // [4][kRC][XS]
+  T* Gs = Xs + 4 * xbuf;       // [3][CP][GT]
+  T* Hs = Gs + 3 * gbuf;       // [3] of [kRC][c], then the chunk's weights
 
   // V: k index 16g + 4lk + t for "step" 4g + t; a row of the block is a uniform base plus vo
   const int col = wave * 16 + li;
   const bool cok = busy && col < CT;
   const uint32_t vo = 4 * lk * (uint32_t)SC + (cok ? col : 0);
-  const float* Bt = B + col0;
-  float breg[4 * D16];
+  const T* Bt = B + col0;
+  T breg[4 * D16];
 #pragma unroll
   for (int g = 0; g < D16; ++g)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       if (g + 1 < D16) {
-        const float v = Bt[(uint32_t)(16 * g + t) * (uint32_t)SC + vo];
-        breg[4 * g + t] = cok ? v : 0.f;
+        const T v = Bt[(uint32_t)(16 * g + t) * (uint32_t)SC + vo];
+        breg[4 * g + t] = cok ? v : T(0);
       } else {
         const int k = 16 * g + 4 * lk + t;
-        breg[4 * g + t] = cok && k < d ? Bt[(uint32_t)k * (uint32_t)SC + col] : 0.f;
+        breg[4 * g + t] = cok && k < d ? Bt[(uint32_t)k * (uint32_t)SC + col] : T(0);
       }
     }
-  f32x4 acc2[D16];
+  typename MF::acc acc2[D16];
 #pragma unroll
-  for (int ab = 0; ab < D16; ++ab) acc2[ab] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int ab = 0; ab < D16; ++ab) acc2[ab] = MF::zero();
 
   // staging: value tid + 512 q of the chunk's kRC d (and kRC c) values; the columns from d on are
   // zeroed once.  A fetch has no branch and no use of what it loads (either would wait for the
   // loads in flight, 1.7 us a chunk): values past the chunk's end read its last one, and go to
   // places that nothing reads, or are zeroed when stored in a chunk that ends early.
-  int xo[D16], ho[NH];
+  int xo[NX], ho[NH];
   {
     const int dr = kThreads / d, da = kThreads % d;
     int r = tid / d, a = tid - r * d;
 #pragma unroll
-    for (int q = 0; q < D16; ++q) {
+    for (int q = 0; q < NX; ++q) {
       xo[q] = r < kRC ? r * XS + a : DP;
       r += dr;
       a += da;
@@ -417,41 +435,42 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
         ++r;
       }
     }
-    for (int z = d + (tid & 3); z < XS; z += 4) Xs[(tid >> 2) * XS + z] = 0.f;   // 128 rows
+    for (int z = d + (tid & 3); z < XS; z += 4)   // 4 kRC rows
+      if (tid < 16 * kRC) Xs[(tid >> 2) * XS + z] = T(0);
   }
   const int nc = kRC * c;
 #pragma unroll
   for (int q = 0; q < NH; ++q) ho[q] = tid + kThreads * q < nc ? tid + kThreads * q : nc + kRC;
-  float xr[D16], hr[NH];
+  T xr[NX], hr[NH];
   double om;
   const double* wsrc = omega ? omega : &kFusedUnitWeight;
   auto load = [&](int i) {
     const int64_t r0 = rb + (int64_t)i * kRC;
     const int R = min(kRC, rows - i * kRC);
-    const float* xp = X + r0 * d;
-    const float* hp = H + r0 * c;
+    const T* xp = X + r0 * d;
+    const T* hp = H + r0 * c;
 #pragma unroll
-    for (int q = 0; q < D16; ++q) xr[q] = xp[min((uint32_t)(tid + kThreads * q), (uint32_t)(R * d - 1))];
+    for (int q = 0; q < NX; ++q) xr[q] = xp[min((uint32_t)(tid + kThreads * q), (uint32_t)(R * d - 1))];
 #pragma unroll
     for (int q = 0; q < NH; ++q) hr[q] = hp[min((uint32_t)(tid + kThreads * q), (uint32_t)(R * c - 1))];
     om = wsrc[omega ? r0 + min(lane, R - 1) : 0];
   };
   auto store = [&](int i) {
-    float* xs = Xs + (i & 3) * xbuf;
-    float* hs = Hs + i % 3 * hbuf;
+    T* xs = Xs + (i & 3) * xbuf;
+    T* hs = Hs + i % 3 * hbuf;
     const int R = min(kRC, rows - i * kRC);
     if (R < kRC) {
 #pragma unroll
-      for (int q = 0; q < D16; ++q) xr[q] = tid + kThreads * q < R * d ? xr[q] : 0.f;
+      for (int q = 0; q < NX; ++q) xr[q] = tid + kThreads * q < R * d ? xr[q] : T(0);
 #pragma unroll
-      for (int q = 0; q < NH; ++q) hr[q] = tid + kThreads * q < R * c ? hr[q] : 0.f;
+      for (int q = 0; q < NH; ++q) hr[q] = tid + kThreads * q < R * c ? hr[q] : T(0);
       om = lane < R ? om : 0.0;
     }
 #pragma unroll
-    for (int q = 0; q < D16; ++q) xs[xo[q]] = xr[q];
+    for (int q = 0; q < NX; ++q) xs[xo[q]] = xr[q];
 #pragma unroll
     for (int q = 0; q < NH; ++q) hs[ho[q]] = hr[q];
-    if (wave == 0 && lane < kRC) hs[nc + lane] = (float)om;
+    if (wave == 0 && lane < kRC) hs[nc + lane] = (T)om;
   };
 
   if (n > 0) {
@@ -469,46 +488,65 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
     for (int ph = 0; ph < 2; ++ph) {
       if (ph != order) {
         if (i < 0 || i >= n) continue;
-        const float* hs = Hs + i % 3 * hbuf;
+        const T* hs = Hs + i % 3 * hbuf;
+        if constexpr (sizeof(T) == 8) {
+          if (c > 16) {
+            for (int j = wave; j < sp; j += kNW)
+              gamma_lanes<GT>(Gs + i % 3 * gbuf + j * c * GT + li, hs + li * c, hs[nc + li], c, lk);
+            continue;
+          }
+        }
         for (int j = gp; j < sp; j += kThreads / kRC)
-          gamma_any(Gs + i % 3 * gbuf + j * c * GT + gr, hs + gr * c, hs[nc + gr], c);
+          gamma_any<GT>(Gs + i % 3 * gbuf + j * c * GT + gr, hs + gr * c, hs[nc + gr], c);
         continue;
       }
       if (!busy) continue;
       if (i + 1 < n) {   // G of chunk i + 1
-        const float* xs = Xs + ((i + 1) & 3) * xbuf + li * XS + 4 * lk;
-        f32x4 g0 = f32x4{0.f, 0.f, 0.f, 0.f}, g1 = g0;
-        f32x4v a0[2], a1[2];   // read a group ahead (the compiler alone reads them when needed)
-        a0[0] = *(const f32x4v*)xs;
-        a1[0] = *(const f32x4v*)(xs + 16 * XS);
+        const T* xs = Xs + ((i + 1) & 3) * xbuf + li * XS + 4 * lk;
+        typename MF::acc ga[RB];
+        v4 a[2][RB];   // read a group ahead (the compiler alone reads them when needed)
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          ga[r] = MF::zero();
+          a[0][r] = *(const v4*)(xs + 16 * r * XS);
+        }
 #pragma unroll
         for (int g = 0; g < D16; ++g) {
           if (g + 1 < D16) {
-            a0[(g + 1) & 1] = *(const f32x4v*)(xs + 16 * (g + 1));
-            a1[(g + 1) & 1] = *(const f32x4v*)(xs + 16 * XS + 16 * (g + 1));
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+              a[(g + 1) & 1][r] = *(const v4*)(xs + 16 * r * XS + 16 * (g + 1));
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            g0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[g & 1][t], breg[4 * g + t], g0, 0, 0, 0);
-            g1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[g & 1][t], breg[4 * g + t], g1, 0, 0, 0);
-          }
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < RB; ++r) ga[r] = MF::run(a[g & 1][r][t], breg[4 * g + t], ga[r]);
           __builtin_amdgcn_sched_barrier(0);
         }
-        float* gs = Gs + (i + 1) % 3 * gbuf + (wave * 16 + li) * GT + 4 * lk;
-        *(f32x4v*)gs = f32x4v{g0[0], g0[1], g0[2], g0[3]};
-        *(f32x4v*)(gs + 16) = f32x4v{g1[0], g1[1], g1[2], g1[3]};
+        T* gs = Gs + (i + 1) % 3 * gbuf + (wave * 16 + li) * GT;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          if (sizeof(T) == 4) {
+            *(v4*)(gs + 16 * r + 4 * lk) = v4{ga[r][0], ga[r][1], ga[r][2], ga[r][3]};
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gs[16 * r + MF::row(lk, v)] = ga[r][v];
+          }
+        }
       }
       if (i >= 1) {      // Out += X^T G' of chunk i - 1
-        const float* xs = Xs + ((i - 1) & 3) * xbuf + 4 * lk * XS + li;
-        const float* gs = Gs + (i - 1) % 3 * gbuf + (wave * 16 + li) * GT + 4 * lk;
-        const f32x4v b0 = *(const f32x4v*)gs, b1 = *(const f32x4v*)(gs + 16);
-        float xa[2][D16];      // X of a row group, read a group ahead
+        const T* xs = Xs + ((i - 1) & 3) * xbuf + 4 * lk * XS + li;
+        const T* gs = Gs + (i - 1) % 3 * gbuf + (wave * 16 + li) * GT + 4 * lk;
+        v4 bq[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) bq[r] = *(const v4*)(gs + 16 * r);
+        T xa[2][D16];          // X of a row group, read a group ahead
 #pragma unroll
         for (int ab = 0; ab < D16; ++ab) xa[0][ab] = xs[16 * ab];
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {   // rows 16 (m / 4) + 4 lk + m % 4
-          if (m < 7) {
+        for (int m = 0; m < 4 * RB; ++m) {   // rows 16 (m / 4) + 4 lk + m % 4
+          if (m + 1 < 4 * RB) {
 #pragma unroll
             for (int ab = 0; ab < D16; ++ab)
               xa[(m + 1) & 1][ab] = xs[(16 * ((m + 1) / 4) + (m + 1) % 4) * XS + 16 * ab];
@@ -516,8 +554,7 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int ab = 0; ab < D16; ++ab)
-            acc2[ab] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                xa[m & 1][ab], m < 4 ? b0[m % 4] : b1[m % 4], acc2[ab], 0, 0, 0);
+            acc2[ab] = MF::run(xa[m & 1][ab], bq[m / 4][m % 4], acc2[ab]);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -526,13 +563,14 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused_pipe(
   }
 
   if (cok) {
-    float* out = part + (int64_t)split * d * SC + col0;
+    T* out = part + (int64_t)split * d * SC + col0;
+    const uint32_t wo = MF::row(lk, 0) * (uint32_t)SC + col;
 #pragma unroll
     for (int ab = 0; ab < D16; ++ab)
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (ab + 1 < D16 || ab * 16 + 4 * lk + v < d)
-          out[(uint32_t)(16 * ab + v) * (uint32_t)SC + vo] = acc2[ab][v];
+        if (ab + 1 < D16 || ab * 16 + MF::row(lk, v) < d)
+          out[(uint32_t)(16 * ab + MF::row(0, v)) * (uint32_t)SC + wo] = acc2[ab][v];
   }
 }
 
@@ -980,6 +1018,10 @@ typedef void (*FusedKernel)(const float*, const float*, const double*, int64_t, 
                             const float*, int, int, int, int64_t, int, int, int, int, int, float*,
                             XPlanes, Skip);
 
+typedef void (*FusedKernel64)(const double*, const double*, const double*, int64_t, int, int, int,
+                              const double*, int, int, int, int64_t, int, int, int, int, int,
+                              double*, XPlanes, Skip);
+
 template <int D16>
 static FusedKernel pick_ncb(int ncb) {
   if (ncb == 1) return k_hvp_fused<D16, 1>;
@@ -989,9 +1031,9 @@ static FusedKernel pick_ncb(int ncb) {
 
 template <int... D>
 static FusedKernel pick_pipe(int D16, int c, std::integer_sequence<int, D...>) {
-  static const FusedKernel k[3][sizeof...(D)] = {{k_hvp_fused_pipe<D + 1, 1>...},
-                                                 {k_hvp_fused_pipe<D + 1, 2>...},
-                                                 {k_hvp_fused_pipe<D + 1, 8>...}};
+  static const FusedKernel k[3][sizeof...(D)] = {{k_hvp_fused_pipe<float, D + 1, 1>...},
+                                                 {k_hvp_fused_pipe<float, D + 1, 2>...},
+                                                 {k_hvp_fused_pipe<float, D + 1, 8>...}};
   return k[c <= 16 ? 0 : c <= 32 ? 1 : 2][D16 - 1];
 }
 
@@ -1067,7 +1109,7 @@ bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise)
   p->part_elems = splits * (int64_t)d * s * c;
   // one column block a wave: the pipelined kernel where its buffers fit in LDS
   const size_t pipe_lds = 4 * ((size_t)4 * kRC * g.XS + (size_t)3 * g.CP * g.GT +
-                               (size_t)3 * pipe_hbuf(c));
+                               (size_t)3 * pipe_hbuf(kRC, c));
   const bool pipe = !bf3 && ncb == 1 && pipe_lds <= 156 * 1024;
   if (pipe) lds_bytes = pipe_lds;
   p->kernel = bf3 ? (void*)pick_bf3(D16, ncb) : pipe ? (void*)pick_pipe(D16, c, std::make_integer_sequence<int, 8>{})
@@ -1124,6 +1166,71 @@ int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_
                         skip);
   FIRAL_LAUNCHED();
   return reduce_parts_launch<float>(part, (int64_t)x->d * SC, p.n_splits, shift, B, out, skip, st);
+}
+
+// ------------------------------------------------------------- FP64
+// The pipelined kernel for FP64 contexts, one pass over the rows instead of G' written and read
+// again by the two row-tiled kernels, whose launches are most of a small call: N = 2050, d = 20,
+// c = 5, s = 10 27 -> 12.6 us; N = 50,010, d = 100, c = 10, s = 20 202 -> 121 us; N = 200,000, d = 30,
+// c = 10, s = 10 443 -> 109 us; N = 20,000, d = c = 100, s = 2 96 -> 81 us.  It was the faster one at
+// every shape measured that fits its LDS.
+struct Fused64 {
+  int D16, pp, n_ct, CP, splits;
+  int64_t rps;
+  size_t lds;
+};
+static bool fused64_plan(int d, int c, int s, int64_t n_rows, Fused64* p) {
+  constexpr int RC = pipe_rc<double>;
+  p->D16 = (d + 15) / 16;
+  if (p->D16 > 8 || c > kNW * 16 || n_rows <= 0) return false;
+  p->pp = std::min(s, kNW * 16 / c);
+  p->n_ct = (int)cdiv(s, p->pp);
+  p->pp = (int)cdiv(s, p->n_ct);
+  p->CP = 16 * (int)cdiv(p->pp * c, 16);
+  p->lds = 8 * ((size_t)4 * RC * (16 * p->D16 + 4) + (size_t)3 * p->CP * (RC + 4) +
+                (size_t)3 * pipe_hbuf(RC, c));
+  if (p->lds > 156 * 1024) return false;
+  const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(cdiv(n_rows, RC), 256 / p->n_ct));
+  p->rps = cdiv(cdiv(n_rows, splits), RC) * RC;
+  p->splits = (int)cdiv(n_rows, p->rps);
+  return true;
+}
+// scratch for its partial sums with any s <= s_max (tiles of at most 128 columns, 256 of them)
+size_t fused64_bytes(int d, int c, int s_max) {
+  return d <= 128 && c <= kNW * 16
+             ? (size_t)256 * d * std::min<int64_t>(kNW * 16, (int64_t)s_max * c) * 8 : 0;
+}
+
+template <int... D>
+static FusedKernel64 pick_pipe64(int D16, int c, std::integer_sequence<int, D...>) {
+  static const FusedKernel64 k[2][sizeof...(D)] = {{k_hvp_fused_pipe<double, D + 1, 1>...},
+                                                   {k_hvp_fused_pipe<double, D + 1, 4>...}};
+  return k[c <= 32 ? 0 : 1][D16 - 1];
+}
+
+int hvp_fused64_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const double* B,
+                       double* out, int s, Skip skip, hipStream_t st, bool* taken) {
+  Fused64 p;
+  const int d = x->d, c = x->c, SC = s * c;
+  *taken = fused64_plan(d, c, s, n_rows, &p) && (size_t)p.splits * d * SC * 8 <= x->g_bytes;
+  if (!*taken) return FIRAL_OK;
+  FusedKernel64 k = pick_pipe64(p.D16, c, std::make_integer_sequence<int, 8>{});
+  static DeviceOnce once[2][8];
+  DeviceOnce& o = once[c <= 32 ? 0 : 1][p.D16 - 1];
+  if (!o.done()) {
+    FIRAL_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  156 * 1024));
+    o.set();
+  }
+  double* part = (double*)x->G;
+  hipEvent_t e0, e1;   // the kernel's own execution when profiling
+  FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT, &e0, &e1));
+  hipExtLaunchKernelGGL(k, dim3((unsigned)cdiv((int64_t)p.splits * p.n_ct, 8) * 8), dim3(kThreads),
+                        (uint32_t)p.lds, st, e0, e1, 0u, (const double*)x->X, (const double*)x->H,
+                        omega, n_rows, d, c, SC, B, p.pp, s, p.n_ct, p.rps, p.splits, 0, 0, 0, p.CP,
+                        part, XPlanes{}, skip);
+  FIRAL_LAUNCHED();
+  return reduce_parts_launch<double>(part, (int64_t)d * SC, p.splits, shift, B, out, skip, st);
 }
 
 }  // namespace firal
