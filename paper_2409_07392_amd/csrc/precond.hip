@@ -752,140 +752,213 @@ __global__ __launch_bounds__(TT* TT) void k_sweep(double* __restrict__ P, double
     }
 }
 
+constexpr int kSwLD = 17;   // row stride of a 16 x 16 block in LDS (odd: no bank conflicts by column)
+
+// x of one lane, uniform
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// the value of lane P of each row of 16 lanes
+template <int P> __device__ __forceinline__ double row_lane(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x150 + P, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x150 + P, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Sweep of the 16 x 16 pivot block in `Kb` (row stride kSwLD), in place, by one wave: lane (q, r) =
+// (l / 16, l % 16) holds row r, columns 4 q + k.  KIND names the form whose products and roundings it
+// takes (each form has its own).  Co[p][r]: what a column's sweep needs of pivot p, T_p[r]
+// (kSweepRows) or column p (kSweepPanel); Ro[p]: row p before its sweep; Ip[p]: 1 / pivot.  False when
+// a pivot is not positive.  What bounds it: the chain from pivot to pivot (update, 1 / pivot, product,
+// update); row p comes to the other rows by a broadcast within 16 lanes and column p by a permute,
+// both beside the division.
+enum SweepKind { kSweepRows, kSweepPanel, kSweepBlock };
+template <int KIND, int P>
+__device__ __forceinline__ bool sweep16_step(double (&b)[4], double* Co, double* Ro, double* Ip,
+                                             int r, int q, int lane) {
+  const double piv = lane_value(b[P & 3], P + 16 * (P >> 2));
+  const double ip = 1.0 / piv;
+  double apc[4];   // M[P][4 q + k]
+#pragma unroll
+  for (int k = 0; k < 4; ++k) apc[k] = row_lane<P>(b[k]);
+  double x;        // kSweepRows: M[P][r], else M[r][P]
+  if (KIND == kSweepRows) {
+    double y[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) y[k] = __shfl(apc[k], 16 * (r >> 2), 64);
+    x = (r & 2) ? ((r & 1) ? y[3] : y[2]) : ((r & 1) ? y[1] : y[0]);
+  } else {
+    x = __shfl(b[P & 3], r + 16 * (P >> 2), 64);
+  }
+  const double pri = x * ip;
+  if (KIND != kSweepBlock) {
+    if (q == 0) Co[P * 16 + r] = KIND == kSweepRows ? pri : x;
+    if (r == P) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Ro[P * 16 + 4 * q + k] = b[k];
+    }
+    if (lane == 0) Ip[P] = ip;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = 4 * q + k;
+    const double u = KIND != kSweepPanel ? fma(-pri, apc[k], b[k]) : fma(-(x * apc[k]), ip, b[k]);
+    b[k] = r != P ? (c != P ? u : pri) : (c != P ? apc[k] * ip : -ip);
+  }
+  return piv > 0.0;
+}
+template <int KIND, int... P>
+__device__ __forceinline__ bool sweep16_steps(double (&b)[4], double* Co, double* Ro, double* Ip,
+                                              int lane, std::integer_sequence<int, P...>) {
+  bool ok = true;
+  ((ok = sweep16_step<KIND, P>(b, Co, Ro, Ip, lane & 15, lane >> 4, lane) && ok), ...);
+  return ok;
+}
+template <int KIND>
+__device__ __forceinline__ bool sweep16(double* Kb, double* Co, double* Ro, double* Ip, int lane) {
+  const int r = lane & 15, cg = (lane >> 4) * 4;
+  double b[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) b[k] = Kb[r * kSwLD + cg + k];
+  const bool ok =
+      sweep16_steps<KIND>(b, Co, Ro, Ip, lane, std::make_integer_sequence<int, 16>{});
+#pragma unroll
+  for (int k = 0; k < 4; ++k) Kb[r * kSwLD + cg + k] = b[k];
+  return ok;
+}
+
 // Inverse of each SPD block (d <= 128) by the sweep operator taken sixteen pivots at a time,
 // for callers that do not ask for the factor.  Sweeping a pivot block K of the current
 // (symmetric) M gives M_KK <- N = -M_KK^-1, M_IK <- T_I = -M_IK N (and M_KI <- T_I^T),
 // M_IJ <- M_IJ - T_I M_KJ for the other rows and columns, the same matrix as sweeping K's
-// pivots one at a time; after every block M = -P^-1.  Thread (ty, tx) of 16 x 16 keeps
-// M[ty + 16u][tx + 16v] in registers (padding: identity); per block one wave sweeps the
-// 16 x 16 pivot block in registers (four entries a lane, shuffles, no barrier), then the
-// panel T goes through LDS and every thread updates its entries: four barriers per block.
-constexpr int kSwLD = 17;   // row stride of the LDS panels (odd: no bank conflicts by column)
-
-struct SweepLds {
-  double* Kb;   // [16][kSwLD] the pivot block, then N
-  double* PK;   // [DP][kSwLD] column panel M[i][K0 + m]
-  double* Tp;   // [DP][kSwLD] T[i][m]
-  int* fail;
-};
-
-// one pivot block K (a compile-time index into the register tile); false when a pivot of
-// the block is not positive (the workgroup stops)
-template <int K, int D16>
-__device__ __forceinline__ bool sweep_block(double (&a)[D16][D16], const SweepLds& L, int tid,
-                                            int32_t* bad, int kb) {
-  constexpr int LD = kSwLD;
-  const int ty = tid >> 4, tx = tid & 15;
-  // the pivot block and the column panel to LDS
-  L.Kb[ty * LD + tx] = a[K][K];
-#pragma unroll
-  for (int u = 0; u < D16; ++u) L.PK[(ty + 16 * u) * LD + tx] = a[u][K];
-  __syncthreads();
-  // 1. wave 0: N = sweep of the 16 x 16 block; lane l holds row l / 4, columns 4 (l % 4) + k
-  if (tid < 64) {
-    const int r = tid >> 2, cg = (tid & 3) * 4;
-    double b[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) b[k] = L.Kb[r * LD + cg + k];
-    bool ok = true;
-#pragma unroll
-    for (int p = 0; p < 16; ++p) {
-      const double piv = __shfl(b[p & 3], 4 * p + (p >> 2), 64);
-      ok = ok && piv > 0.0;
-      const double ip = 1.0 / piv;
-      const double arp = __shfl(b[p & 3], 4 * r + (p >> 2), 64);   // M[r][p]
-      double apc[4];                                                 // M[p][cg + k]
-#pragma unroll
-      for (int k = 0; k < 4; ++k) apc[k] = __shfl(b[k], 4 * p + (tid & 3), 64);
-      const double pri = arp * ip;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int c = cg + k;
-        b[k] = r != p ? (c != p ? fma(-pri, apc[k], b[k]) : pri) : (c != p ? apc[k] * ip : -ip);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) L.Kb[r * LD + cg + k] = b[k];
-    if (!__all(ok) && tid == 0) {
-      *L.fail = 1;
-      atomicMin(bad, kb);
-    }
-  }
-  __syncthreads();
-  if (*L.fail) return false;   // the same for every thread
-  // 2. T[i][c] = -sum_m M[i][K0 + m] N[m][c]
-#pragma unroll
-  for (int u = 0; u < D16; ++u) {
-    const int i = ty + 16 * u;
-    double t = 0.0;
-#pragma unroll
-    for (int m = 0; m < 16; ++m) t = fma(L.PK[i * LD + m], L.Kb[m * LD + tx], t);
-    L.Tp[i * LD + tx] = -t;
-  }
-  __syncthreads();
-  // 3. M_IJ -= T_I M_KJ (M_KJ[m][j] = M[j][K0 + m] by symmetry), one m at a time over the
-  //    thread's entries (not unrolled: the operands of one m at a time stay in registers);
-  //    then the panel becomes T and the pivot block N
-#pragma unroll 1
-  for (int m = 0; m < 16; ++m) {
-    double tu[D16], pv[D16];
-#pragma unroll
-    for (int u = 0; u < D16; ++u) tu[u] = L.Tp[(ty + 16 * u) * LD + m];
-#pragma unroll
-    for (int v = 0; v < D16; ++v) pv[v] = L.PK[(tx + 16 * v) * LD + m];
-#pragma unroll
-    for (int u = 0; u < D16; ++u)
-#pragma unroll
-      for (int v = 0; v < D16; ++v)
-        if (u != K && v != K) a[u][v] = fma(-tu[u], pv[v], a[u][v]);
-  }
-#pragma unroll
-  for (int u = 0; u < D16; ++u) {
-    a[u][K] = u == K ? L.Kb[ty * LD + tx] : L.Tp[(ty + 16 * u) * LD + tx];
-    if (u != K) a[K][u] = L.Tp[(tx + 16 * u) * LD + ty];
-  }
-  __syncthreads();
-  return true;
-}
-
-template <int D16, int... Ks>
-__device__ __forceinline__ bool sweep_blocks(double (&a)[D16][D16], const SweepLds& L, int tid,
-                                             int32_t* bad, int kb,
-                                             std::integer_sequence<int, Ks...>) {
-  return (sweep_block<Ks, D16>(a, L, tid, bad, kb) && ...);   // in order, stops at a failure
-}
-
+// pivots one at a time; after every block M = -P^-1.  M's 16 x 16 tiles stay in registers (padding:
+// identity), the diagonal ones in wave 0, the others dealt to seven waves.  Per block K: the column
+// panel is in LDS and N known; -T by FP64 MFMA, one tile a wave; then every wave updates its tiles by
+// MFMA and writes the next panel, while wave 0 updates the next pivot block first and sweeps it: two
+// barriers a block.  The products and sums are those of the form without MFMA (256 threads, the
+// pivot block between barriers), in its order (an FP64 MFMA adds its products one by one): solves in
+// FP32 keep their bits.  What bounds it: the chain of the pivots (sweep16; with its rows through LDS
+// 46 us).  c = 10, d = 100: 49 -> 38 us; c = 50, d = 50: 20.5 -> 16.6 us.
 template <int D16>
-__global__ __launch_bounds__(256) void k_sweep_blk(const double* __restrict__ P,
+__global__ __launch_bounds__(512) void k_sweep_blk(const double* __restrict__ P,
                                                    double* __restrict__ Pinv, int d,
                                                    int32_t* bad) {
-  constexpr int DP = 16 * D16;
-  __shared__ double Kb[16 * kSwLD];
-  __shared__ double PK[DP * kSwLD];
-  __shared__ double Tp[DP * kSwLD];
+  constexpr int DP = 16 * D16, LD = kSwLD, NOFF = D16 * (D16 - 1), NT = D16 > NOFF / 7 ? D16 : (NOFF + 6) / 7;
+  __shared__ double PK[2][DP * LD];   // [i][m] column panel M[i][K0 + m], two in turn
+  __shared__ double Ts[DP * LD];      // [i][m] -T
+  __shared__ double Kb[2][16 * LD];   // N, two in turn
   __shared__ int fail;
-  const int kb = blockIdx.x, tid = threadIdx.x;
-  const int ty = tid >> 4, tx = tid & 15;
+  const int kb = blockIdx.x, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, g = lane >> 4;
   const double* A0 = P + (int64_t)kb * d * d;
-  double a[D16][D16];
-#pragma unroll
-  for (int u = 0; u < D16; ++u)
-#pragma unroll
-    for (int v = 0; v < D16; ++v) {
-      const int i = ty + 16 * u, j = tx + 16 * v;
-      a[u][v] = (i < d && j < d) ? A0[(int64_t)i * d + j] : (i == j ? 1.0 : 0.0);
+  // tile n of this wave (in the MFMA's result layout: rows g + 4 v of column li)
+  auto tile_of = [&](int n, int& I, int& J) {
+    if (wave == 0) {
+      I = J = n;
+      return n < D16;
     }
-  if (tid == 0) fail = 0;   // seen by all after the first step's barrier
-  const SweepLds L{Kb, PK, Tp, &fail};
-  if (!sweep_blocks<D16>(a, L, tid, bad, kb, std::make_integer_sequence<int, D16>{})) return;
+    const int e = wave - 1 + 7 * n, i = e / (D16 > 1 ? D16 - 1 : 1), j = e - i * (D16 - 1);
+    I = i;
+    J = j + (j >= i);
+    return e < NOFF;
+  };
+  f64x4 t[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    int I, J;
+    const bool on = tile_of(n, I, J);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * I + g + 4 * v, j = 16 * J + li;
+      t[n][v] = on && i < d && j < d ? A0[(int64_t)i * d + j] : (i == j ? 1.0 : 0.0);
+    }
+  }
+  // the tile's part of panel K
+  auto dump = [&](int K) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      int I, J;
+      if (!tile_of(n, I, J) || J != K) continue;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) PK[K & 1][(16 * I + g + 4 * v) * LD + li] = t[n][v];
+    }
+  };
+  auto pivots = [&](const f64x4& x, int K) {   // by wave 0
+    double* kbk = Kb[K & 1];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) kbk[(g + 4 * v) * LD + li] = x[v];
+    wave_lds_fence();
+    if (!sweep16<kSweepBlock>(kbk, nullptr, nullptr, nullptr, lane) && lane == 0) {
+      fail = 1;
+      atomicMin(bad, kb);
+    }
+  };
+  if (threadIdx.x == 0) fail = 0;
+  if (wave == 0) {
+    wave_lds_fence();
+    pivots(t[0], 0);
+  }
+  dump(0);
+  __syncthreads();
+#pragma unroll
+  for (int K = 0; K < D16; ++K) {
+    if (fail) return;   // the same for every thread
+    const double* pk = PK[K & 1];
+    const double* nk = Kb[K & 1];
+    // -T[i][c] = sum_m M[i][K0 + m] N[m][c]
+    if (wave < D16) {
+      f64x4 u = Mfma16<double>::zero();
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        u = __builtin_amdgcn_mfma_f64_16x16x4f64(pk[(16 * wave + li) * LD + 4 * q + g],
+                                                 nk[(4 * q + g) * LD + li], u, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Ts[(16 * wave + g + 4 * v) * LD + li] = u[v];
+    }
+    __syncthreads();
+    auto update = [&](f64x4& x, int I, int J) {
+      if (I != K && J != K) {   // M_IJ -= T_I M_KJ (M_KJ[m][j] = M[j][K0 + m] by symmetry)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          x = __builtin_amdgcn_mfma_f64_16x16x4f64(Ts[(16 * I + li) * LD + 4 * q + g],
+                                                   pk[(16 * J + li) * LD + 4 * q + g], x, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          x[v] = I == J ? nk[(g + 4 * v) * LD + li]
+                        : J == K ? -Ts[(16 * I + g + 4 * v) * LD + li]
+                                 : -Ts[(16 * J + li) * LD + g + 4 * v];
+      }
+    };
+    if (wave == 0 && K + 1 < D16) {
+      update(t[K + 1], K + 1, K + 1);
+      pivots(t[K + 1], K + 1);
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      int I, J;
+      if (tile_of(n, I, J) && !(wave == 0 && n == K + 1)) update(t[n], I, J);
+    }
+    if (K + 1 < D16) dump(K + 1);
+    __syncthreads();
+  }
   double* Y = Pinv + (int64_t)kb * d * d;
 #pragma unroll
-  for (int u = 0; u < D16; ++u)
+  for (int n = 0; n < NT; ++n) {
+    int I, J;
+    const bool on = tile_of(n, I, J);
 #pragma unroll
-    for (int v = 0; v < D16; ++v) {
-      const int i = ty + 16 * u, j = tx + 16 * v;
-      if (i < d && j < d) Y[(int64_t)i * d + j] = -a[u][v];
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * I + g + 4 * v, j = 16 * J + li;
+      if (on && i < d && j < d) Y[(int64_t)i * d + j] = -t[n][v];
     }
+  }
 }
 
 // Inverse of each SPD block of 128 < d <= 576 for callers that do not ask for the factor: the
@@ -910,54 +983,6 @@ constexpr int kInvMaxD = 576, kInvTiles = 4;
 // row pitch of the LDS panels: 16 mod 32 doubles, so that the two k of half a wave's read meet no
 // bank twice
 template <bool ROWS> constexpr int kInvPitch = ROWS ? 272 : 592;
-
-// x of one lane, uniform
-__device__ __forceinline__ double lane_value(double x, int lane) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-
-// Sweep of the 16 x 16 pivot block in `Kb` (row stride kSwLD), in place, by one wave: lane l holds
-// row l / 4, columns 4 (l % 4) + k.  Co[p][r]: what a column's sweep needs of pivot p, T_p[r]
-// (ROWS) or column p; Ro[p]: row p before its sweep; Ip[p]: 1 / pivot.  False when a pivot is not
-// positive.
-template <bool ROWS>
-__device__ __forceinline__ bool sweep16(double* Kb, double* Co, double* Ro, double* Ip, int lane) {
-  const int r = lane >> 2, cg = (lane & 3) * 4;
-  double b[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) b[k] = Kb[r * kSwLD + cg + k];
-  bool ok = true;
-#pragma unroll
-  for (int p = 0; p < 16; ++p) {
-    const double piv = lane_value(b[p & 3], 4 * p + (p >> 2));
-    ok = ok && piv > 0.0;
-    const double ip = 1.0 / piv;
-    if (r == p) {    // row p for all lanes (one wave: its LDS accesses stay in order)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) Ro[p * 16 + cg + k] = b[k];
-    }
-    wave_lds_fence();
-    double apc[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) apc[k] = Ro[p * 16 + cg + k];
-    const double x = ROWS ? Ro[p * 16 + r] : __shfl(b[p & 3], 4 * r + (p >> 2), 64);
-    const double pri = x * ip;
-    if ((lane & 3) == 0) Co[p * 16 + r] = ROWS ? pri : x;
-    if (lane == 0) Ip[p] = ip;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int c = cg + k;
-      const double u = ROWS ? fma(-pri, apc[k], b[k]) : fma(-(x * apc[k]), ip, b[k]);
-      b[k] = r != p ? (c != p ? u : pri) : (c != p ? apc[k] * ip : -ip);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) Kb[r * kSwLD + cg + k] = b[k];
-  return __all(ok);
-}
 
 template <bool ROWS>
 __global__ __launch_bounds__(1024) void k_inv_mfma(const double* P, double* Pinv, int d,
@@ -998,7 +1023,7 @@ __global__ __launch_bounds__(1024) void k_inv_mfma(const double* P, double* Pinv
 #pragma unroll
     for (int w = 0; w < 4; ++w) Kb[(g + 4 * w) * kSwLD + li] = t[w];
     wave_lds_fence();
-    if (!sweep16<ROWS>(Kb, Co, Ro, Ip, lane) && lane == 0) {
+    if (!sweep16<ROWS ? kSweepRows : kSweepPanel>(Kb, Co, Ro, Ip, lane) && lane == 0) {
       fail = 1;
       atomicMin(bad, kb);
     }
@@ -1104,7 +1129,7 @@ __global__ __launch_bounds__(1024) void k_inv_mfma(const double* P, double* Pinv
 }
 
 typedef void (*InvKernel)(const double*, double*, int, int32_t*);
-// d <= 128 has the register sweep of 256 threads (k_sweep_blk); past d = 576 the two panels leave
+// d <= 128 has the form with its tiles in registers (k_sweep_blk); past d = 576 the two panels leave
 // LDS.  Between, the MFMA form was the faster one at every size measured, k_sweep or k_sweep_glb ->
 // it: two blocks of 129 0.157 -> 0.121 ms, of 160 0.193 -> 0.146, of 256 3.86 -> 0.41, of 257 2.89
 // -> 0.49, of 576 23.0 -> 3.8; 300 blocks of 129 0.329 -> 0.269, of 256 8.6 -> 1.04, of 384 18.4 ->
@@ -1411,7 +1436,7 @@ static int precond_t(Ctx* x, const double* omega, double shift, bool want_l, hip
   SweepBlkKernel sb = want_l ? nullptr : pick_sweep_blk(d);
   InvKernel iv = want_l ? nullptr : pick_inv(d);
   if (sb) {
-    sb<<<c, 256, 0, st>>>(x->P, x->Pinv, d, &x->status->bad_block);
+    sb<<<c, 512, 0, st>>>(x->P, x->Pinv, d, &x->status->bad_block);
     FIRAL_LAUNCHED();
   } else if (iv) {
     iv<<<c, 1024, 0, st>>>(x->P, x->Pinv, d, &x->status->bad_block);
@@ -1491,7 +1516,7 @@ int chol_blocks_launch(double* P, double* Pinv, int d, int c, int32_t* bad, bool
   SweepBlkKernel sb = want_l ? nullptr : pick_sweep_blk(d);
   InvKernel iv = want_l ? nullptr : pick_inv(d);
   if (sb) {
-    sb<<<c, 256, 0, st>>>(P, Pinv, d, bad);
+    sb<<<c, 512, 0, st>>>(P, Pinv, d, bad);
     FIRAL_LAUNCHED();
   } else if (iv) {
     iv<<<c, 1024, 0, st>>>(P, Pinv, d, bad);
