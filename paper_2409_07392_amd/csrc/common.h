@@ -81,6 +81,7 @@ struct Ctx {
   int64_t fused_part_elems;
   int fused_max_ncb;    // fused product: column blocks per wave, 2 (wide tiles) or 1 (two
                         // workgroups' registers per CU, next chunk fetched ahead)
+  void* slab;           // the one allocation behind the device buffers
   bool gram_packed;     // Gram blocks from packed operands (in G)
   size_t g_bytes;       // of G (the Gram kernel's packed operands, FP64 fused partials too)
   int gram_form;        // preconditioner Gram kernel (kGramClassic, kGramWide, kGramWideBf3)
@@ -356,6 +357,12 @@ int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_
 size_t fused64_bytes(int d, int c, int s_max);
 int hvp_fused64_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const double* B,
                        double* out, int s, Skip skip, hipStream_t st, bool* taken);
+
+struct SlabItem {
+  void** p;
+  size_t bytes;
+};
+int slab_alloc(const std::vector<SlabItem>& items, void** base);   // buffers of one object
 
 // ------------------------------------------------- host-side launchers
 // All enqueue on `st`; `skip` (see Skip) makes every kernel of the call return at once.
