@@ -40,6 +40,8 @@ sys.path.insert(0, ROOT)
 METRIC = "Relax iter time + HVP TFLOP/s, FP32 vs bf16x3 at ≤1e-4 rel grad error"
 # TFLOP/s, MI355X dense MFMA; bf16x3 counts the FP32-equivalent products of three bf16 passes
 PEAK = {"f32": 157.3, "f64": 78.6, "bf16x3": 2500.0 / 3}
+# firal_hvp on packed operands in FP32: six bf16-plane products per FP32 product (FP32 accuracy)
+PEAK_PACKED = {"f32": 2500.0 / 6, "bf16x3": 2500.0 / 3}
 HBM_PEAK = 8.0e12   # bytes/s, MI355X HBM3E
 
 
@@ -286,10 +288,9 @@ def headline(args):
     kern = leg["kernels"]
     dom = max(kern, key=lambda k: kern[k]["ms_per_product"])
     pre = "k_nt" if mprec == "f32" else "k_nt3"
-    kname = {"product": f"{pre}_xv (first contraction X V^T with the row sums of Lemma 1, "
-                        f"{mprec})",
-             "product_t": f"{pre}_xtg{'_m<3>' if p.d <= 384 else ''} (second contraction "
-                          f"X^T G'^T with the row step, {mprec})"}[dom]
+    how = {"f32": "FP32 as six bf16-plane products", "bf16x3": "bf16x3"}[mprec]
+    kname = {"product": f"k_pk_xv (first contraction X V with the row sums of Lemma 1, {how})",
+             "product_t": f"k_pk_xtg (second contraction X^T G' with the row step, {how})"}[dom]
     traffic_file = {"product": f"{pre}_xv_cfg4_traffic.md",
                     "product_t": f"{pre}_xtg_cfg4_traffic.md"}[dom]
     res = {
@@ -310,8 +311,8 @@ def headline(args):
                    "relax_iter_s_bf16x3": legs.get("bf16x3", {}).get("relax_iter_s")},
         "precision_legs": legs,
         "roofline": {"bound": "mfma", "kernel": kname,
-                     "achieved": kern[dom]["tflops"], "peak": PEAK[mprec], "unit": "TFLOP/s",
-                     "frac": kern[dom]["tflops"] / PEAK[mprec],
+                     "achieved": kern[dom]["tflops"], "peak": PEAK_PACKED[mprec],
+                     "unit": "TFLOP/s", "frac": kern[dom]["tflops"] / PEAK_PACKED[mprec],
                      "avg_launch_us": kern[dom]["avg_launch_us"],
                      "algorithmic_flop_per_launch": 2.0 * p.N * p.c * p.d * p.s /
                      max(kern[dom]["launches_per_product"], 1),
@@ -473,7 +474,7 @@ def round_leg(p, w, eta, fp32, cpu_rounds=2):
     t_cpu = (time.perf_counter() - tc) / cpu_rounds
     same = [int(i) for i in st.selected] == [int(i) for i in res["selected"][:cpu_rounds]]
     pk = PEAK["f32" if fp32 else "f64"]
-    kname = ("k_round_score<float, float> (per-point objective, FP32 MFMA; achieved counts "
+    kname = ("k_round_score_cls<float, float, 7> (per-point objective, FP32 MFMA; achieved counts "
              "2 n c d^2 per round)" if fp32 else
              "k_round_score<float, double> (per-point objective, FP64 MFMA; achieved counts "
              "2 n c d^2 per round)")
@@ -761,9 +762,9 @@ def workload2(args):
         "fp32_decision": round_leg(p, main_leg["w"], args.eta, True),
         "fp64_decision": round_leg(p, main_leg["w"], args.eta, False)}
     peak = PEAK[args.prec]
-    kname = {"f32": "k_hvp_fused (fused Lemma 1 product, FP32)",
+    kname = {"f32": "k_hvp_fused_pipe (fused Lemma 1 product, FP32)",
              "bf16x3": "k_hvp_fused_bf3 (fused Lemma 1 product, bf16x3)",
-             "f64": "k_xv (row-tiled first contraction, FP64)"}[args.prec]
+             "f64": "k_hvp_fused_pipe (fused Lemma 1 product, FP64)"}[args.prec]
     tfile = {"f32": "k_hvp_fused_cfg2_traffic.md", "bf16x3": "k_hvp_fused_bf3_cfg2_traffic.md",
              "f64": ""}[args.prec]
     res = {

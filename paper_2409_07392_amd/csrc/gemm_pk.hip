@@ -266,8 +266,15 @@ constexpr size_t pk_xv_lds() {
 }
 
 // Kernel 1: tile of 128 rows x 128 columns, four waves of 32 rows each.  X blocks go straight from
-// memory to the wave's registers (no other wave reads them), the tile's V blocks through two LDS
+// memory to the wave's registers (no other wave reads them), the tile's V blocks through kPkBufs LDS
 // buffers shared by the four; the next stage's loads are in flight during the stage's MFMAs.
+// What bounds it: in FP32 the MFMA rate (70% of what a large product reaches; the rest is the fill of
+// the pipeline and the epilogue, whose vector instructions issue one per MFMA beside another wave's
+// FP32 MFMA); with bf16 planes the tile's way from L2 and LDS to the matrix cores (1.2 of 2.1 PFLOP/s
+// at three planes) and G's way to memory.  The products as wholes, before (row-tiled tiles, or
+// transposed operands staged through LDS) and now: d = 256, c = 100, s = 32, N = 200,100 bf16x3 5.57
+// -> 2.53 ms; d = 384, c = 1000, s = 16, N = 1,282,000 FP32 entry 296 -> 160 ms; d = 203, c = 37, s =
+// 7, N = 30,048 FP32 entry 197 -> 100 us; the gradient at d = 256, c = 100, s = 32 FP32 11.0 -> 6.2 ms.
 // kPkDot: dpart[ct][row] = sum over the tile's columns of G_u (G - alpha) h, G and alpha those of
 // the earlier kPkFlat call on W.
 template <int AR, int MODE>
@@ -601,7 +608,8 @@ __global__ __launch_bounds__(256) void k_pk_alpha(const double* __restrict__ apa
 // waves covers NW MI 16-row blocks of the output (all of d up to 8 x 48) for a 128-column tile;
 // each wave owns MI of them, its X^T blocks straight from memory to registers, while G' is formed
 // once per workgroup: 16-column blocks wave, wave + NW of each 32-row stage, G and h of the next
-// stage in flight during the stage's MFMAs, through two LDS buffers.
+// stage in flight during the stage's MFMAs, through kPkBufs LDS buffers.  What bounds it: as
+// k_pk_xv; G is read from memory once.
 template <int AR, int MI, int TASKS, bool WIN>
 __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     const float* __restrict__ XTp, int nab, int d, const float* __restrict__ G, int64_t nrb,
