@@ -385,7 +385,8 @@ __global__ __launch_bounds__(256, 2) void k_syrkw(const float* __restrict__ X,
 // fitted to c (100 classes: 7 blocks, not 8) and the equal runs below (16.3 and 19.9 ms without).
 // The order of the rows of an accumulator's sum is that of the kernels which read X and H as they
 // are: instruction q of a 16-row block takes rows 4 g + q (kGramWide) or 4 q + g.
-constexpr int kGramMaxWgs = 4096, kGramMinStages = 16, kGramCutStages = 64;
+constexpr int kGramMaxWgs = 4092, kGramMinStages = 16, kGramCutStages = 64;
+constexpr int64_t kGramFlagBytes = 16384;   // a flag a workgroup, the counter
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_gram_pack(const float* __restrict__ X,
                                                    const float* __restrict__ H,
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(256) void k_gram_pack(const float* __restrict__ X,
                                                    int32_t* __restrict__ done) {
   const int sp = blockIdx.x / T, t = blockIdx.x % T;
   if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int e = threadIdx.x; e < kGramMaxWgs; e += 256) done[e] = 0;
+    for (int e = threadIdx.x; e <= kGramMaxWgs; e += 256) done[e] = 0;   // flags and counter
   const int64_t rb = (int64_t)sp * rps, re = rb + rps < N ? rb + rps : N;
   const int64_t r0 = rb + (int64_t)(stage0 + t) * 32;
   if (r0 >= re) return;   // never read
@@ -436,8 +437,9 @@ __global__ __launch_bounds__(256) void k_gram_pack(const float* __restrict__ X,
 // empty: 1088 units on 512 slots at d = 256, c = 100).  A run is at least a unit long, so a unit
 // is cut at most once, and its sum is carried over the cut through `part`: a workgroup takes the
 // head of its last unit first and the tail of its first unit last, for which the workgroup before
-// it has then had as much time as the head takes.  That workgroup's head waits for nothing and
-// was dispatched earlier, so the wait ends.  Units of under 64 stages are not cut: what a run
+// it has then had as much time as the head takes.  Runs are dealt by a counter in the order in which
+// workgroups start, so the workgroup waited for is running, whatever else the device runs and in
+// whatever order its dies take workgroups, and its head waits for nothing: the wait ends.  Units of under 64 stages are not cut: what a run
 // exchanges then costs more than the uneven last round (c = 1000, d = 400, N = 500, 16 stages: 4.07
 // ms, cut 4.43).
 // workgroups that a CU's registers hold
@@ -454,8 +456,15 @@ __global__ __launch_bounds__(256, gram_wgs_per_cu(CMW)) void k_gram(
   const int tid = threadIdx.x, lane = tid & 63;
   const int li = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ int ticket;
+  int id = blockIdx.x;
+  if ((int)gridDim.x < units) {   // units may be cut
+    if (tid == 0) ticket = atomicAdd(done + kGramMaxWgs, 1);
+    __syncthreads();
+    id = __builtin_amdgcn_readfirstlane(ticket);
+  }
   const int64_t total = (int64_t)units * nkc, run = (total + gridDim.x - 1) / gridDim.x;
-  const int64_t lo = blockIdx.x * run, hi = lo + run < total ? lo + run : total;
+  const int64_t lo = id * run, hi = lo + run < total ? lo + run : total;
   if (lo >= hi) return;
   const int u0 = (int)(lo / nkc), u1 = (int)((hi - 1) / nkc);
 
@@ -476,7 +485,7 @@ __global__ __launch_bounds__(256, gram_wgs_per_cu(CMW)) void k_gram(
     const int b = b0 + li;
     if (kb > 0) {
       if (tid == 0)
-        while (__hip_atomic_load(done + blockIdx.x - 1, __ATOMIC_ACQUIRE,
+        while (__hip_atomic_load(done + id - 1, __ATOMIC_ACQUIRE,
                                  __HIP_MEMORY_SCOPE_AGENT) == 0)
           __builtin_amdgcn_s_sleep(8);
       __syncthreads();
@@ -577,7 +586,7 @@ __global__ __launch_bounds__(256, gram_wgs_per_cu(CMW)) void k_gram(
     if (ke < nkc) {
       __syncthreads();   // the other waves' sums are out: thread 0 releases them with its own
       if (tid == 0)
-        __hip_atomic_store(done + blockIdx.x, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(done + id, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -1369,7 +1378,7 @@ static int64_t gram_stage_bytes(const Ctx* x) {
 // Scratch that a context holds at least (its product buffer, mostly larger): 32 stages a split, so
 // that taking the sums out of `part` and back is little beside them, or all there are.
 int64_t gram_min_bytes(const Ctx* x) {
-  return kGramMaxWgs * 4 +
+  return kGramFlagBytes +
          gram_stage_bytes(x) * std::min<int64_t>(32, cdiv(cdiv(x->N, x->syrk_splits), 32));
 }
 
@@ -1379,9 +1388,9 @@ static int gram_launch(Ctx* x, const double* omega, int64_t rps, hipStream_t st)
   const int nab = (int)cdiv(x->d, 16), S = x->syrk_splits;
   const int64_t stages = cdiv(rps, 32);
   const int T = (int)std::min<int64_t>(
-      stages, ((int64_t)x->g_bytes - kGramMaxWgs * 4) / gram_stage_bytes(x));
+      stages, ((int64_t)x->g_bytes - kGramFlagBytes) / gram_stage_bytes(x));
   int32_t* done = (int32_t*)x->G;
-  f32x4* U = (f32x4*)(done + kGramMaxWgs);
+  f32x4* U = (f32x4*)((char*)x->G + kGramFlagBytes);
   f32x4* XP = U + (int64_t)S * T * nct * cmw * 128;
   auto pack = x->gram_form == kGramClassic ? k_gram_pack<false> : k_gram_pack<true>;
   typedef void (*K)(const f32x4*, const f32x4*, int64_t, int, int, const int32_t*, int, int, int,
