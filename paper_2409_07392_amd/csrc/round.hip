@@ -334,19 +334,20 @@ __global__ __launch_bounds__(kTriThreads) void k_tridiag(double* __restrict__ A,
 // The same reduction for d <= 128 with the block in registers: thread (ty, tx) of 16 x 16
 // keeps A[ty + 16u][tx + 16w] (zero padding).  Per step two barriers: column j goes to LDS; every
 // thread forms the reflector and beta for itself (each wave sums the squares), its part of A v, and
-// the wave the sums of its rows (a row's sixteen parts lie in one wave: they pass through LDS, two
-// lanes a row) and its part of v . A v; after the second barrier every thread has p = beta A v and
+// the wave the sums of its rows (a row's sixteen parts lie in one wave: they pass through LDS, a
+// lane a row); after the second barrier every wave sums p . v, p = beta A v, and every thread has
 // K = (beta/2) p . v and updates its entries.  v and p are zero on the finished rows 0..j, so the
 // rank-2 update leaves them alone; the blocks of finished rows and columns are skipped (the columns
 // are walked in blocks of 16, a compile-time index into the register tile).
-// What bounds it: the latency of a step's chain (sum, square root, A v, sum).  c = 10, d = 100: 193 us
-// with four barriers and the scalar work of a step in one wave -> 114 us; c = 50, d = 50 58 -> 48 us.
+// The order of every sum is fixed (squares and p . v: lane l takes rows r0 + 1 + l and l, a row's
+// parts one after the other): nu follows the eigenvalues to the bit, and the FP32 copy of the
+// operand that is formed with it rounds to the other neighbour when nu moves in its last bits.
+// What bounds it: the latency of a step's chain (sum, square root, A v, sums).
 constexpr int kTriRS = 18;   // row stride of the parts of A v in LDS (16-byte aligned)
 struct TriLds {
   double* col;   // [2][128] column j of the current matrix, alternate by step
   double* p;     // [128] beta A v
   double* part;  // this wave's parts of A v, [4 D16][kTriRS]
-  double* pv;    // [4] v . A v by wave
   double* dg;    // [128]
   double* of;    // [128]
 };
@@ -369,14 +370,15 @@ __device__ __forceinline__ void tri_block(double (&a)[D16][D16], const TriLds& L
     }
     __syncthreads();
     // the reflector v (zero on rows 0..j) and beta
-    double vq[D16], vi[D16];
+    double vq[D16], vi[D16], vl[2];
     const double x0 = col[r0];
     double sg = 0.0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int i = lane + 64 * h;
-      const double x = i > r0 && i < 16 * D16 ? col[i] : 0.0;
+      const int i = r0 + 1 + lane + 64 * h, l = lane + 64 * h;
+      const double x = i < d ? col[i] : 0.0;
       sg = fma(x, x, sg);
+      vl[h] = l > r0 && l < 16 * D16 ? col[l] : 0.0;
     }
 #pragma unroll
     for (int w = J; w < D16; ++w) {
@@ -400,29 +402,35 @@ __device__ __forceinline__ void tri_block(double (&a)[D16][D16], const TriLds& L
         vi[w] = ty + 16 * w == r0 ? v0 : vi[w];
       }
     }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) vl[h] = lane + 64 * h == r0 ? v0 : vl[h];
     // A v: this thread's parts, then its wave's rows
-    double pv = 0.0;
 #pragma unroll
     for (int u = J; u < D16; ++u) {
       double sp = 0.0;
 #pragma unroll
       for (int w = J; w < D16; ++w) sp = fma(a[u][w], vq[w], sp);
       L.part[(4 * u + (ty & 3)) * kTriRS + tx] = sp;
-      pv = fma(vi[u], sp, pv);
     }
     wave_lds_fence();
-    if (lane >> 1 < 4 * D16) {
-      const double* q = L.part + (lane >> 1) * kTriRS + 8 * (lane & 1);
-      double s = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
-      s += lane_xor1(s);
-      const int i = (ty & ~3) + (lane >> 1 & 3) + 16 * (lane >> 3);
-      if ((lane & 1) == 0) L.p[i] = i > j ? beta * s : 0.0;
+    if (lane < 4 * D16) {
+      const double* q = L.part + lane * kTriRS;
+      double s = 0.0;
+#pragma unroll
+      for (int t = 0; t < 16; ++t) s += q[t];
+      const int i = (ty & ~3) + (lane & 3) + 16 * (lane >> 2);
+      L.p[i] = i > j ? beta * s : 0.0;
     }
-    pv = wave_sum(pv);
-    if (lane == 0) L.pv[tid >> 6] = pv;
     __syncthreads();
     // w = p - K v; A -= v w^T + w v^T on this thread's entries
-    const double K = 0.5 * beta * (beta * ((L.pv[0] + L.pv[1]) + (L.pv[2] + L.pv[3])));
+    double pv = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (64 * h < 16 * D16) {
+        const int l = lane + 64 * h;
+        pv = fma(l < 16 * D16 ? L.p[l] : 0.0, vl[h], pv);
+      }
+    const double K = 0.5 * beta * wave_sum(pv);
     double wi[D16], wq[D16];
 #pragma unroll
     for (int u = J; u < D16; ++u) {
@@ -446,7 +454,7 @@ template <int D16>
 __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all, int d,
                                                      double* __restrict__ diag,
                                                      double* __restrict__ off) {
-  __shared__ double col[2 * 128], p[128], pv[4], dg[128], of[128];
+  __shared__ double col[2 * 128], p[128], dg[128], of[128];
   __shared__ __align__(16) double part[4][4 * D16 * kTriRS];
   const int blk = blockIdx.x, tid = threadIdx.x;
   const int ty = tid >> 4, tx = tid & 15;
@@ -459,7 +467,7 @@ __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all,
       const int i = ty + 16 * u, j = tx + 16 * q;
       a[u][q] = i < d && j < d ? Ag[(int64_t)i * d + j] : 0.0;
     }
-  const TriLds L{col, p, part[tid >> 6], pv, dg, of};
+  const TriLds L{col, p, part[tid >> 6], dg, of};
   tri_blocks<D16>(a, L, d, tid, std::make_integer_sequence<int, D16>{});
   // the last 2 x 2 (or 1 x 1) block
 #pragma unroll
@@ -481,100 +489,162 @@ __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all,
   }
 }
 
-// Eigenvalues of each tridiagonal (diag a, off-diagonal e) on Sturm counts: with the leading minors
-// p_i = (a_i - x) p_i-1 - e_i-1^2 p_i-2 of T - x I, the number of changes of sign is the number of
-// eigenvalues below x (monotone in x).  Eigenvalue j starts from Gershgorin's bounds; S lanes of a
-// wave share it and each evaluates one of S interior points of its bracket, a ballot finds the first
-// point above the eigenvalue, and the bracket shrinks (S + 1)-fold per step (S = 1: bisection).
+// Eigenvalues of each tridiagonal (diag a, off-diagonal e) on Sturm counts: the number of
+// negative pivots of the LDL^T factorisation of T - x I is the number of eigenvalues below x
+// (monotone in x).  Eigenvalue j starts from Gershgorin's bounds; S lanes of a wave share it
+// and each evaluates one of S interior points of its bracket, a ballot finds the first point
+// above the eigenvalue, and the bracket shrinks (S + 1)-fold per step (S = 1: bisection).
 // Steps stop once the bracket is within 4 u ||T|| + 4 u |x| (u = 2^-53, the accuracy of the
-// counts) or stops shrinking.
-// T is scaled by a power of two to a norm below one (exact), and p_i, p_i-1 by one every eight steps,
-// so that no minor leaves the range.  e^2 is at least 2^-120 (e moves by 2^-60 ||T|| at most, far
-// below the bracket's width): after a minor of exactly zero the next one has the sign opposite to
-// the one before, one change whichever sign the zero has, and the recurrence does not stop there.
-// What bounds it: the chain of d dependent steps, one fma each.  The pivots q_i = p_i / p_i-1 need a
-// division a step: d = 100, c = 10 63 -> 23 us, d = 50, c = 50 69 -> 24 us.
+// counts) or stops shrinking.  Pivots smaller than pivmin are replaced by -pivmin (LAPACK's
+// safeguard).
+// What bounds it: the chain of d dependent steps of a count, with a division in each.  The changes of
+// sign of the leading minors p_i = (a_i - x) p_i-1 - e_i-1^2 p_i-2 count the same with one fma a
+// step, except where x lies within rounding of an eigenvalue.  So the wide brackets are cut by minors;
+// then the pivots are counted at both ends of every bracket so obtained (the lanes of a group hold
+// them), the steps whose brackets they confirm stand, and the rest are taken by pivots.  As the count
+// of pivots is monotone in x, a bracket that has its ends on the right sides of the eigenvalue is the
+// one that pivots alone give: the eigenvalues are theirs to the bit.
+// The minors are those of T scaled by a power of two to a norm below one, with e^2 at least 2^-120;
+// p_i and p_i-1 are scaled by one every eight steps, by the larger, so that they stay in range.
 // Grid: (block, eigenvalue range of 256 / S).
 template <int S>
 __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
                                                const double* __restrict__ off, int d,
                                                double* __restrict__ lam) {
   constexpr int EPW = 256 / S;
-  __shared__ __align__(16) double ae[2 * kMaxD];   // a_i, e_i-1^2
-  __shared__ double bnd[2];
+  constexpr int kKept = S > 1 ? S / 2 : 1;         // brackets by minors that the lanes hold
+  constexpr double kWide = S > 1 ? 0x1p-40 : 0x1p-30;
+  __shared__ double a[kMaxD], e2[kMaxD];
+  __shared__ __align__(16) double ae[2 * kMaxD];   // scaled: a_i, e_i-1^2
+  __shared__ double bnd[3];
   const int blk = blockIdx.x, tid = threadIdx.x;
   const double* dg = diag + (int64_t)blk * d;
   const double* of = off + (int64_t)blk * d;
-  double lo = INFINITY, hi = -INFINITY;
+  double lo = INFINITY, hi = -INFINITY, emax = 0.0;
   for (int i = tid; i < d; i += blockDim.x) {
+    a[i] = dg[i];
     const double el = i > 0 ? fabs(of[i - 1]) : 0.0, er = i + 1 < d ? fabs(of[i]) : 0.0;
+    e2[i] = i + 1 < d ? of[i] * of[i] : 0.0;
     lo = fmin(lo, dg[i] - el - er);
     hi = fmax(hi, dg[i] + el + er);
+    emax = fmax(emax, er * er);
   }
   lo = -block_max<256>(-lo);
   hi = block_max<256>(hi);
+  emax = block_max<256>(emax);
   if (tid == 0) {
     bnd[0] = lo;
     bnd[1] = hi;
+    bnd[2] = 2.2250738585072014e-308 * fmax(1.0, emax);
   }
   __syncthreads();
-  const double nrm0 = fmax(fabs(bnd[0]), fabs(bnd[1]));
-  const int sh = nrm0 > 0.0 && nrm0 < INFINITY ? ilogb(nrm0) + 1 : 0;
-  for (int i = tid; i < d; i += blockDim.x) {
-    ae[2 * i] = ldexp(dg[i], -sh);
-    const double el = i > 0 ? ldexp(of[i - 1], -sh) : 0.0;
-    ae[2 * i + 1] = i > 0 ? fmax(el * el, 0x1p-120) : 0.0;
-  }
-  __syncthreads();
-  const double L0 = ldexp(bnd[0], -sh), H0 = ldexp(bnd[1], -sh);
+  const double L0 = bnd[0], H0 = bnd[1], pivmin = bnd[2];
   const double nrm = fmax(fabs(L0), fabs(H0));
-  const double tol = 4.0 * 1.1102230246251565e-16 * nrm + 2.2250738585072014e-308;
+  const bool scaled = nrm > 0x1p-500 && nrm < 0x1p500;   // else by pivots alone
+  const int sh = scaled ? ilogb(nrm) + 1 : 0;
+  if (scaled)
+    for (int i = tid; i < d; i += blockDim.x) {
+      ae[2 * i] = ldexp(dg[i], -sh);
+      const double el = i > 0 ? ldexp(of[i - 1], -sh) : 0.0;
+      ae[2 * i + 1] = i > 0 ? fmax(el * el, 0x1p-120) : 0.0;
+    }
+  __syncthreads();
+  const double tol = 4.0 * 1.1102230246251565e-16 * nrm + pivmin;
   const int sl = tid % S, j = blockIdx.y * EPW + tid / S;
   const int gshift = (tid & 63) / S * S;        // first lane of this lane's group in the wave
   constexpr unsigned long long kGroupMask = S == 64 ? ~0ull : (1ull << (S % 64)) - 1;
   const bool on = j < d;
+
+  auto pivots = [&](double x) {
+    double q = a[0] - x;
+    if (fabs(q) < pivmin) q = -pivmin;
+    int cnt = q < 0.0;
+    for (int i = 1; i < d; ++i) {
+      q = (a[i] - x) - e2[i - 1] / q;
+      if (fabs(q) < pivmin) q = -pivmin;
+      cnt += q < 0.0;
+    }
+    return cnt;
+  };
+  auto minors = [&](double x0) {
+    const double x = ldexp(x0, -sh);
+    double p0 = 1.0, p1 = 1.0;   // minors i - 2 and i - 1 (that of index -2 takes e^2 = 0)
+    uint32_t signs = 0;          // of the minors so far, the last one in bit 0
+    int cnt = 0, i = 0;
+    auto minor = [&](int i) {
+      const double t = ae[2 * i + 1] * p0;
+      p0 = p1;
+      p1 = fma(ae[2 * i] - x, p1, -t);
+      signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p1), 31);
+    };
+    for (; i + 8 <= d; i += 8) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) minor(i + n);
+      cnt += __popc((signs ^ (signs >> 1)) & 0xffu);
+      const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+      p0 = ldexp(p0, e);
+      p1 = ldexp(p1, e);
+    }
+    for (; i < d; ++i) {
+      minor(i);
+      cnt += (signs ^ (signs >> 1)) & 1u;
+    }
+    return cnt;
+  };
+
   double l = L0 - tol, u = H0 + tol;
-  bool active = on;
-  for (int it = 0; it < 200 && __any(active); ++it) {
+  // one step of the groups with `act` set; false where the bracket is final
+  auto step = [&](bool act, auto count) {
     const double h = (u - l) / (S + 1);
     const double x = l + (sl + 1) * h;
     int cnt = 0;
-    if (active) {
-      double p0 = 1.0, p1 = 1.0;   // minors i - 2 and i - 1 (that of index -2 takes e^2 = 0)
-      uint32_t signs = 0;          // of the minors so far, the last one in bit 0
-      auto minor = [&](int i) {
-        const double t = ae[2 * i + 1] * p0;
-        p0 = p1;
-        p1 = fma(ae[2 * i] - x, p1, -t);
-        signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p1), 31);
-      };
-      int i = 0;
-      for (; i + 8 <= d; i += 8) {
-#pragma unroll
-        for (int n = 0; n < 8; ++n) minor(i + n);
-        cnt += __popc((signs ^ (signs >> 1)) & 0xffu);
-        const int e = -max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
-        p0 = ldexp(p0, e);
-        p1 = ldexp(p1, e);
-      }
-      for (; i < d; ++i) {
-        minor(i);
-        cnt += (signs ^ (signs >> 1)) & 1u;
+    if (act) cnt = count(x);
+    const uint64_t m = __ballot(act && cnt > j);
+    if (!act) return false;
+    const unsigned long long bits = (m >> gshift) & kGroupMask;
+    const double nl = bits == 0 ? l + S * h : (bits & 1ull ? l : l + (__ffsll(bits) - 1) * h);
+    const double nu = bits == 0 ? u : l + __ffsll(bits) * h;
+    const bool more = nu - nl > tol + 4.0 * 1.1102230246251565e-16 * fmax(fabs(nl), fabs(nu)) &&
+                      !(nl == l && nu == u);
+    l = nl;
+    u = nu;
+    return more;
+  };
+
+  if (scaled) {
+    const double l0 = l, u0 = u, wide = kWide * nrm;
+    double kept = 0.0;   // S > 1: lanes 0 .. S/2 - 1 the lower, the others the upper ends
+    int nkept = 0;       // of this group
+    for (int it = 0; it < (S > 1 ? kKept : 64); ++it) {
+      const bool act = on && u - l > wide;
+      if (!__any(act)) break;
+      step(act, minors);
+      if (act) {
+        if (sl % kKept == it) kept = sl < kKept ? l : u;
+        nkept = it + 1;
       }
     }
-    const uint64_t m = __ballot(active && cnt > j);
-    if (active) {
+    if constexpr (S > 1) {
+      const bool held = sl % kKept < nkept;
+      const int cnt = held ? pivots(kept) : 0;
+      const uint64_t m = __ballot(held && (sl < kKept ? cnt <= j : cnt > j));
       const unsigned long long bits = (m >> gshift) & kGroupMask;
-      const double nl = bits == 0 ? l + S * h : (bits & 1ull ? l : l + (__ffsll(bits) - 1) * h);
-      const double nu = bits == 0 ? u : l + __ffsll(bits) * h;
-      if (!(nu - nl > tol + 4.0 * 1.1102230246251565e-16 * fmax(fabs(nl), fabs(nu))) ||
-          (nl == l && nu == u))
-        active = false;
-      l = nl;
-      u = nu;
+      const unsigned long long good = bits & (bits >> kKept) & ((1ull << kKept) - 1);
+      const int n = __ffsll(~good) - 1;   // brackets that stand
+      const double nl = __shfl(kept, gshift + (n > 0 ? n - 1 : 0), 64);
+      const double nu = __shfl(kept, gshift + kKept + (n > 0 ? n - 1 : 0), 64);
+      l = n > 0 ? nl : l0;
+      u = n > 0 ? nu : u0;
+    } else {
+      if (!(on && pivots(l) <= j && pivots(u) > j)) {
+        l = l0;
+        u = u0;
+      }
     }
   }
-  if (on && sl == 0) lam[(int64_t)blk * d + j] = ldexp(0.5 * (l + u), sh);
+  bool active = on;
+  for (int it = 0; it < 200 && __any(active); ++it) active = step(active, pivots);
+  if (on && sl == 0) lam[(int64_t)blk * d + j] = 0.5 * (l + u);
 }
 
 // ------------------------------------------------------------------ nu
@@ -583,60 +653,83 @@ __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
 // Newton steps on phi^-1/2 - 1 (close to linear in nu), replaced by bisection whenever they
 // leave the bracket; stops when the bracket or the step vanishes.  One workgroup; every thread
 // receives the sums over the waves and takes the same steps, so an iteration has one barrier (the
-// sums alternate between two places).  Up to kNuReg eigenvalues a thread stay in registers.
-// Four waves up to 4096 eigenvalues: c d = 2500 47 us with two reductions of four barriers and a
-// scalar step by one thread, 24 us in 16 waves -> 13 us; c d = 1000 14 us in one wave, 26 us in 16
-// -> 12.5 us.
-constexpr int kNuReg = 16;
-template <int kNuThreads>
-__global__ __launch_bounds__(kNuThreads) void k_round_nu(const double* __restrict__ lam, int64_t n,
-                                                         double eta, double* __restrict__ nu_out) {
-  constexpr int NW = kNuThreads / 64;
+// sums alternate between two places).  The order of the sums is that of NV threads, each taking
+// every NV-th eigenvalue, then its wave, then the waves in turn; a thread stands for NV / NT of
+// them, with up to UR eigenvalues of each in registers.  NV is 64 up to 2048 eigenvalues, else 1024.
+template <int NT, int NV, int UR>
+__global__ __launch_bounds__(NT) void k_round_nu(const double* __restrict__ lam, int64_t n,
+                                                 double eta, double* __restrict__ nu_out) {
+  constexpr int V = NV / NT, NW = NV / 64;
   __shared__ double red[2][2][NW];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  double lv[kNuReg];
+  double lv[V][UR];
   double mn = INFINITY;
 #pragma unroll
-  for (int u = 0; u < kNuReg; ++u) {
-    const int64_t e = tid + (int64_t)kNuThreads * u;
-    lv[u] = e < n ? lam[e] : INFINITY;
-    mn = fmin(mn, lv[u]);
-  }
-  for (int64_t e = tid + (int64_t)kNuThreads * kNuReg; e < n; e += kNuThreads) mn = fmin(mn, lam[e]);
-  for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));   // exact: any order
-  if (lane == 0) red[1][0][wave] = mn;
-  __syncthreads();
+  for (int v = 0; v < V; ++v) {
 #pragma unroll
-  for (int w = 0; w < NW; ++w) mn = fmin(mn, red[1][0][w]);
+    for (int u = 0; u < UR; ++u) {
+      const int64_t e = tid + NT * v + (int64_t)NV * u;
+      lv[v][u] = e < n ? lam[e] : INFINITY;
+      mn = fmin(mn, lv[v][u]);
+    }
+    for (int64_t e = tid + NT * v + (int64_t)NV * UR; e < n; e += NV) mn = fmin(mn, lam[e]);
+  }
+  for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));   // exact: any order
+  if constexpr (NT > 64) {
+    if (lane == 0) red[1][0][wave] = mn;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) mn = fmin(mn, red[1][0][w]);
+  }
   double lo = 1.0 - eta * mn, hi = sqrt((double)n) - eta * mn;
   double nu = lo;
   for (int it = 0; it < 300; ++it) {
-    double f = 0.0, fp = 0.0;
-    auto add = [&](double l) {
-      const double a = 1.0 / (nu + eta * l);
-      const double a2 = a * a;
-      f += a2;
-      fp += a2 * a;
-    };
+    double f[V], fp[V];
 #pragma unroll
-    for (int u = 0; u < kNuReg; ++u)
-      if (tid + (int64_t)kNuThreads * u < n) add(lv[u]);
-    for (int64_t e = tid + (int64_t)kNuThreads * kNuReg; e < n; e += kNuThreads) add(lam[e]);
-    f = wave_sum(f);
-    fp = wave_sum(fp);
-    double(*rd)[NW] = red[it & 1];
-    if (lane == 0) {
-      rd[0][wave] = f;
-      rd[1][wave] = fp;
-    }
-    __syncthreads();
-    f = fp = 0.0;
+    for (int v = 0; v < V; ++v) {
+      f[v] = fp[v] = 0.0;
+      auto add = [&](double l) {
+        double q;
+        if constexpr (NV == 64) {   // eta l is rounded by itself
+#pragma clang fp contract(off)
+          const double t = eta * l;
+          q = nu + t;
+        } else {
+          q = fma(eta, l, nu);
+        }
+        const double a = 1.0 / q;
+        f[v] = fma(a, a, f[v]);
+        fp[v] = fma(a, a * a, fp[v]);
+      };
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      f += rd[0][w];
-      fp += rd[1][w];
+      for (int u = 0; u < UR; ++u)
+        if (tid + NT * v + (int64_t)NV * u < n) add(lv[v][u]);
+      for (int64_t e = tid + NT * v + (int64_t)NV * UR; e < n; e += NV) add(lam[e]);
     }
-    const double phi = f, dphi = -2.0 * fp;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      f[v] = wave_sum(f[v]);
+      fp[v] = wave_sum(fp[v]);
+    }
+    double phi = f[0], dphi = fp[0];
+    if constexpr (NT > 64) {
+      double(*rd)[NW] = red[it & 1];
+      if (lane == 0) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          rd[0][wave + NT / 64 * v] = f[v];
+          rd[1][wave + NT / 64 * v] = fp[v];
+        }
+      }
+      __syncthreads();
+      phi = dphi = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        phi += rd[0][w];
+        dphi += rd[1][w];
+      }
+    }
+    dphi = -2.0 * dphi;
     if (phi > 1.0) lo = nu;
     else if (phi < 1.0) hi = nu;
     double nn;
@@ -651,6 +744,17 @@ __global__ __launch_bounds__(kNuThreads) void k_round_nu(const double* __restric
     if (stop) break;
   }
   if (tid == 0) *nu_out = nu;
+}
+
+static int round_nu_launch(const double* lam, int64_t n, double eta, double* nu, hipStream_t st) {
+  if (n <= 2048)
+    k_round_nu<64, 64, 32><<<1, 64, 0, st>>>(lam, n, eta, nu);
+  else if (n <= 4096)
+    k_round_nu<256, 1024, 4><<<1, 256, 0, st>>>(lam, n, eta, nu);
+  else
+    k_round_nu<1024, 1024, 16><<<1, 1024, 0, st>>>(lam, n, eta, nu);
+  FIRAL_LAUNCHED();
+  return FIRAL_OK;
 }
 
 // D_k = nu I + eta (C_k + O_k / b)
@@ -1354,11 +1458,7 @@ static int round_step_launch(Round* r, hipStream_t st) {
                                              r->Hacc, r->Ew, r->mask, r->flags + 1);
   FIRAL_LAUNCHED();
   FIRAL_CHECK(eigvals_launch(r, r->Ew, st));
-  if ((int64_t)c * d <= 256 * kNuReg)
-    k_round_nu<256><<<1, 256, 0, st>>>(r->lam, (int64_t)c * d, r->eta, r->nu + t + 1);
-  else
-    k_round_nu<1024><<<1, 1024, 0, st>>>(r->lam, (int64_t)c * d, r->eta, r->nu + t + 1);
-  FIRAL_LAUNCHED();
+  FIRAL_CHECK(round_nu_launch(r->lam, (int64_t)c * d, r->eta, r->nu + t + 1, st));
   FIRAL_CHECK(round_operand(r, r->nu + t + 1, st));
   r->t = t + 1;
   return FIRAL_OK;
