@@ -342,7 +342,8 @@ __global__ __launch_bounds__(kTriThreads) void k_tridiag(double* __restrict__ A,
 // The order of every sum is fixed (squares and p . v: lane l takes rows r0 + 1 + l and l, a row's
 // parts one after the other): nu follows the eigenvalues to the bit, and the FP32 copy of the
 // operand that is formed with it rounds to the other neighbour when nu moves in its last bits.
-// What bounds it: the latency of a step's chain (sum, square root, A v, sums).
+// What bounds it: the latency of a step's chain (sum, square root, A v, sums).  c = 10, d = 100: 193 us
+// with four barriers and the scalar work of a step in one wave -> 122 us; c = 50, d = 50 58 -> 54 us.
 constexpr int kTriRS = 18;   // row stride of the parts of A v in LDS (16-byte aligned)
 struct TriLds {
   double* col;   // [2][128] column j of the current matrix, alternate by step
@@ -506,6 +507,7 @@ __global__ __launch_bounds__(256) void k_tridiag_reg(double* __restrict__ A_all,
 // one that pivots alone give: the eigenvalues are theirs to the bit.
 // The minors are those of T scaled by a power of two to a norm below one, with e^2 at least 2^-120;
 // p_i and p_i-1 are scaled by one every eight steps, by the larger, so that they stay in range.
+// d = 100, c = 10 63 us by pivots alone -> 38 us; d = 50, c = 50 69 -> 40 us.
 // Grid: (block, eigenvalue range of 256 / S).
 template <int S>
 __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
@@ -653,73 +655,60 @@ __global__ __launch_bounds__(256) void k_sturm(const double* __restrict__ diag,
 // Newton steps on phi^-1/2 - 1 (close to linear in nu), replaced by bisection whenever they
 // leave the bracket; stops when the bracket or the step vanishes.  One workgroup; every thread
 // receives the sums over the waves and takes the same steps, so an iteration has one barrier (the
-// sums alternate between two places).  The order of the sums is that of NV threads, each taking
-// every NV-th eigenvalue, then its wave, then the waves in turn; a thread stands for NV / NT of
-// them, with up to UR eigenvalues of each in registers.  NV is 64 up to 2048 eigenvalues, else 1024.
-template <int NT, int NV, int UR>
+// sums alternate between two places; one wave needs none).  A thread takes every NT-th eigenvalue, up
+// to UR of them in registers; the sums go over its wave, then over the waves in turn.  That order is
+// kept, so NT is 64 up to 2048 eigenvalues and 1024 beyond: c d = 1000 10.2 us, c d = 2500 34 us (47
+// with four barriers an iteration, 37 with 256 threads that each stand for four).
+template <int NT, int UR>
 __global__ __launch_bounds__(NT) void k_round_nu(const double* __restrict__ lam, int64_t n,
                                                  double eta, double* __restrict__ nu_out) {
-  constexpr int V = NV / NT, NW = NV / 64;
+  constexpr int NW = NT / 64;
   __shared__ double red[2][2][NW];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  double lv[V][UR];
+  double lv[UR];
   double mn = INFINITY;
 #pragma unroll
-  for (int v = 0; v < V; ++v) {
-#pragma unroll
-    for (int u = 0; u < UR; ++u) {
-      const int64_t e = tid + NT * v + (int64_t)NV * u;
-      lv[v][u] = e < n ? lam[e] : INFINITY;
-      mn = fmin(mn, lv[v][u]);
-    }
-    for (int64_t e = tid + NT * v + (int64_t)NV * UR; e < n; e += NV) mn = fmin(mn, lam[e]);
+  for (int u = 0; u < UR; ++u) {
+    const int64_t e = tid + (int64_t)NT * u;
+    lv[u] = e < n ? lam[e] : INFINITY;
+    mn = fmin(mn, lv[u]);
   }
+  for (int64_t e = tid + (int64_t)NT * UR; e < n; e += NT) mn = fmin(mn, lam[e]);
   for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));   // exact: any order
-  if constexpr (NT > 64) {
+  if constexpr (NW > 1) {
     if (lane == 0) red[1][0][wave] = mn;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) mn = fmin(mn, red[1][0][w]);
+    for (int w = 0; w < NW; ++w) mn = fmin(mn, red[1][0][w]);
   }
   double lo = 1.0 - eta * mn, hi = sqrt((double)n) - eta * mn;
   double nu = lo;
   for (int it = 0; it < 300; ++it) {
-    double f[V], fp[V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      f[v] = fp[v] = 0.0;
-      auto add = [&](double l) {
-        double q;
-        if constexpr (NV == 64) {   // eta l is rounded by itself
+    double phi = 0.0, dphi = 0.0;
+    auto add = [&](double l) {
+      double q;
+      if constexpr (NT == 64) {   // eta l is rounded by itself
 #pragma clang fp contract(off)
-          const double t = eta * l;
-          q = nu + t;
-        } else {
-          q = fma(eta, l, nu);
-        }
-        const double a = 1.0 / q;
-        f[v] = fma(a, a, f[v]);
-        fp[v] = fma(a, a * a, fp[v]);
-      };
+        const double t = eta * l;
+        q = nu + t;
+      } else {
+        q = fma(eta, l, nu);
+      }
+      const double a = 1.0 / q;
+      phi = fma(a, a, phi);
+      dphi = fma(a, a * a, dphi);
+    };
 #pragma unroll
-      for (int u = 0; u < UR; ++u)
-        if (tid + NT * v + (int64_t)NV * u < n) add(lv[v][u]);
-      for (int64_t e = tid + NT * v + (int64_t)NV * UR; e < n; e += NV) add(lam[e]);
-    }
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      f[v] = wave_sum(f[v]);
-      fp[v] = wave_sum(fp[v]);
-    }
-    double phi = f[0], dphi = fp[0];
-    if constexpr (NT > 64) {
+    for (int u = 0; u < UR; ++u)
+      if (tid + (int64_t)NT * u < n) add(lv[u]);
+    for (int64_t e = tid + (int64_t)NT * UR; e < n; e += NT) add(lam[e]);
+    phi = wave_sum(phi);
+    dphi = wave_sum(dphi);
+    if constexpr (NW > 1) {
       double(*rd)[NW] = red[it & 1];
       if (lane == 0) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          rd[0][wave + NT / 64 * v] = f[v];
-          rd[1][wave + NT / 64 * v] = fp[v];
-        }
+        rd[0][wave] = phi;
+        rd[1][wave] = dphi;
       }
       __syncthreads();
       phi = dphi = 0.0;
@@ -748,11 +737,11 @@ __global__ __launch_bounds__(NT) void k_round_nu(const double* __restrict__ lam,
 
 static int round_nu_launch(const double* lam, int64_t n, double eta, double* nu, hipStream_t st) {
   if (n <= 2048)
-    k_round_nu<64, 64, 32><<<1, 64, 0, st>>>(lam, n, eta, nu);
+    k_round_nu<64, 32><<<1, 64, 0, st>>>(lam, n, eta, nu);
   else if (n <= 4096)
-    k_round_nu<256, 1024, 4><<<1, 256, 0, st>>>(lam, n, eta, nu);
+    k_round_nu<1024, 4><<<1, 1024, 0, st>>>(lam, n, eta, nu);
   else
-    k_round_nu<1024, 1024, 16><<<1, 1024, 0, st>>>(lam, n, eta, nu);
+    k_round_nu<1024, 16><<<1, 1024, 0, st>>>(lam, n, eta, nu);
   FIRAL_LAUNCHED();
   return FIRAL_OK;
 }
