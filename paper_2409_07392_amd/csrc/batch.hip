@@ -14,7 +14,7 @@
 // with one or two 16-column blocks per wave and 256, 512 or 1024 workgroups, i.e. rows per
 // workgroup, wherever its plan fits; or the row-tiled kernels) and PCG step forms
 // (column-local or separate kernels), keeps the fastest of each, and remembers the choice per
-// bucket (precision, d, c, s, n rounded to a power of two) for the process.
+// bucket (precision, d, c, s, n rounded to a power of two, packed products or not) for the process.
 #include <algorithm>
 #include <cmath>
 #include <map>
@@ -32,7 +32,8 @@ int pcg_launch(Ctx* x, const double* omega, double shift, const double* Pinv, co
 
 namespace {
 
-typedef std::tuple<int, int, int, int, int> TuneKey;   // prec, d, c, s, log2 N bucket
+// prec, d, c, s, log2 N bucket, packed products
+typedef std::tuple<int, int, int, int, int, int> TuneKey;
 
 std::mutex g_tune_mu;
 std::map<TuneKey, int> g_tune;   // choice bits: 1 = row-tiled product, 2 = separate-kernel
@@ -41,7 +42,7 @@ std::map<TuneKey, int> g_tune;   // choice bits: 1 = row-tiled product, 2 = sepa
 
 TuneKey tune_key(const Ctx* x, int s) {
   const int nb = (int)std::ceil(std::log2((double)std::max<int64_t>(x->N, 1)));
-  return TuneKey(x->prec, x->d, x->c, s, nb);
+  return TuneKey(x->prec, x->d, x->c, s, nb, x->use_pk);
 }
 
 void apply_choice(Ctx* x, int choice) {

@@ -345,7 +345,8 @@ struct FusedPlan {
   int64_t part_elems;   // n_splits * d * s * c
 };
 bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise = false);
-// whether the context's products fit the fused kernel (its plan for s_max probes)
+// whether the context's products fit the fused kernel (its plan for s_max probes; in bf16x3, where
+// only contexts that it may serve hold the planes it reads, the widest plan the tuner may choose)
 bool fused_covers(const Ctx* x);
 template <typename T>
 int reduce_parts_launch(const T* part, int64_t n, int P, double shift, const T* B, T* out,

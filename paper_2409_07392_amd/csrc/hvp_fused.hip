@@ -1079,6 +1079,7 @@ bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise)
   const int d = x->d, c = x->c;
   const int D16 = (d + 15) / 16;
   const bool bf3 = x->prec == FIRAL_BF16X3 && !precise;
+  if (bf3 && x->use_pk) return false;   // such a context holds no planes of X and X^T
   // above d = 128 the row-tiled kernels are faster (measured at d = 256, c = 100: 2x)
   if (D16 > 8) return false;
   const int max_ncb = x->fused_max_ncb;
@@ -1132,7 +1133,10 @@ bool fused_plan(const Ctx* x, int s, int64_t n_rows, FusedPlan* p, bool precise)
 
 bool fused_covers(const Ctx* x) {
   FusedPlan p;
-  return fused_plan(x, x->s_max, x->N, &p);
+  if (x->prec != FIRAL_BF16X3) return fused_plan(x, x->s_max, x->N, &p);
+  Ctx widest = *x;
+  widest.fused_max_ncb = 2;
+  return fused_plan(&widest, x->s_max, x->N, &p);
 }
 
 int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_rows, double shift,
