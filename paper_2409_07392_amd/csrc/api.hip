@@ -223,8 +223,10 @@ static int create_ctx(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, 
   x->fused_max_ncb = ncb ? (atoi(ncb) == 2 ? 2 : 1) : (prec == FIRAL_BF16X3 ? 2 : 1);
   // bf16x3: chunks start on multiples of 32 rows (the X^T planes are read 8 rows at a time);
   // so are the windows form's of the packed products
+  const char* unf = getenv("FIRAL_UNFUSED");
+  x->force_tiled = x->force_multik = unf && atoi(unf) != 0;
   const char* nt_env = getenv("FIRAL_NT");
-  x->use_pk = packed && prec != FIRAL_F64 && (d > 128 || !fused_covers(x)) &&
+  x->use_pk = packed && !x->force_tiled && prec != FIRAL_F64 && (d > 128 || !fused_covers(x)) &&
               !(nt_env && atoi(nt_env) == 0);
   if (prec == FIRAL_BF16X3 || (x->use_pk && pk_windows(prec, d, c)))
     rows = std::max<int64_t>(32, rows - rows % 32);
@@ -243,8 +245,6 @@ static int create_ctx(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, 
   x->col_parts = (int)std::max<int64_t>(1, std::min<int64_t>(d, cdiv(256, s_max)));
   x->red_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(n_pool, 256), 1024));
 
-  const char* unf = getenv("FIRAL_UNFUSED");
-  x->force_tiled = x->force_multik = unf && atoi(unf) != 0;
   // BF16X3 PCG: switch to FP32 products below this relative residual (0 = never).  With the
   // residual kept in the projected space the split products converge like FP32 ones, so
   // the switch is off unless asked for.
