@@ -53,8 +53,7 @@ typedef struct firal_ctx_s* firal_ctx;
 
 typedef enum {
   FIRAL_F64 = 0,     /* FP64 storage, FP64 MFMA */
-  FIRAL_F32 = 1,     /* FP32 storage, FP32 MFMA (firal_hvp beyond the fused kernels: each FP32 product
-                        as six products of exact bf16 planes, FP32 accuracy) */
+  FIRAL_F32 = 1,     /* FP32 storage, FP32 MFMA */
   FIRAL_BF16X3 = 2   /* FP32 storage, products as three bf16 MFMA passes (hi*hi + hi*lo + lo*hi) */
 } firal_prec;
 

@@ -392,8 +392,7 @@ int firal_hvp(firal_ctx ctx, const double* omega, int64_t n_rows, double shift, 
   FIRAL_REQ(B != out, "out must not alias B");
   FIRAL_REQ(n_rows >= 0 && n_rows <= x->N, "n_rows = %lld outside [0, %lld]", (long long)n_rows,
             (long long)x->N);
-  return hvp_launch(x, omega, n_rows, shift, B, out, s, skip_none(), (hipStream_t)stream, false,
-                    true);
+  return hvp_launch(x, omega, n_rows, shift, B, out, s, skip_none(), (hipStream_t)stream);
 }
 
 int firal_build_precond(firal_ctx ctx, const double* omega, double shift, double* L, double* Pinv,

@@ -367,11 +367,9 @@ int slab_alloc(const std::vector<SlabItem>& items, void** base);   // buffers of
 
 // ------------------------------------------------- host-side launchers
 // All enqueue on `st`; `skip` (see Skip) makes every kernel of the call return at once.
-// precise: in a BF16X3 context, take the FP32 products for this call (mixed-precision PCG);
-// entry: a call of firal_hvp itself, not of a solve
+// precise: in a BF16X3 context, take the FP32 products for this call (mixed-precision PCG)
 int hvp_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const void* B,
-               void* out, int s, Skip skip, hipStream_t st, bool precise = false,
-               bool entry = false);
+               void* out, int s, Skip skip, hipStream_t st, bool precise = false);
 // Gram blocks, then P^-1 into x->Pinv; the factor L goes to x->P only when want_l (for d <= 256
 // x->P otherwise keeps the Gram blocks)
 int precond_launch(Ctx* x, const double* omega, double shift, hipStream_t st, bool want_l = false);
@@ -404,7 +402,7 @@ int pcg_launch(Ctx* x, const double* omega, double shift, const double* Pinv, co
 int grad_launch(Ctx* x, const void* U, const void* W, int s, double* g, hipStream_t st);
 // packed-operand products (gemm_pk.hip): whether a shape takes the windows form of the row step,
 // buffer sizes in bytes (ldn: leading dimension of H^T) for the context's chunk_rows, the packed
-// operands of a context, the product (entry: a call of firal_hvp itself) and the gradient
+// operands of a context, the product and the gradient
 bool pk_windows(int prec, int d, int c);
 struct PkSizes {
   int64_t ldn;
@@ -413,7 +411,7 @@ struct PkSizes {
 PkSizes pk_sizes(const Ctx* x);
 int pk_prepare_ctx(Ctx* x, hipStream_t st);
 int hvp_pk_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const float* B,
-                  float* out, int s, bool entry, Skip skip, hipStream_t st);
+                  float* out, int s, Skip skip, hipStream_t st);
 bool grad_pk_applies(const Ctx* x);
 int grad_pk_launch(Ctx* x, const float* U, const float* W, int s, double* g, hipStream_t st);
 // general (any d, c) product through the row-tiled kernels of tiled.hip

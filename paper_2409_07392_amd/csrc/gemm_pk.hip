@@ -12,16 +12,9 @@
 // on U with an epilogue that sums U^T x (G - alpha) h over the tile's columns.
 //
 // Arithmetic of the products (PkArith):
-//   kPkF32  FP32 MFMA 16x16x4: the products inside FP32 solves and the FP32 gradient.
+//   kPkF32  FP32 contexts: FP32 MFMA 16x16x4.
 //   kPkB2   bf16x3 contexts: operands as two bf16 planes x_0 + x_1 (rounded to nearest even),
 //           x_0 y_0 + x_0 y_1 + x_1 y_0 on the 16x16x32 bf16 MFMA, FP32 accumulation.
-//   kPkX3   firal_hvp in FP32 contexts: three planes, which hold every FP32 value of magnitude
-//           above 2^-110 exactly (3 x 8 significant bits), and the six plane products of relative
-//           size 2^-18 or more; those dropped are below 2^-25, so a product keeps FP32's accuracy
-//           (measured against 64 bits: no larger an error than the FP32 MFMA's) while the matrix
-//           cores take 6 bf16 passes at 16 times the FP32 rate.  A non-finite operand may give NaN
-//           where FP32 arithmetic gives an infinity.  The solves stay on the FP32 MFMA: their
-//           iterates, and the FP64 arrays that they return, keep their rounding.
 //
 // Two forms of the row step (kept apart so that each problem keeps its order of summation):
 //   flat     column tiles run over the s c columns without regard to probes; G is stored as it is,
@@ -40,7 +33,7 @@
 //   bf16x3         half p: plane p, k = 8 g + u, u = 0..7
 //   X    [row block][k block]                 (context creation)
 //   X^T  [32-row block][a block]              (context creation)
-//   V    [column tile][k block][8 column blocks] (once per call; kPkX3: three 1 KB planes)
+//   V    [column tile][k block][8 column blocks] (once per call)
 //   G    [column tile][16-row block][8 column blocks] of 16 x 16 FP32 in the MFMA's result layout:
 //        lane (g, li) holds result rows 4 g .. 4 g + 3 of column li
 // The rows of each 32-row group are taken in the order (pk_row) that makes the lane's values of two
@@ -60,13 +53,10 @@ namespace {
 constexpr int kPkT = 128;             // rows and columns of a first-contraction tile
 constexpr int kPkMaxWaves = 8;        // waves of a second-contraction workgroup
 
-enum PkArith { kPkF32 = 0, kPkB2 = 1, kPkX3 = 2 };
+enum PkArith { kPkF32 = 0, kPkB2 = 1 };
 enum PkMode { kPkFlat = 0, kPkWin = 1, kPkDot = 2, kPkFlatX = 3 };
 
 typedef float f4 __attribute__((ext_vector_type(4)));
-
-// 1 KB parts of a block of V (and of G' in LDS).
-template <int AR> constexpr int pk_parts() { return AR == kPkX3 ? 3 : 2; }
 
 // Workgroup b of n runs on XCD b % 8; give each XCD a contiguous range of logical tiles.
 __device__ __forceinline__ unsigned pk_lid(unsigned b, unsigned n) {
@@ -89,43 +79,18 @@ __device__ __forceinline__ int pk_k32(int order, int h, int g, int q) {
   return 16 * h + (order == kPkRowQ ? 4 * q + g : 4 * g + q);
 }
 
-template <int P>
-__device__ __forceinline__ void pk_split8(const float (&v)[8], bf16x8 (&o)[P]) {
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    float r = v[u];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const __bf16 h = (__bf16)r;
-      o[p][u] = h;
-      if (p + 1 < P) r -= (float)h;
-    }
-  }
-}
-
-// Eight FP32 values of a lane (two f4 in k order) as the parts of an operand block.
+// Eight FP32 values of a lane (two f4 in k order) as the two parts of an operand block.
 template <int AR>
-__device__ __forceinline__ void pk_parts_of(const f4 (&y)[2], f4 (&o)[pk_parts<AR>()]) {
+__device__ __forceinline__ void pk_parts_of(const f4 (&y)[2], f4 (&o)[2]) {
   if constexpr (AR == kPkF32) {
     o[0] = y[0];
     o[1] = y[1];
   } else {
     const float v[8] = {y[0][0], y[0][1], y[0][2], y[0][3], y[1][0], y[1][1], y[1][2], y[1][3]};
-    bf16x8 b[pk_parts<AR>()];
-    pk_split8<pk_parts<AR>()>(v, b);
-#pragma unroll
-    for (int p = 0; p < pk_parts<AR>(); ++p) o[p] = __builtin_bit_cast(f4, b[p]);
-  }
-}
-
-// The row operand of a stage as the MFMAs take it, from its two 16-byte halves.
-template <int AR>
-__device__ __forceinline__ void pk_operand(const f4 (&raw)[2], f4 (&o)[pk_parts<AR>()]) {
-  if constexpr (AR == kPkX3) {
-    pk_parts_of<AR>(raw, o);
-  } else {
-    o[0] = raw[0];
-    o[1] = raw[1];
+    bf16x8 hi, lo;
+    split8(v, hi, lo);
+    o[0] = __builtin_bit_cast(f4, hi);
+    o[1] = __builtin_bit_cast(f4, lo);
   }
 }
 
@@ -147,12 +112,11 @@ __device__ __forceinline__ f4 pk_keep(f4 x, int lim, F row) {
   return x;
 }
 
-// A unit of a stage: the wave's MI row blocks (a, registers) times UJ column blocks (b, registers).
-// Every accumulator takes its products in the order of k (bf16: x_0 y_0, x_0 y_1, x_1 y_0 in
-// kPkB2, the smallest first in kPkX3); the MI UJ accumulators take turns.
-template <int AR, int MI, int UJ>
-__device__ __forceinline__ void pk_unit(const f4 (&a)[MI][pk_parts<AR>()],
-                                        const f4 (&b)[UJ][pk_parts<AR>()], int j0,
+// A unit of a stage: the wave's MI row blocks (a, registers) times two column blocks (b, registers).
+// Every accumulator takes its products in the order of k (bf16: x_0 y_0, x_0 y_1, x_1 y_0); the 2 MI
+// accumulators take turns.
+template <int AR, int MI>
+__device__ __forceinline__ void pk_unit(const f4 (&a)[MI][2], const f4 (&b)[2][2], int j0,
                                         f32x4 (&acc)[MI][8]) {
   if constexpr (AR == kPkF32) {
 #pragma unroll
@@ -160,19 +124,17 @@ __device__ __forceinline__ void pk_unit(const f4 (&a)[MI][pk_parts<AR>()],
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int q = 0; q < UJ; ++q)
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
           for (int i = 0; i < MI; ++i)
             acc[i][j0 + q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][h][e], b[q][h][e],
                                                                   acc[i][j0 + q], 0, 0, 0);
   } else {
-    constexpr int n = AR == kPkB2 ? 3 : 6;
-    constexpr int pa[6] = {AR == kPkB2 ? 0 : 2, 0, 1, 1, 0, 0};
-    constexpr int pb[6] = {0, AR == kPkB2 ? 1 : 2, AR == kPkB2 ? 0 : 1, 0, 1, 0};
+    constexpr int pa[3] = {0, 0, 1}, pb[3] = {0, 1, 0};
 #pragma unroll
-    for (int t = 0; t < n; ++t)
+    for (int t = 0; t < 3; ++t)
 #pragma unroll
-      for (int q = 0; q < UJ; ++q)
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int i = 0; i < MI; ++i)
           acc[i][j0 + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
@@ -183,18 +145,14 @@ __device__ __forceinline__ void pk_unit(const f4 (&a)[MI][pk_parts<AR>()],
 
 // The LDS stage buffers of both kernels: one is read, the next is complete, the third is written, so
 // that a unit's operands are read from LDS a unit ahead, across the stage barrier too.
-constexpr int kPkBufs = 3;
-template <int AR> constexpr int pk_buf() { return 8 * pk_parts<AR>() * 256; }   // floats
+constexpr int kPkBufs = 3, kPkBuf = 8 * 2 * 256;   // floats of one
 
-template <int AR, int UJ>
-__device__ __forceinline__ void pk_read(f4 (&b)[UJ][pk_parts<AR>()], const float* buf, int j0,
-                                        int lane) {
-  constexpr int P = pk_parts<AR>();
+__device__ __forceinline__ void pk_read(f4 (&b)[2][2], const float* buf, int j0, int lane) {
 #pragma unroll
-  for (int q = 0; q < UJ; ++q)
+  for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int p = 0; p < P; ++p)
-      b[q][p] = *reinterpret_cast<const f4*>(buf + ((j0 + q) * P + p) * 256 + lane * 4);
+    for (int p = 0; p < 2; ++p)
+      b[q][p] = *reinterpret_cast<const f4*>(buf + ((j0 + q) * 2 + p) * 256 + lane * 4);
 }
 
 // Keeps the compiler's scheduler from moving instructions across this point: the next stage's
@@ -258,9 +216,9 @@ struct PkCols {
 constexpr int kPkSegLd = kPkT + 1;   // LDS row stride of the narrow-probe epilogue
 constexpr int kPkSegC = 64;          // probes narrower than this are summed through LDS
 
-template <int AR, int MODE>
+template <int MODE>
 constexpr size_t pk_xv_lds() {
-  const size_t main_b = (size_t)kPkBufs * pk_buf<AR>() * 4;
+  const size_t main_b = (size_t)kPkBufs * kPkBuf * 4;
   const size_t seg_b = MODE == kPkFlat ? (size_t)4 * 16 * kPkSegLd * 4 : 0;
   return main_b > seg_b ? main_b : seg_b;
 }
@@ -268,25 +226,23 @@ constexpr size_t pk_xv_lds() {
 // Kernel 1: tile of 128 rows x 128 columns, four waves of 32 rows each.  X blocks go straight from
 // memory to the wave's registers (no other wave reads them), the tile's V blocks through kPkBufs LDS
 // buffers shared by the four; the next stage's loads are in flight during the stage's MFMAs.
-// What bounds it: in FP32 the MFMA rate (70% of what a large product reaches; the rest is the fill of
-// the pipeline and the epilogue, whose vector instructions issue one per MFMA beside another wave's
-// FP32 MFMA); with bf16 planes the tile's way from L2 and LDS to the matrix cores (1.2 of 2.1 PFLOP/s
-// at three planes) and G's way to memory.  The products as wholes, before (row-tiled tiles, or
-// transposed operands staged through LDS) and now: d = 256, c = 100, s = 32, N = 200,100 bf16x3 5.57
-// -> 2.53 ms; d = 384, c = 1000, s = 16, N = 1,282,000 FP32 entry 296 -> 160 ms; d = 203, c = 37, s =
-// 7, N = 30,048 FP32 entry 197 -> 100 us; the gradient at d = 256, c = 100, s = 32 FP32 11.0 -> 6.2 ms.
+// What bounds it: in FP32 the MFMA rate (the rest is the fill of the pipeline and the epilogue, whose
+// vector instructions issue one per MFMA beside another wave's FP32 MFMA); with bf16 planes the
+// tile's way from L2 and LDS to the matrix cores and G's way to memory.  The products as wholes,
+// before (row-tiled tiles, or transposed operands staged through LDS) and now: d = 256, c = 100, s =
+// 32, N = 200,100 bf16x3 5.57 -> 2.53 ms; s = 16 FP32 4.88 -> 3.68 ms; d = 203, c = 37, s = 7, N =
+// 30,048 FP32 205 -> 159 us; the gradient at d = 256, c = 100, s = 32 FP32 11.0 -> 6.2 ms.
 // kPkDot: dpart[ct][row] = sum over the tile's columns of G_u (G - alpha) h, G and alpha those of
 // the earlier kPkFlat call on W.
 template <int AR, int MODE>
-__global__ __launch_bounds__(256, AR == kPkX3 ? 2 : 3) void k_pk_xv(
+__global__ __launch_bounds__(256, 3) void k_pk_xv(
     const float* __restrict__ Xp, int nkb, int64_t R, const float* __restrict__ Vp, PkCols cols,
     const float* __restrict__ HT, int64_t ldh, const double* __restrict__ omega,
     float* __restrict__ G, int64_t nrb, double* __restrict__ apart, int64_t ldb,
     const float* __restrict__ alpha, double* __restrict__ dpart, Skip skip) {
   if (skip_now(skip)) return;
   extern __shared__ __align__(16) unsigned char pk_lds[];
-  float* Bs = reinterpret_cast<float*>(pk_lds);   // [3][8][parts][1 KB]
-  constexpr int P = pk_parts<AR>(), kBuf = pk_buf<AR>();
+  float* Bs = reinterpret_cast<float*>(pk_lds);   // [3][8][2][1 KB]
   constexpr int order = pk_order<AR, MODE == kPkWin>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -310,8 +266,8 @@ __global__ __launch_bounds__(256, AR == kPkX3 ? 2 : 3) void k_pk_xv(
 
   // uniform bases: the lane's share of an address is a constant 32-bit offset
   const float* xw = Xp + (row0 >> 4) * nkb * 512;
-  const float* vt = Vp + (int64_t)ct * nkb * kBuf;
-  f4 bn[2 * P], bu[2][2][P];
+  const float* vt = Vp + (int64_t)ct * nkb * kPkBuf;
+  f4 bn[4], bu[2][2][2];
   auto load_a = [&](f4 (&r)[2][2], int kb) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -321,31 +277,31 @@ __global__ __launch_bounds__(256, AR == kPkX3 ? 2 : 3) void k_pk_xv(
   };
   auto load_b = [&](int kb) {
 #pragma unroll
-    for (int t = 0; t < 2 * P; ++t)
-      bn[t] = reinterpret_cast<const f4*>(vt + (int64_t)kb * kBuf + t * 1024)[tid];
+    for (int t = 0; t < 4; ++t)
+      bn[t] = reinterpret_cast<const f4*>(vt + (int64_t)kb * kPkBuf + t * 1024)[tid];
   };
   auto store_b = [&](int buf) {
 #pragma unroll
-    for (int t = 0; t < 2 * P; ++t)
-      *reinterpret_cast<f4*>(Bs + buf * kBuf + t * 1024 + tid * 4) = bn[t];
+    for (int t = 0; t < 4; ++t)
+      *reinterpret_cast<f4*>(Bs + buf * kPkBuf + t * 1024 + tid * 4) = bn[t];
   };
   const int last = nkb - 1;
   // past the last stage the loads repeat it into buffers whose values are not used
   int rd = 0, nx = 1, wr = 2;
   // one stage with the operand a; the next stage's raw operand is loaded into r
-  auto stage = [&](const f4 (&a)[2][P], f4 (&r)[2][2], int kb) {
-    const float* b = Bs + rd * kBuf;
+  auto stage = [&](const f4 (&a)[2][2], f4 (&r)[2][2], int kb) {
+    const float* b = Bs + rd * kPkBuf;
     load_a(r, kb < last ? kb + 1 : last);
     load_b(kb + 2 <= last ? kb + 2 : last);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (u == 3) store_b(wr);
       if (u < 3)
-        pk_read<AR, 2>(bu[(u + 1) & 1], b, 2 * u + 2, lane);
+        pk_read(bu[(u + 1) & 1], b, 2 * u + 2, lane);
       else
-        pk_read<AR, 2>(bu[0], Bs + nx * kBuf, 0, lane);
+        pk_read(bu[0], Bs + nx * kPkBuf, 0, lane);
       pk_order_fence();
-      pk_unit<AR, 2, 2>(a, bu[u & 1], 2 * u, acc);
+      pk_unit<AR, 2>(a, bu[u & 1], 2 * u, acc);
       pk_order_fence();
     }
     const int t = rd;
@@ -354,30 +310,20 @@ __global__ __launch_bounds__(256, AR == kPkX3 ? 2 : 3) void k_pk_xv(
     wr = t;
     __syncthreads();
   };
-  f4 r0[2][2];
+  f4 r0[2][2], r1[2][2];   // the operands as loaded, two sets in turn
   load_a(r0, 0);
   load_b(0);
   store_b(0);
   load_b(last > 0 ? 1 : 0);
   store_b(1);
   __syncthreads();
-  pk_read<AR, 2>(bu[0], Bs, 0, lane);
-  if constexpr (AR == kPkX3) {
-    f4 a[2][P];
-    for (int kb = 0; kb < nkb; ++kb) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) pk_operand<AR>(r0[i], a[i]);
-      stage(a, r0, kb);
-    }
-  } else {
-    f4 r1[2][2];   // the raw operands are the operands: two sets in turn
-    int kb = 0;
-    for (; kb + 1 < nkb; kb += 2) {
-      stage(r0, r1, kb);
-      stage(r1, r0, kb + 1);
-    }
-    if (kb < nkb) stage(r0, r1, kb);
+  pk_read(bu[0], Bs, 0, lane);
+  int kb = 0;
+  for (; kb + 1 < nkb; kb += 2) {
+    stage(r0, r1, kb);
+    stage(r1, r0, kb + 1);
   }
+  if (kb < nkb) stage(r0, r1, kb);
 
   // Epilogue.  Lane (g, li) of block (i, j) holds positions row0 + 16 i + 4 g + v, v = 0..3, of
   // column n0 + 16 j + li of the tile.  Columns beyond the tile's width have zero G.  Positions beyond the call's rows hold other rows' values or zero: the second kernel
@@ -619,8 +565,8 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     Skip skip) {
   if (skip_now(skip)) return;
   extern __shared__ __align__(16) unsigned char pk_lds[];
-  float* Bs = reinterpret_cast<float*>(pk_lds);   // [3][8][parts][1 KB]
-  constexpr int P = pk_parts<AR>(), kBuf = pk_buf<AR>(), order = pk_order<AR, WIN>();
+  float* Bs = reinterpret_cast<float*>(pk_lds);   // [3][8][2][1 KB]
+  constexpr int order = pk_order<AR, WIN>();
   const int tid = threadIdx.x, lane = tid & 63, NW = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, g = lane >> 4;
@@ -697,11 +643,11 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
         for (int q = 0; q < 2; ++q)
           y[q] = pk_keep<false>(y[q], lim, [&](int v) { return pk_row(order, 16 * q + 4 * g + v); });
       }
-      f4 o[P];
+      f4 o[2];
       pk_parts_of<AR>(y, o);
 #pragma unroll
-      for (int p = 0; p < P; ++p)
-        *reinterpret_cast<f4*>(Bs + buf * kBuf + ((wave + NW * t) * P + p) * 256 + lane * 4) = o[p];
+      for (int p = 0; p < 2; ++p)
+        *reinterpret_cast<f4*>(Bs + buf * kPkBuf + ((wave + NW * t) * 2 + p) * 256 + lane * 4) = o[p];
     }
   };
   auto mask_a = [&](f4 (&r)[MI][2], int64_t kb) {
@@ -715,9 +661,7 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
           return pk_row(order, AR == kPkB2 ? 16 * (u >> 2) + 4 * g + (u & 3) : 16 * h + 4 * g + u);
         });
   };
-  constexpr int UJ = AR == kPkX3 && MI == 3 ? 1 : 2;   // column blocks of a unit, by registers
-  constexpr int NU = 8 / UJ;
-  f4 bu[2][UJ][P], r0[MI][2];
+  f4 bu[2][2][2], r0[MI][2], r1[MI][2];   // the row operands as loaded, two sets in turn
   const int64_t kb0 = rb >> 5, kb1 = re > rb ? (re + 31) >> 5 : kb0, last = kb1 - 1;
   auto at = [&](int64_t kb) { return kb < last ? kb : last; };   // past the last stage: it again
   if (kb1 > kb0) {
@@ -729,21 +673,21 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     load_a(r0, kb0);
   }
   __syncthreads();
-  pk_read<AR, UJ>(bu[0], Bs, 0, lane);
+  pk_read(bu[0], Bs, 0, lane);
   const bool live = ab0 < nab;   // uniform
   int rd = 0, nx = 1, wr = 2;
   // one stage with the operand a; the next stage's raw operand is loaded into r
-  auto stage = [&](const f4 (&a)[MI][P], f4 (&r)[MI][2], int64_t kb) {
-    const float* b = Bs + rd * kBuf;
+  auto stage = [&](const f4 (&a)[MI][2], f4 (&r)[MI][2], int64_t kb) {
+    const float* b = Bs + rd * kPkBuf;
     load_a(r, at(kb + 1));
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      if (u < NU - 1)
-        pk_read<AR, UJ>(bu[(u + 1) & 1], b, UJ * (u + 1), lane);
+    for (int u = 0; u < 4; ++u) {
+      if (u < 3)
+        pk_read(bu[(u + 1) & 1], b, 2 * u + 2, lane);
       else
-        pk_read<AR, UJ>(bu[0], Bs + nx * kBuf, 0, lane);
+        pk_read(bu[0], Bs + nx * kPkBuf, 0, lane);
       pk_order_fence();
-      if (live) pk_unit<AR, MI, UJ>(a, bu[u & 1], UJ * u, acc);
+      if (live) pk_unit<AR, MI>(a, bu[u & 1], 2 * u, acc);
       pk_order_fence();
       if (u == 0) {   // G' two stages ahead; its next values are loaded as soon as it is stored
         store_g(at(kb + 2), wr);
@@ -756,26 +700,15 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     wr = t;
     __syncthreads();
   };
-  if constexpr (AR == kPkX3) {
-    f4 a[MI][P];
-    for (int64_t kb = kb0; kb < kb1; ++kb) {
-      mask_a(r0, kb);
-#pragma unroll
-      for (int i = 0; i < MI; ++i) pk_operand<AR>(r0[i], a[i]);
-      stage(a, r0, kb);
-    }
-  } else {
-    f4 r1[MI][2];   // the raw operands are the operands: two sets in turn
-    int64_t kb = kb0;
-    for (; kb + 1 < kb1; kb += 2) {
-      stage(r0, r1, kb);
-      mask_a(r1, kb + 1);
-      stage(r1, r0, kb + 1);
-    }
-    if (kb < kb1) {
-      mask_a(r0, kb);
-      stage(r0, r1, kb);
-    }
+  int64_t kb = kb0;
+  for (; kb + 1 < kb1; kb += 2) {
+    stage(r0, r1, kb);
+    mask_a(r1, kb + 1);
+    stage(r1, r0, kb + 1);
+  }
+  if (kb < kb1) {
+    mask_a(r0, kb);
+    stage(r0, r1, kb);
   }
 
   // the split's partial output: lane (g, li) of block (i, j) holds rows a = 16 (ab0 + i) + 4 g + v
@@ -895,8 +828,7 @@ __global__ __launch_bounds__(256) void k_pk_pack_v(const float* __restrict__ B, 
   int n0, width;
   cols.tile((int)(tk / nkb), n0, width);
   const int m = (int)(b & 7) * 16 + li, k0 = (int)(tk % nkb) * 32;
-  constexpr int P = pk_parts<AR>();
-  f4 y[2], o[P];
+  f4 y[2], o[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -906,8 +838,8 @@ __global__ __launch_bounds__(256) void k_pk_pack_v(const float* __restrict__ B, 
     }
   pk_parts_of<AR>(y, o);
 #pragma unroll
-  for (int p = 0; p < P; ++p)
-    *reinterpret_cast<f4*>(Vp + (b * P + p) * 256 + lane * 4) = o[p];
+  for (int p = 0; p < 2; ++p)
+    *reinterpret_cast<f4*>(Vp + (b * 2 + p) * 256 + lane * 4) = o[p];
 }
 
 // g_r = -(1/s) sum over column tiles (in order) of the tile's row dot product.
@@ -970,9 +902,9 @@ int pk_xv_launch(const PkChunk& k, bool prof, const float* Vp) {
   if (prof) FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT, &e0, &e1));
   const unsigned nwg = (unsigned)(k.Rp / kPkT * k.cols.tiles());
   static DeviceOnce attr;
-  FIRAL_CHECK(pk_set_lds((const void*)k_pk_xv<AR, MODE>, pk_xv_lds<AR, MODE>(), attr));
+  FIRAL_CHECK(pk_set_lds((const void*)k_pk_xv<AR, MODE>, pk_xv_lds<MODE>(), attr));
   hipExtLaunchKernelGGL((k_pk_xv<AR, MODE>), dim3(nwg), dim3(256),
-                        (uint32_t)pk_xv_lds<AR, MODE>(), k.st, e0, e1, 0u,
+                        (uint32_t)pk_xv_lds<MODE>(), k.st, e0, e1, 0u,
                         (const float*)x->Xpk + k.ch * (k.q.cp / 16) * k.q.nkb * 512, k.q.nkb, k.R,
                         Vp, k.cols, (const float*)x->HTf + k.ch * k.q.cp, x->ldn,
                         k.omega, (float*)x->G, k.Rp / 16, x->pk_apart, k.Rp,
@@ -993,7 +925,7 @@ template <int AR, int MI, int TASKS, bool WIN>
 int pk_xtg_launch(const PkChunk& k, int nw, int nmt, int S) {
   Ctx* x = k.x;
   const int64_t rps = cdiv(cdiv(k.R, S), 32) * 32;   // splits start on whole stages
-  constexpr size_t lds = kPkBufs * pk_buf<AR>() * 4;
+  constexpr size_t lds = kPkBufs * kPkBuf * 4;
   static DeviceOnce attr;
   FIRAL_CHECK(pk_set_lds((const void*)k_pk_xtg<AR, MI, TASKS, WIN>, lds, attr));
   hipEvent_t e0, e1;
@@ -1020,25 +952,21 @@ int pk_pack_v(const Ctx* x, const PkGeom& q, const PkCols& cols, const float* B,
   return FIRAL_OK;
 }
 
-// Row splits of the second contraction.  kPkF32 and kPkB2 keep the splits that fix the solves'
-// rounding: flat, enough for several rounds of 128 x 128 output tiles; windows, the count with the
-// least time in rounds over the device's slots.  kPkX3: the latter over its own workgroups.
-int pk_splits(const Ctx* x, const PkGeom& q, int ar, int s, int tiles2, int nw2, int64_t n_rows) {
-  const int64_t cap = (int64_t)x->max_splits * x->s_max / s;
-  if (ar != kPkX3 && !q.win) {
-    const int64_t tiles = cdiv(x->d, kPkT) * cdiv((int64_t)s * x->c, kPkT);
+// Row splits of the second contraction, which fix the rounding: flat, enough for several rounds of
+// 128 x 128 output tiles; windows, the count with the least time in rounds over the device's slots of
+// the workgroups that the row-tiled form of that shape has.
+int pk_splits(const Ctx* x, const PkGeom& q, int s) {
+  const int64_t cap = (int64_t)x->max_splits * x->s_max / s, nmt = cdiv(x->d, kPkT);
+  if (!q.win) {
+    const int64_t tiles = nmt * cdiv((int64_t)s * x->c, kPkT);
     return (int)std::max<int64_t>(1, std::min<int64_t>({cdiv(4096, tiles), cap, 256}));
   }
-  int64_t tiles = tiles2, slots = (nw2 > 4 ? 1 : 2) * (int64_t)std::max(1, x->n_cu);
-  int64_t rows = std::min(x->chunk_rows, n_rows);
-  if (ar != kPkX3) {
-    const int nmt = (int)cdiv(x->d, kPkT), nct = s * (int)cdiv(x->c, kPkT);
-    const bool one = nmt == 2 || nmt == 3;
-    tiles = one ? nct : (int64_t)nmt * nct;
-    slots = (int64_t)(one ? 1 : 2) * std::max(1, x->n_cu);
-    rows = x->chunk_rows;
-  }
-  const int64_t hi = std::max<int64_t>(1, std::min<int64_t>({cap, 256, cdiv(rows, 256)}));
+  const int64_t nct = s * cdiv(x->c, kPkT);
+  const bool one = nmt == 2 || nmt == 3;
+  const int64_t tiles = one ? nct : nmt * nct;
+  const int64_t slots = (int64_t)(one ? 1 : 2) * std::max(1, x->n_cu);
+  const int64_t hi =
+      std::max<int64_t>(1, std::min<int64_t>({cap, 256, cdiv(x->chunk_rows, 256)}));
   int S = 1;
   for (int64_t t = 2; t <= hi; ++t)   // rounds / S, compared as cross products
     if (cdiv(tiles * t, slots) * S < cdiv(tiles * S, slots) * t) S = (int)t;
@@ -1057,7 +985,7 @@ int hvp_pk_t(Ctx* x, const PkGeom& q, const double* omega, int64_t n_rows, doubl
   const int MI = q.nab > 2 * kPkMaxWaves ? 3 : 2;
   const int nw = q.nab <= 8 ? 4 : kPkMaxWaves;
   const int nmt = (int)cdiv(q.nab, MI * nw);
-  const int S = pk_splits(x, q, AR, s, nmt * cols.tiles(), nw, n_rows);
+  const int S = pk_splits(x, q, s);
   for (int64_t ch = 0; ch * x->chunk_rows < n_rows; ++ch) {
     const int64_t r0 = ch * x->chunk_rows, R = std::min<int64_t>(x->chunk_rows, n_rows - r0);
     const PkChunk k{x, q, cols, ch, R, cdiv(R, kPkT) * kPkT, omega ? omega + r0 : nullptr, skip,
@@ -1086,7 +1014,7 @@ int grad_pk_t(Ctx* x, const PkGeom& q, const float* U, const float* W, int s, do
   const int c = x->c;
   const PkCols cols = pk_cols(x, s, false);
   float* Wp = (float*)x->Vpk;
-  float* Up = Wp + (int64_t)pk_cols(x, x->s_max, false).tiles() * q.nkb * 8 * pk_parts<AR>() * 256;
+  float* Up = Wp + (int64_t)pk_cols(x, x->s_max, false).tiles() * q.nkb * 8 * 512;
   FIRAL_CHECK(pk_pack_v<AR>(x, q, cols, W, Wp, skip_none(), st));
   FIRAL_CHECK(pk_pack_v<AR>(x, q, cols, U, Up, skip_none(), st));
   for (int64_t ch = 0; ch * x->chunk_rows < x->n_pool; ++ch) {
@@ -1136,7 +1064,7 @@ PkSizes pk_sizes(const Ctx* x) {
   z.x = (size_t)(Np / 16) * q.nkb * 2048;
   z.xt = (size_t)(Np / 32) * q.nab * 2048;
   z.ht = (size_t)Np * x->c * 4;
-  // two blocks of V in two parts (the gradient's W and U), or one in three
+  // two blocks of V (the gradient's W and U)
   z.v = (size_t)2 * nct * q.nkb * 8 * 2048;
   z.g = (size_t)nct * kPkT * q.cp * 4;
   z.apart = (size_t)(nct + x->s_max) * q.cp * 8;
@@ -1152,13 +1080,12 @@ int pk_prepare_ctx(Ctx* x, hipStream_t st) {
 }
 
 int hvp_pk_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const float* B,
-                  float* out, int s, bool entry, Skip skip, hipStream_t st) {
+                  float* out, int s, Skip skip, hipStream_t st) {
   const PkGeom q = pk_geom(x);
 #define FIRAL_PK_HVP(AR)                                                              \
   return q.win ? hvp_pk_t<AR, true>(x, q, omega, n_rows, shift, B, out, s, skip, st) \
                : hvp_pk_t<AR, false>(x, q, omega, n_rows, shift, B, out, s, skip, st)
   if (q.b2) FIRAL_PK_HVP(kPkB2);
-  if (entry) FIRAL_PK_HVP(kPkX3);
   FIRAL_PK_HVP(kPkF32);
 #undef FIRAL_PK_HVP
 }

@@ -67,7 +67,7 @@ template int reduce_parts_launch<double>(const double*, int64_t, int, double, co
                                          double*, Skip, hipStream_t);
 
 int hvp_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const void* B,
-               void* out, int s, Skip skip, hipStream_t st, bool precise, bool entry) {
+               void* out, int s, Skip skip, hipStream_t st, bool precise) {
   FusedPlan plan;
   if (x->prec != FIRAL_F64 && !x->force_tiled && fused_plan(x, s, n_rows, &plan, precise) &&
       plan.part_elems <= x->fused_part_elems)
@@ -81,8 +81,7 @@ int hvp_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const 
   }
   // a bf16x3 context's packed operands are bf16 planes: its FP32 products (precise) are row-tiled
   if (x->use_pk && !(x->prec == FIRAL_BF16X3 && precise))
-    return hvp_pk_launch(x, omega, n_rows, shift, (const float*)B, (float*)out, s, entry, skip,
-                         st);
+    return hvp_pk_launch(x, omega, n_rows, shift, (const float*)B, (float*)out, s, skip, st);
   return hvp_tiled_launch(x, omega, n_rows, shift, B, out, s, skip, st, precise);
 }
 
