@@ -921,8 +921,41 @@ int pk_alpha_launch(const PkChunk& k) {
   return FIRAL_OK;
 }
 
+// Output row tile of a second-contraction workgroup: nw waves of mi 16-row blocks, nmt tiles.  Three
+// forms: 8 waves of three or of two blocks, one workgroup a CU, and 4 waves of two, two a CU; the split
+// sums are the same in all.  The form with the least time by this model, in 1/20 of a block's stage on
+// one SIMD: rounds of workgroups over the device, each the stages of a split at 120, 80 or 76 (windows
+// and bf16x3 100; half of it for 4 waves that have their CU alone) and a start of 200 or 220 (bf16x3
+// 40, 60).
+// Fitted to 440 shapes (d = 100 .. 768, SC = 35 .. 2100, 3,000 and 30,000 rows; 0.2% above the best of
+// the three in the mean).  FP32 products, three blocks from d = 257 and two below -> this: d = 257, SC
+// = 35, N = 30,000 151 -> 78 us; d = 256, SC = 1600 611 -> 569 us; d = 512, SC = 2100 1898 -> 1612 us.
+struct PkTile {
+  int mi, nw, nmt;
+};
+PkTile pk_tile(const Ctx* x, const PkGeom& q, int nct, int S, int64_t rows) {
+  const int64_t stages = cdiv(cdiv(rows, S), 32), splits = cdiv(rows, 32 * stages);
+  const int64_t n_cu = std::max(1, x->n_cu);
+  PkTile best = {};
+  int64_t least = 0;
+  for (int form = 0; form < 3; ++form) {
+    PkTile t = {form == 0 ? 3 : 2, form == 2 ? kPkMaxWaves / 2 : kPkMaxWaves, 0};
+    t.nmt = (int)cdiv(q.nab, t.mi * t.nw);
+    const int64_t wgs = (int64_t)t.nmt * nct * splits;
+    const bool alone = form < 2 || wgs <= n_cu;
+    const int64_t unit = form < 2 ? 40 * t.mi : (q.b2 || q.win ? 100 : 76) / (alone ? 2 : 1);
+    const int64_t time = cdiv(wgs, form < 2 ? n_cu : 2 * n_cu) *
+                         (stages * unit + (q.b2 ? 40 : 200) + (form < 2 ? 0 : 20));
+    if (form == 0 || time < least) {
+      best = t;
+      least = time;
+    }
+  }
+  return best;
+}
+
 template <int AR, int MI, int TASKS, bool WIN>
-int pk_xtg_launch(const PkChunk& k, int nw, int nmt, int S) {
+int pk_xtg_launch(const PkChunk& k, const PkTile& t, int S) {
   Ctx* x = k.x;
   const int64_t rps = cdiv(cdiv(k.R, S), 32) * 32;   // splits start on whole stages
   constexpr size_t lds = kPkBufs * kPkBuf * 4;
@@ -931,12 +964,12 @@ int pk_xtg_launch(const PkChunk& k, int nw, int nmt, int S) {
   hipEvent_t e0, e1;
   FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT_T, &e0, &e1));
   hipExtLaunchKernelGGL((k_pk_xtg<AR, MI, TASKS, WIN>),
-                        dim3((unsigned)((int64_t)nmt * k.cols.tiles() * S)), dim3(64 * nw),
+                        dim3((unsigned)((int64_t)t.nmt * k.cols.tiles() * S)), dim3(64 * t.nw),
                         (uint32_t)lds, k.st, e0, e1, 0u,
                         (const float*)x->XTpk + k.ch * (k.q.cp / 32) * k.q.nab * 512, k.q.nab,
                         x->d, (const float*)x->G, k.Rp / 16, k.cols,
                         (const float*)x->HTf + k.ch * k.q.cp, x->ldn, (const float*)x->pk_alpha,
-                        (const float*)x->pk_om, k.Rp, k.R, rps, nmt, (float*)x->part,
+                        (const float*)x->pk_om, k.Rp, k.R, rps, t.nmt, (float*)x->part,
                         (int64_t)x->d * k.cols.SC, (int)(k.ch > 0), k.skip);
   FIRAL_LAUNCHED();
   return FIRAL_OK;
@@ -980,12 +1013,9 @@ int hvp_pk_t(Ctx* x, const PkGeom& q, const double* omega, int64_t n_rows, doubl
   const PkCols cols = pk_cols(x, s, WIN);
   float* Vp = (float*)x->Vpk;
   if (n_rows > 0) FIRAL_CHECK(pk_pack_v<AR>(x, q, cols, B, Vp, skip, st));
-  // output row tiles: 8 waves of MI 16-row blocks (one G' task per wave and stage), or 4 of two
-  // blocks and tasks up to d = 128; waves beyond the last block only form G'
-  const int MI = q.nab > 2 * kPkMaxWaves ? 3 : 2;
-  const int nw = q.nab <= 8 ? 4 : kPkMaxWaves;
-  const int nmt = (int)cdiv(q.nab, MI * nw);
   const int S = pk_splits(x, q, s);
+  const PkTile t =
+      pk_tile(x, q, cols.tiles(), S, std::max<int64_t>(1, std::min(x->chunk_rows, n_rows)));
   for (int64_t ch = 0; ch * x->chunk_rows < n_rows; ++ch) {
     const int64_t r0 = ch * x->chunk_rows, R = std::min<int64_t>(x->chunk_rows, n_rows - r0);
     const PkChunk k{x, q, cols, ch, R, cdiv(R, kPkT) * kPkT, omega ? omega + r0 : nullptr, skip,
@@ -997,12 +1027,12 @@ int hvp_pk_t(Ctx* x, const PkGeom& q, const double* omega, int64_t n_rows, doubl
     else
       FIRAL_CHECK((pk_xv_launch<AR, kPkFlatX>(k, true, Vp)));
     FIRAL_CHECK(pk_alpha_launch(k));
-    if (nw == 4)
-      FIRAL_CHECK((pk_xtg_launch<AR, 2, 2, WIN>(k, nw, nmt, S)));
-    else if (MI == 2)
-      FIRAL_CHECK((pk_xtg_launch<AR, 2, 1, WIN>(k, nw, nmt, S)));
+    if (t.nw < kPkMaxWaves)
+      FIRAL_CHECK((pk_xtg_launch<AR, 2, 2, WIN>(k, t, S)));
+    else if (t.mi == 2)
+      FIRAL_CHECK((pk_xtg_launch<AR, 2, 1, WIN>(k, t, S)));
     else
-      FIRAL_CHECK((pk_xtg_launch<AR, 3, 1, WIN>(k, nw, nmt, S)));
+      FIRAL_CHECK((pk_xtg_launch<AR, 3, 1, WIN>(k, t, S)));
   }
   return reduce_parts_launch<float>((const float*)x->part, (int64_t)d * SC, n_rows > 0 ? S : 0,
                                     shift, B, out, skip, st);
