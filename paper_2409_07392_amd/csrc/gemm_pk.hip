@@ -257,6 +257,9 @@ __global__ __launch_bounds__(256, 3) void k_pk_xv(
   const int ct = (int)(gsz == 8 ? in >> 3 : in / gsz);
   const int64_t rt = grp * 8 + (in - (unsigned)ct * gsz);
   const int64_t row0 = rt * kPkT + 32 * wave;
+  int n0, width;
+  cols.tile(ct, n0, width);
+  const int units = (width + 31) >> 5;   // uniform; the others' products are zero
 
   f32x4 acc[2][8];
 #pragma unroll
@@ -301,7 +304,7 @@ __global__ __launch_bounds__(256, 3) void k_pk_xv(
       else
         pk_read(bu[0], Bs + nx * kPkBuf, 0, lane);
       pk_order_fence();
-      pk_unit<AR, 2>(a, bu[u & 1], 2 * u, acc);
+      if (u < units) pk_unit<AR, 2>(a, bu[u & 1], 2 * u, acc);
       pk_order_fence();
     }
     const int t = rd;
@@ -329,8 +332,6 @@ __global__ __launch_bounds__(256, 3) void k_pk_xv(
   // column n0 + 16 j + li of the tile.  Columns beyond the tile's width have zero G.  Positions beyond the call's rows hold other rows' values or zero: the second kernel
   // clears them.  Every load is issued before the first is used.  VALU work here competes with the
   // other workgroup's MFMAs for issue, so the sums use as few operations as their order allows.
-  int n0, width;
-  cols.tile(ct, n0, width);
   float* gt = G + ((int64_t)ct * nrb + (row0 >> 4)) * 2048;   // uniform
   // probe and class of the tile's first column, and the last probe
   const int p_lo = (int)((unsigned)n0 / (unsigned)c), k_lo = n0 - p_lo * c;
@@ -674,7 +675,8 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
   }
   __syncthreads();
   pk_read(bu[0], Bs, 0, lane);
-  const bool live = ab0 < nab;   // uniform
+  // units with a column of the tile, and none of a wave without an output block (uniform)
+  const int units = ab0 < nab ? (width + 31) >> 5 : 0;
   int rd = 0, nx = 1, wr = 2;
   // one stage with the operand a; the next stage's raw operand is loaded into r
   auto stage = [&](const f4 (&a)[MI][2], f4 (&r)[MI][2], int64_t kb) {
@@ -687,7 +689,7 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
       else
         pk_read(bu[0], Bs + nx * kPkBuf, 0, lane);
       pk_order_fence();
-      if (live) pk_unit<AR, MI>(a, bu[u & 1], 2 * u, acc);
+      if (u < units) pk_unit<AR, MI>(a, bu[u & 1], 2 * u, acc);
       pk_order_fence();
       if (u == 0) {   // G' two stages ahead; its next values are loaded as soon as it is stored
         store_g(at(kb + 2), wr);
