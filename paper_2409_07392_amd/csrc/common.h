@@ -410,6 +410,7 @@ struct PkSizes {
 };
 PkSizes pk_sizes(const Ctx* x);
 int pk_prepare_ctx(Ctx* x, hipStream_t st);
+bool hvp_pk_applies(const Ctx* x, int64_t n_rows, bool precise);
 int hvp_pk_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const float* B,
                   float* out, int s, Skip skip, hipStream_t st);
 bool grad_pk_applies(const Ctx* x);

@@ -1111,6 +1111,17 @@ int pk_prepare_ctx(Ctx* x, hipStream_t st) {
   return q.b2 ? pk_pack_ctx<true>(x, q, st) : pk_pack_ctx<false>(x, q, st);
 }
 
+// A bf16x3 context's packed operands are bf16 planes: its FP32 products (precise) are row-tiled.  So are
+// those of FP32 contexts with d <= 128 (and wide probes) up to 2048 rows, where the two launches more
+// of the packed form show: d = 98, c = 500, s = 7, N = 408 97 us, row-tiled 80; d = 91, c = 300, N = 1182
+// 72, 63; at 2,500 rows and more the packed form is the faster one (d = 89, c = 160, s = 8, N = 2600 59,
+// row-tiled 64).
+bool hvp_pk_applies(const Ctx* x, int64_t n_rows, bool precise) {
+  if (!x->use_pk) return false;
+  if (x->prec == FIRAL_BF16X3) return !precise;
+  return x->d > 128 || n_rows > 2048;
+}
+
 int hvp_pk_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const float* B,
                   float* out, int s, Skip skip, hipStream_t st) {
   const PkGeom q = pk_geom(x);

@@ -79,8 +79,7 @@ int hvp_launch(Ctx* x, const double* omega, int64_t n_rows, double shift, const 
                                    st, &taken));
     if (taken) return FIRAL_OK;
   }
-  // a bf16x3 context's packed operands are bf16 planes: its FP32 products (precise) are row-tiled
-  if (x->use_pk && !(x->prec == FIRAL_BF16X3 && precise))
+  if (hvp_pk_applies(x, n_rows, precise))
     return hvp_pk_launch(x, omega, n_rows, shift, (const float*)B, (float*)out, s, skip, st);
   return hvp_tiled_launch(x, omega, n_rows, shift, B, out, s, skip, st, precise);
 }
