@@ -1,6 +1,7 @@
 """Products on both sides of the lines between their kernels, against the FP64 oracle: the packed and
-the row-tiled FP32 form for wide probes at d <= 128 (2048 rows).  Normwise; FP32 1e-5, the bar of the
-fused and packed kernels' other tests.
+the row-tiled FP32 form for wide probes at d <= 128 (2048 rows), and the one-pass and the row-tiled
+FP64 form for c > 64 (rows times probes of 100,000).  Normwise; FP32 1e-5 and FP64 1e-12, the bars of
+the same kernels' other tests.
 """
 import numpy as np
 import pytest
@@ -32,3 +33,9 @@ def check(n, d, c, s, rows, prec, bar):
 @pytest.mark.parametrize("d,c,s", [(40, 300, 2), (128, 129, 3), (7, 513, 1)])
 def test_wide_probes_at_the_row_line(d, c, s):
     check(2200, d, c, s, (1, 2047, 2048, 2049, 2203), "f32", 1e-5)
+
+
+@pytest.mark.parametrize("d,c,s", [(22, 128, 25), (30, 65, 20), (9, 64, 30)])
+def test_fp64_probes_beyond_half_a_tile_at_the_row_line(d, c, s):
+    k = 100000 // s
+    check(k + 50, d, c, s, (k - 1, k, k + 1, k + 53), "f64", 1e-12)
