@@ -385,7 +385,7 @@ __global__ __launch_bounds__(256, 2) void k_syrkw(const float* __restrict__ X,
 // fitted to c (100 classes: 7 blocks, not 8) and the equal runs below (16.3 and 19.9 ms without).
 // The order of the rows of an accumulator's sum is that of the kernels which read X and H as they
 // are: instruction q of a 16-row block takes rows 4 g + q (kGramWide) or 4 q + g.
-constexpr int kGramMaxWgs = 4092, kGramMinStages = 16, kGramCutStages = 64;
+constexpr int kGramMaxWgs = 4092, kGramMinStages = 16, kGramCutStages = 16;
 constexpr int64_t kGramFlagBytes = 16384;   // a flag a workgroup, the counter
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_gram_pack(const float* __restrict__ X,
@@ -439,9 +439,12 @@ __global__ __launch_bounds__(256) void k_gram_pack(const float* __restrict__ X,
 // head of its last unit first and the tail of its first unit last, for which the workgroup before
 // it has then had as much time as the head takes.  Runs are dealt by a counter in the order in which
 // workgroups start, so the workgroup waited for is running, whatever else the device runs and in
-// whatever order its dies take workgroups, and its head waits for nothing: the wait ends.  Units of under 64 stages are not cut: what a run
-// exchanges then costs more than the uneven last round (c = 1000, d = 400, N = 500, 16 stages: 4.07
-// ms, cut 4.43).
+// whatever order its dies take workgroups, and its head waits for nothing: the wait ends.
+// Ranges of under 16 stages (the rest that the scratch left over) are not cut.  From there on the
+// preconditioner with and without cuts: c = 200, d = 383 2.41 -> 2.38 ms at 16 stages, 2.85 -> 2.64 at
+// 47, 7.5 -> 5.3 at 375; c = 100, d = 256 1.15 -> 1.07 ms at 20 stages, 1.39 -> 1.23 at 32; with many
+// units a workgroup they cost what they gain (c = 300, d = 400: 5.24 -> 5.27 ms at 17 stages, 7.28 ->
+// 7.18 at 157).
 // workgroups that a CU's registers hold
 constexpr int gram_wgs_per_cu(int cmw) {
   return cmw <= 1 ? 7 : cmw <= 2 ? 5 : cmw <= 3 ? 4 : cmw <= 5 ? 3 : 2;
@@ -1398,10 +1401,10 @@ static int gram_launch(Ctx* x, const double* omega, int64_t rps, hipStream_t st)
   static const K kernels[8] = {k_gram<1>, k_gram<2>, k_gram<3>, k_gram<4>,
                                k_gram<5>, k_gram<6>, k_gram<7>, k_gram<8>};
   const int units = nct * x->syrk_ntiles * S;
-  const bool cut = stages >= kGramCutStages;
-  const int wgs = !cut ? units : std::min({units, x->n_cu * gram_wgs_per_cu(cmw), kGramMaxWgs});
   for (int64_t s0 = 0; s0 < stages; s0 += T) {
     const int nkc = (int)std::min<int64_t>(T, stages - s0);
+    const int wgs = nkc < kGramCutStages
+                        ? units : std::min({units, x->n_cu * gram_wgs_per_cu(cmw), kGramMaxWgs});
     pack<<<dim3((unsigned)(S * T), (unsigned)cdiv(nct * cmw + nab, 4)), 256, 0, st>>>((const float*)x->X, (const float*)x->H, omega, x->N,
                                             x->d, x->c, rps, (int)s0, T, nct, cmw, nab, U, XP,
                                             done);
