@@ -587,7 +587,11 @@ __global__ __launch_bounds__(256, gram_wgs_per_cu(CMW)) void k_gram(
         }
       }
     if (ke < nkc) {
-      __syncthreads();   // the other waves' sums are out: thread 0 releases them with its own
+      // Every wave waits for its own stores before the barrier (which does not wait for them: a barrier
+      // orders within the workgroup), so that all the sums are in L2 when thread 0 writes L2 back and
+      // sets the flag; a release by every thread would write L2 back 256 times (235 us, so 126).
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
       if (tid == 0)
         __hip_atomic_store(done + id, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
