@@ -1411,8 +1411,8 @@ static int round_score_t(Round* r, const CT* W, double* r_out, hipStream_t st) {
       hipExtLaunchKernelGGL(cls, dim3((unsigned)(wpc * r->c)), dim3(512), (unsigned)lds, st, e0, e1,
                             0u, X, H, r0, R, r->d, r->c, W, r->eta, wpc, Tb);
     } else {
-    hipExtLaunchKernelGGL(k_round_score<T, CT>, dim3((unsigned)nwg), dim3(256), 0u, st, e0, e1,
-                          0u, X, H, r0, R, r->d, r->c, W, r->ldo, r->eta, rows_major, Tb);
+      hipExtLaunchKernelGGL(k_round_score<T, CT>, dim3((unsigned)nwg), dim3(256), 0u, st, e0, e1,
+                            0u, X, H, r0, R, r->d, r->c, W, r->ldo, r->eta, rows_major, Tb);
     }
     FIRAL_LAUNCHED();
     k_round_rsum<CT><<<(unsigned)cdiv(R, 256), 256, 0, st>>>(Tb, R, r->c, r0, r->mask, r_out,
