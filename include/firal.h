@@ -87,7 +87,11 @@ typedef struct {
 
 /* Create a context for one problem.  X and H (device, element type of prec)
  * are borrowed: they must stay valid and unchanged while the context lives.
- * All workspace for blocks of up to s_max probes is allocated here.
+ * All workspace for blocks of up to s_max probes is allocated here.  FP32 and bf16x3 contexts that the
+ * fused kernels do not cover (d > 128, or more classes than a fused tile holds) also hold X, X^T and
+ * H^T in the order of the matrix instructions, about 8 d + 4 c bytes a row.  When that does not fit in
+ * memory the context is created without (the row-tiled kernels; FIRAL_NT=0 in the environment asks for
+ * that): the same arithmetic, with sums in FP64 and, for c > 128, over classes in another order.
  * Errors: EINVAL (n_pool < 1, n_lab < 0, d < 1, c < 2, s_max < 1, null X/H/out,
  * prec unknown), EHIP (no device), ENOMEM. */
 int firal_create(firal_ctx* out, int64_t n_pool, int64_t n_lab, int32_t d, int32_t c,
