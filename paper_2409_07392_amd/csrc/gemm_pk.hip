@@ -890,21 +890,12 @@ struct PkChunk {
   hipStream_t st;
 };
 
-int pk_set_lds(const void* kernel, size_t bytes, DeviceOnce& once) {
-  if (bytes <= 64 * 1024 || once.done()) return FIRAL_OK;
-  FIRAL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  once.set();
-  return FIRAL_OK;
-}
-
 template <int AR, int MODE>
 int pk_xv_launch(const PkChunk& k, bool prof, const float* Vp) {
   Ctx* x = k.x;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (prof) FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT, &e0, &e1));
   const unsigned nwg = (unsigned)(k.Rp / kPkT * k.cols.tiles());
-  static DeviceOnce attr;
-  FIRAL_CHECK(pk_set_lds((const void*)k_pk_xv<AR, MODE>, pk_xv_lds<MODE>(), attr));
   hipExtLaunchKernelGGL((k_pk_xv<AR, MODE>), dim3(nwg), dim3(256),
                         (uint32_t)pk_xv_lds<MODE>(), k.st, e0, e1, 0u,
                         (const float*)x->Xpk + k.ch * (k.q.cp / 16) * k.q.nkb * 512, k.q.nkb, k.R,
@@ -960,9 +951,7 @@ template <int AR, int MI, int TASKS, bool WIN>
 int pk_xtg_launch(const PkChunk& k, const PkTile& t, int S) {
   Ctx* x = k.x;
   const int64_t rps = cdiv(cdiv(k.R, S), 32) * 32;   // splits start on whole stages
-  constexpr size_t lds = kPkBufs * kPkBuf * 4;
-  static DeviceOnce attr;
-  FIRAL_CHECK(pk_set_lds((const void*)k_pk_xtg<AR, MI, TASKS, WIN>, lds, attr));
+  constexpr size_t lds = kPkBufs * kPkBuf * 4;   // below the 64 KB that need no attribute, as above
   hipEvent_t e0, e1;
   FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT_T, &e0, &e1));
   hipExtLaunchKernelGGL((k_pk_xtg<AR, MI, TASKS, WIN>),
