@@ -208,6 +208,11 @@ struct PkCols {
       width = SC - n0 < kPkT ? SC - n0 : kPkT;
     }
   }
+  // whether pairs of column blocks beyond the tiles' widths are a tenth of all or more
+  __host__ bool part() const {
+    const int last = nw ? c - (nw - 1) * kPkT : SC - (tiles() - 1) * kPkT, n = nw ? nw : tiles();
+    return 10 * (4 - (last + 31) / 32) >= 4 * n;
+  }
   // partial-sum slots: flat tile ct and its probe p share slot ct + p (a step to the next column
   // either stays in both or moves on in one of them); windows p nw + w
   __host__ __device__ __forceinline__ int64_t slots() const { return (int64_t)tiles() + s; }
@@ -259,7 +264,8 @@ __global__ __launch_bounds__(256, 3) void k_pk_xv(
   const int64_t row0 = rt * kPkT + 32 * wave;
   int n0, width;
   cols.tile(ct, n0, width);
-  const int units = (width + 31) >> 5;   // uniform; the others' products are zero
+  // pairs of column blocks within the tile's width (uniform); the others' products are zero
+  const int units = (width + 31) >> 5;
 
   f32x4 acc[2][8];
 #pragma unroll
@@ -557,7 +563,10 @@ __global__ __launch_bounds__(256) void k_pk_alpha(const double* __restrict__ apa
 // once per workgroup: 16-column blocks wave, wave + NW of each 32-row stage, G and h of the next
 // stage in flight during the stage's MFMAs, through kPkBufs LDS buffers.  What bounds it: as
 // k_pk_xv; G is read from memory once.
-template <int AR, int MI, int TASKS, bool WIN>
+// PART: the pairs of column blocks beyond the tile's width are left out; a branch at every pair costs the
+// full tiles 5 to 9% (FP32, three blocks a wave: d = 383, c = 200, s = 10, N = 60,200 843 -> 915 us), so
+// that form serves where it leaves out a tenth of the pairs or more.
+template <int AR, int MI, int TASKS, bool WIN, bool PART>
 __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
     const float* __restrict__ XTp, int nab, int d, const float* __restrict__ G, int64_t nrb,
     PkCols cols, const float* __restrict__ HT, int64_t ldh,
@@ -675,8 +684,9 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
   }
   __syncthreads();
   pk_read(bu[0], Bs, 0, lane);
-  // units with a column of the tile, and none of a wave without an output block (uniform)
-  const int units = ab0 < nab ? (width + 31) >> 5 : 0;
+  // a wave without an output block only forms G'; units with a column of the tile (both uniform)
+  const bool live = ab0 < nab;
+  const int units = live ? (width + 31) >> 5 : 0;
   int rd = 0, nx = 1, wr = 2;
   // one stage with the operand a; the next stage's raw operand is loaded into r
   auto stage = [&](const f4 (&a)[MI][2], f4 (&r)[MI][2], int64_t kb) {
@@ -689,7 +699,7 @@ __global__ __launch_bounds__(64 * kPkMaxWaves, 2) void k_pk_xtg(
       else
         pk_read(bu[0], Bs + nx * kPkBuf, 0, lane);
       pk_order_fence();
-      if (u < units) pk_unit<AR, MI>(a, bu[u & 1], 2 * u, acc);
+      if (PART ? u < units : live) pk_unit<AR, MI>(a, bu[u & 1], 2 * u, acc);
       pk_order_fence();
       if (u == 0) {   // G' two stages ahead; its next values are loaded as soon as it is stored
         store_g(at(kb + 2), wr);
@@ -917,12 +927,12 @@ int pk_alpha_launch(const PkChunk& k) {
 // Output row tile of a second-contraction workgroup: nw waves of mi 16-row blocks, nmt tiles.  Three
 // forms: 8 waves of three or of two blocks, one workgroup a CU, and 4 waves of two, two a CU; the split
 // sums are the same in all.  The form with the least time by this model, in 1/20 of a block's stage on
-// one SIMD: rounds of workgroups over the device, each the stages of a split at 120, 80 or 76 (windows
-// and bf16x3 100; half of it for 4 waves that have their CU alone) and a start of 200 or 220 (bf16x3
-// 40, 60).
-// Fitted to 440 shapes (d = 100 .. 768, SC = 35 .. 2100, 3,000 and 30,000 rows; 0.2% above the best of
-// the three in the mean).  FP32 products, three blocks from d = 257 and two below -> this: d = 257, SC
-// = 35, N = 30,000 151 -> 78 us; d = 256, SC = 1600 611 -> 569 us; d = 512, SC = 2100 1898 -> 1612 us.
+// one SIMD: rounds of workgroups over the device, each the stages of a split (114, 80 and 74 a stage,
+// windows 100; bf16x3 105, 80 and 88, 100; for 4 waves that have their CU alone half of it) and a start
+// (200, for 4 waves 240).  Fitted to 440 shapes (d = 100 .. 768, SC = 35 .. 2100, 3,000 and
+// 30,000 rows; 0.3% above the best of the three in the mean).  FP32 products, three blocks from d = 257
+// and two below -> this: d = 257, SC = 35, N = 30,000 151 -> 78 us; d = 256, SC = 1600 611 -> 569 us; d =
+// 512, SC = 2100 1898 -> 1612 us.
 struct PkTile {
   int mi, nw, nmt;
 };
@@ -936,9 +946,10 @@ PkTile pk_tile(const Ctx* x, const PkGeom& q, int nct, int S, int64_t rows) {
     t.nmt = (int)cdiv(q.nab, t.mi * t.nw);
     const int64_t wgs = (int64_t)t.nmt * nct * splits;
     const bool alone = form < 2 || wgs <= n_cu;
-    const int64_t unit = form < 2 ? 40 * t.mi : (q.b2 || q.win ? 100 : 76) / (alone ? 2 : 1);
-    const int64_t time = cdiv(wgs, form < 2 ? n_cu : 2 * n_cu) *
-                         (stages * unit + (q.b2 ? 40 : 200) + (form < 2 ? 0 : 20));
+    const int64_t four = q.win ? 100 : q.b2 ? 88 : 74;
+    const int64_t unit = form == 0 ? (q.b2 ? 105 : 114) : form == 1 ? 80 : four / (alone ? 2 : 1);
+    const int64_t start = form < 2 ? 200 : 240;
+    const int64_t time = cdiv(wgs, form < 2 ? n_cu : 2 * n_cu) * (stages * unit + start);
     if (form == 0 || time < least) {
       best = t;
       least = time;
@@ -947,14 +958,14 @@ PkTile pk_tile(const Ctx* x, const PkGeom& q, int nct, int S, int64_t rows) {
   return best;
 }
 
-template <int AR, int MI, int TASKS, bool WIN>
+template <int AR, int MI, int TASKS, bool WIN, bool PART>
 int pk_xtg_launch(const PkChunk& k, const PkTile& t, int S) {
   Ctx* x = k.x;
   const int64_t rps = cdiv(cdiv(k.R, S), 32) * 32;   // splits start on whole stages
   constexpr size_t lds = kPkBufs * kPkBuf * 4;   // below the 64 KB that need no attribute, as above
   hipEvent_t e0, e1;
   FIRAL_CHECK(prof_pair(x, FIRAL_PROF_PRODUCT_T, &e0, &e1));
-  hipExtLaunchKernelGGL((k_pk_xtg<AR, MI, TASKS, WIN>),
+  hipExtLaunchKernelGGL((k_pk_xtg<AR, MI, TASKS, WIN, PART>),
                         dim3((unsigned)((int64_t)t.nmt * k.cols.tiles() * S)), dim3(64 * t.nw),
                         (uint32_t)lds, k.st, e0, e1, 0u,
                         (const float*)x->XTpk + k.ch * (k.q.cp / 32) * k.q.nab * 512, k.q.nab,
@@ -964,6 +975,13 @@ int pk_xtg_launch(const PkChunk& k, const PkTile& t, int S) {
                         (int64_t)x->d * k.cols.SC, (int)(k.ch > 0), k.skip);
   FIRAL_LAUNCHED();
   return FIRAL_OK;
+}
+
+template <int AR, bool WIN, bool PART>
+int pk_xtg_form(const PkChunk& k, const PkTile& t, int S) {
+  if (t.nw < kPkMaxWaves) return pk_xtg_launch<AR, 2, 2, WIN, PART>(k, t, S);
+  if (t.mi == 2) return pk_xtg_launch<AR, 2, 1, WIN, PART>(k, t, S);
+  return pk_xtg_launch<AR, 3, 1, WIN, PART>(k, t, S);
 }
 
 template <int AR>
@@ -1018,12 +1036,8 @@ int hvp_pk_t(Ctx* x, const PkGeom& q, const double* omega, int64_t n_rows, doubl
     else
       FIRAL_CHECK((pk_xv_launch<AR, kPkFlatX>(k, true, Vp)));
     FIRAL_CHECK(pk_alpha_launch(k));
-    if (t.nw < kPkMaxWaves)
-      FIRAL_CHECK((pk_xtg_launch<AR, 2, 2, WIN>(k, t, S)));
-    else if (t.mi == 2)
-      FIRAL_CHECK((pk_xtg_launch<AR, 2, 1, WIN>(k, t, S)));
-    else
-      FIRAL_CHECK((pk_xtg_launch<AR, 3, 1, WIN>(k, t, S)));
+    FIRAL_CHECK((cols.part() ? pk_xtg_form<AR, WIN, true>(k, t, S)
+                             : pk_xtg_form<AR, WIN, false>(k, t, S)));
   }
   return reduce_parts_launch<float>((const float*)x->part, (int64_t)d * SC, n_rows > 0 ? S : 0,
                                     shift, B, out, skip, st);
