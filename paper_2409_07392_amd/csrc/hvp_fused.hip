@@ -1178,9 +1178,9 @@ int hvp_fused_launch(Ctx* x, const FusedPlan& p, const double* omega, int64_t n_
 // c = 5, s = 10 27 -> 12.6 us; N = 50,010, d = 100, c = 10, s = 20 202 -> 121 us; N = 200,000, d = 30,
 // c = 10, s = 10 443 -> 109 us; N = 20,000, d = c = 100, s = 2 96 -> 81 us.  Of 330 shapes it was the
 // faster one up to c = 64.  Beyond, a tile holds one probe and a chunk's Gamma step keeps one wave of
-// eight busy; that costs more than G' written and read once a workgroup has about 25 chunks (n s =
-// 100,000): d = 22, c = 128, s = 25, N = 15,957 526 us, row-tiled 391; d = 27, c = 128, s = 13, N = 8101 148,
-// 124; d = 70, c = 105, s = 5, N = 18,352 132, row-tiled 160.  Such calls stay row-tiled.
+// eight busy; that costs more than G' written and read once a workgroup has about 12 chunks (n s =
+// 50,000): d = 22, c = 128, s = 25, N = 15,957 526 us, row-tiled 391; d = 6, c = 128, s = 32, N = 1928 82,
+// 68; d = 62, c = 90, s = 7, N = 6378 65, row-tiled 75.  Such calls stay row-tiled.
 struct Fused64 {
   int D16, pp, n_ct, CP, splits;
   int64_t rps;
@@ -1190,7 +1190,7 @@ static bool fused64_plan(int d, int c, int s, int64_t n_rows, Fused64* p) {
   constexpr int RC = pipe_rc<double>;
   p->D16 = (d + 15) / 16;
   if (p->D16 > 8 || c > kNW * 16 || n_rows <= 0) return false;
-  if (c > kNW * 8 && n_rows > 100000 / s) return false;
+  if (c > kNW * 8 && n_rows > 50000 / s) return false;
   p->pp = std::min(s, kNW * 16 / c);
   p->n_ct = (int)cdiv(s, p->pp);
   p->pp = (int)cdiv(s, p->n_ct);

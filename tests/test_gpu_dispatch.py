@@ -1,6 +1,6 @@
 """Products on both sides of the lines between their kernels, against the FP64 oracle: the packed and
 the row-tiled FP32 form for wide probes at d <= 128 (2048 rows), and the one-pass and the row-tiled
-FP64 form for c > 64 (rows times probes of 100,000).  Normwise; FP32 1e-5 and FP64 1e-12, the bars of
+FP64 form for c > 64 (rows times probes of 50,000).  Normwise; FP32 1e-5 and FP64 1e-12, the bars of
 the same kernels' other tests.
 """
 import numpy as np
@@ -37,5 +37,5 @@ def test_wide_probes_at_the_row_line(d, c, s):
 
 @pytest.mark.parametrize("d,c,s", [(22, 128, 25), (30, 65, 20), (9, 64, 30)])
 def test_fp64_probes_beyond_half_a_tile_at_the_row_line(d, c, s):
-    k = 100000 // s
+    k = 50000 // s
     check(k + 50, d, c, s, (k - 1, k, k + 1, k + 53), "f64", 1e-12)
