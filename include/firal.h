@@ -230,7 +230,8 @@ int firal_profile_end(firal_ctx ctx, double* total_ms, int64_t* launches);
 /* Kernel-variant tuner (the tile plan of extension (2); usable on any context).  Times on this
  * context, for s probes, the product's tilings (the fused single pass with one or two 16-column
  * blocks per wave and a target of 256, 512 or 1024 workgroups, which sets the rows each
- * workgroup covers, wherever its plan fits; the row-tiled kernels) and the PCG step forms
+ * workgroup covers, wherever its plan fits; the packed products of a context that holds them, else
+ * the row-tiled kernels) and the PCG step forms
  * (column-local, separate kernels), keeps the fastest of each for the context and remembers
  * the choice for the process per bucket (precision, d, c, s, n_pool + n_lab rounded up to a
  * power of two); a bucket already tuned is applied without timing.  The context's work blocks

@@ -93,9 +93,9 @@ int autotune(Ctx* x, int s, hipStream_t st, int* choice_out) {
   }
   FIRAL_CHECK(probes_launch(x, 1, 1, s, x->V, st));
   // product: the default path (the fused kernel's first tiling where its plan fits, else the
-  // plane or row-tiled products of the context), the other fused tilings whose plans fit
+  // packed or row-tiled products of the context), the other fused tilings whose plans fit
   // (distinct plans only: the row ranges are capped by the row chunks), then the row-tiled
-  // kernels unless the context takes the plane products
+  // kernels unless the context takes the packed products
   std::vector<int> cands{0};
   std::vector<std::pair<int, int>> plans;   // (column blocks per wave, row ranges)
   for (int ncb_bit = 0; ncb_bit <= 4; ncb_bit += 4)

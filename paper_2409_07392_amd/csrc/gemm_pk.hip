@@ -235,8 +235,9 @@ constexpr size_t pk_xv_lds() {
 // vector instructions issue one per MFMA beside another wave's FP32 MFMA); with bf16 planes the
 // tile's way from L2 and LDS to the matrix cores and G's way to memory.  The products as wholes,
 // before (row-tiled tiles, or transposed operands staged through LDS) and now: d = 256, c = 100, s =
-// 32, N = 200,100 bf16x3 5.57 -> 2.53 ms; s = 16 FP32 4.88 -> 3.68 ms; d = 203, c = 37, s = 7, N =
-// 30,048 FP32 205 -> 159 us; the gradient at d = 256, c = 100, s = 32 FP32 11.0 -> 6.2 ms.
+// 32, N = 200,100 bf16x3 5.58 -> 2.55 ms; d = 203, c = 37, s = 7, N = 30,048 FP32 197 -> 150 us; d =
+// 384, c = 1000, s = 16, N = 1,282,000 FP32 296 -> 281 ms; the gradient at d = 256, c = 100, s = 32 FP32
+// 11.0 -> 6.15 ms.
 // kPkDot: dpart[ct][row] = sum over the tile's columns of G_u (G - alpha) h, G and alpha those of
 // the earlier kPkFlat call on W.
 template <int AR, int MODE>

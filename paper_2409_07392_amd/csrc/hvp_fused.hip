@@ -311,8 +311,8 @@ __global__ __launch_bounds__(kThreads) void k_hvp_fused(
 // row-major X by rows, conflict-free at a row stride of 4 mod 16 floats).  Half the waves take the
 // Gamma step before their products.  The products and sums are those of k_hvp_fused, in its order.
 // What bounds it: the MFMA rate of the SIMDs that hold two of the busy waves (C16 of 8); before, the
-// four barriers a chunk and its LDS reads one at a time: n = 50,000, d = 100, c = 10, s = 20 80 us
-// (5.0 us a chunk) -> 68 us (4.3; its MFMAs 3.3).
+// four barriers a chunk and its LDS reads one at a time: a call at n = 50,000, d = 100, c = 10, s = 20 79
+// us -> 67 us, among others (5.0 -> 4.3 us a chunk; its MFMAs 3.3).
 // Beside FP32 MFMA a SIMD issues about one other vector instruction per MFMA, so the rest of a step
 // is kept short: addresses are a uniform base plus an offset kept per thread, a chunk that ends
 // early is a branch of its own, and the Gamma step is compiled for each c <= 16.
